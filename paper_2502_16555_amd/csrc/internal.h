@@ -10,8 +10,7 @@
 namespace bte {
 
 // Blocking of the batched LU: outer panel width (trailing-update rank); the
-// register-resident sub-panel inside the panel factorization is 8 (FP64) or
-// 16 (FP32) columns wide.
+// panel factorizations take 16 columns at a time.
 constexpr int kNB = 128;
 constexpr int kPanelThreads = 512;
 constexpr int kMaxSwapRows = 2 * kNB;   // rows touched by one panel's interchanges
@@ -229,6 +228,12 @@ struct LuLookAhead {
   int form_overlap = 0;
   hipEvent_t form_ev[2] = {nullptr, nullptr};
 };
+// One FP64 panel with partial pivoting (kernels_panel.hip): rows k0 .. rend - 1
+// (a multiple of 128) of columns k0 .. k0 + 127 of nmat matrices; pivots, the
+// panel's permutation, and the inverses of L11's 16 x 16 diagonal blocks in
+// linv.  xscr: interchange staging, as scratch.
+void launch_panel_f64(double* LU, double* linv, void* xscr, int* piv, int* perm, int* status, int npad, int k0,
+                      int rend, int nmat, hipStream_t s);
 void launch_lu_factor(const DevOps& d, int precision, hipStream_t s, LuTimer* timer = nullptr, int m0 = 0,
                       int count = -1, const LuLookAhead* la = nullptr);
 // A22 -= L21 U12 of the kd = 128 (one panel) or 256 (two panels) columns from

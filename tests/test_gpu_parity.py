@@ -793,6 +793,28 @@ def test_device_factors_match_blocked_restatement(torch, prec):
     s.close()
 
 
+@pytest.mark.parametrize("nr,nth", [(10, 6), (20, 12), (20, 32), (36, 32)])
+def test_fp64_panels_of_every_height_match_restatement(torch, nr, nth):
+    """FP64 panels of every block shape (up to 128, 256, 512, 1024 and 2048 rows: n = 60, 240,
+    640 and 1152 factor panels of each height down to 128) on matrices far from the identity
+    (50 times the usual dt: hundreds of row interchanges), both field signs: identical pivots,
+    factors equal to rounding."""
+    import lu_reference as LR
+    cfg = workloads.small_config(nx=3, nr=nr, nth=nth, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf", dt_frac=0.05)
+    ops = oracle.build_operators(cfg)
+    s = solver(cfg, precision="fp64")
+    E = np.array([1.2e4, -6e3, 0.0])
+    Eg = cuda(torch, E)
+    for x in (0, 1):
+        lu, piv = s.factor_export(Eg, x)
+        ref, ip = LR.factor(LR.pad(S.v_matrix(ops, E[x])), 16, pairs=True)
+        assert (ip != np.arange(len(ip))).sum() > len(ip) // 10
+        assert np.array_equal(piv, ip), x
+        close(lu, ref, 1e-12, (x, "factors"))
+    s.close()
+
+
 @pytest.mark.parametrize("prec", ["mixed_fp32", "mixed_bf16x3", "mixed_bf16"])
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_partial_pivoting_vstep_matches_oracle(torch, case, prec):
