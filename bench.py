@@ -26,7 +26,7 @@ sys.path.insert(0, ROOT)
 MI355X_PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16": 2500.0}
 MI355X_PEAK_HBM_GBS = 8000.0
 
-# HBM bytes of the FP32 trailing update (k_update<float, 16, ...>, K = 128 to 512)
+# HBM bytes of the FP32 trailing update (K = 128 to 512)
 # per launch, averaged over the 15 launches of one factorization at this workload
 # (statically pivoted panels in groups of four: 3 launches of K = 512 beyond a
 # group, and 4 each of K = 128, 256, 384 on the next panel's columns and top rows),
@@ -561,8 +561,19 @@ def main():
     group = _panel_group(main_run)
     upd_flops = _update_flops(npad, 128, nx_total, group)
     n_upd_launches = main_run["update_launches"]
-    achieved = upd_flops / (main_run["ms_update"] * 1e-3) / 1e12
     peak = MI355X_PEAK_TFLOPS[mfma]
+    # FP64 updates are bound by their MFMA rate; the FP32 and BF16 ones run on
+    # 16-bit matrix units (FP32 as three products of split f16 operands) and are
+    # bound by the bytes they move
+    upd_bytes = _update_bytes(npad, 128, nx_total, 8 if args.precision == "fp64" else 4, group)
+    if args.precision == "fp64":
+        upd_roof = {"bound": "mfma", "achieved": upd_flops / (main_run["ms_update"] * 1e-3) / 1e12, "peak": peak,
+                    "unit": "TFLOP/s"}
+    else:
+        upd_roof = {"bound": "hbm", "achieved": upd_bytes * n_upd_launches / (main_run["ms_update"] * 1e-3) / 1e9,
+                    "peak": MI355X_PEAK_HBM_GBS, "unit": "GB/s",
+                    "tflops": upd_flops / (main_run["ms_update"] * 1e-3) / 1e12}
+    upd_roof["frac"] = upd_roof["achieved"] / upd_roof["peak"]
     value = 1000.0 / main_run["ms_per_step"]
     line = {
         "metric": "BTE steps/s at Nx256 Nr64 Ntheta32 (mixed precision step; FP64 step timed beside it)",
@@ -572,12 +583,10 @@ def main():
         "config": {"workload": f"Nx={cfg['nx']} CGL, Nr=64 B-splines (f(vmax)=0), Ntheta=32 GL, n=2048 per point, "
                                f"argon-like sigma, RF E0={cfg['field']['E0']:.1f} V/m, dt=1e-3 T_rf",
                    "precision": args.precision, "nx": cfg["nx"], "nr": 64, "ntheta": 32},
-        "roofline": {"bound": "mfma", "kernel": "k_update (LU trailing update)", "achieved": achieved,
-                     "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
+        "roofline": {**upd_roof, "kernel": "k_update_split (LU trailing update; FP64: k_update)",
                      "traffic": _update_traffic() if args.precision == "mixed_fp32" and npad == 2048 and nx_total == 256
                      else None,
-                     "algorithmic_bytes_per_launch": _update_bytes(npad, 128, nx_total,
-                                                                   8 if args.precision == "fp64" else 4, group),
+                     "algorithmic_bytes_per_launch": upd_bytes,
                      "panels_per_update_group": group,
                      "launches_per_step": n_upd_launches,
                      "avg_launch_ms": main_run["ms_update"] / n_upd_launches},

@@ -60,7 +60,9 @@ typedef enum {
 
 typedef enum {
   BTE_FP64 = 0,           /* FP64 LU (MFMA f64) and FP64 advection                       */
-  BTE_MIXED_FP32 = 1,     /* FP32 LU + FP64 iterative refinement of the V-step residual  */
+  BTE_MIXED_FP32 = 1,     /* FP32 LU + FP64 iterative refinement of the V-step residual
+                           * (groups of four panels: FP32 products from f16 hi + lo
+                           * operands, at least as accurate as FP32 matrix products)   */
   BTE_MIXED_BF16 = 2,     /* as MIXED_FP32, LU trailing updates with bf16 operands
                            * (MFMA bf16, FP32 accumulation)                           */
   BTE_MIXED_BF16X3 = 3,   /* as MIXED_BF16 with operands split a = hi + lo in bf16 and
@@ -404,7 +406,9 @@ bte_status bte_get_timing(bte_handle* h, double* ms_out);
  *   BTE_TUNE_UPDATE_KC: K chunk of the trailing-update tiles staged per LDS
  *     buffer: 16 or 32 (FP32 factors), 8 or 16 (FP64); 0 = default (16).  The
  *     16-chunk FP32 form runs four blocks per CU, the 32-chunk form two.  The
- *     BF16 updates have a fixed chunk of 32 (reported as such).
+ *     BF16 updates have a fixed chunk of 32 (reported as such), and so have the
+ *     FP32 updates of panels in groups of four, whose products run on split f16
+ *     operands (the setting then applies to the other panel groupings only).
  *   BTE_TUNE_FORM_XPB: matrices formed per block of the formation kernel,
  *     1..64; 0 = default (8 for FP32 factors, 16 for FP64).
  *   BTE_TUNE_PANEL_PAIRS: 2 (default), 1 or 0.  1: dense factors take the

@@ -375,6 +375,10 @@ void fill_devops(bte_handle* h) {
   d.lu = h->alloc<char>(nxt * d.npad * d.npad * elt);
   d.xscr = h->alloc<char>(nxt * d.npad * bte::kNB * elt);
   d.linv = h->alloc<char>(nxt * bte::kLinvElems * elt);
+  if (c.precision == BTE_MIXED_FP32) {
+    d.lmax = h->alloc<float>(nxt * d.npad);
+    d.umax = h->alloc<float>(nxt * d.npad);
+  }
   d.piv = h->alloc<int>(nxt * d.npad);
   d.perm = h->alloc<int>(nxt * bte::kMaxPanels * bte::kPermStride);
   d.mirror = h->alloc<int>(nxt);
@@ -1419,6 +1423,7 @@ bte_status bte_set_vsolver(bte_handle* h, int32_t kind, int32_t n_bins, double E
       b.form_xpb = 0;
       b.static_piv = 0;
       b.mirror = nullptr;
+      b.lmax = b.umax = nullptr;
       b.band_kl = 2 * d.nr - 1;
       b.band_ku = 2 * d.nr - 1;
       h->bd = b;
@@ -1477,6 +1482,7 @@ bte_status bte_set_vsolver(bte_handle* h, int32_t kind, int32_t n_bins, double E
     f.form_xpb = 0;
     f.static_piv = 0;   // the bins keep partially pivoted factors
     f.mirror = nullptr;
+    f.lmax = f.umax = nullptr;
     bte::launch_lu_factor(f, lu_prec, nullptr);
     HIP_OK(hipDeviceSynchronize());
     if (fp16) {  // keep the factors in FP16 only: half the bytes per preconditioner solve

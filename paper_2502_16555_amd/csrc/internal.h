@@ -67,6 +67,8 @@ struct DevOps {
   int lu_pairs = 2;             // dense factors: 1 panels in pairs (K = 256 trailing updates), 2 statically
                                 // pivoted factors in groups of four (K = 512; pairs otherwise), 0 single panels
   void* linv = nullptr;        // [nx_total][kLinvElems] of T: inverses of L11's diagonal blocks, of L11, of U11
+  float* lmax = nullptr;       // [nx_total][npad] groups of four: max |L| of every row over the group's panels so far
+  float* umax = nullptr;       // [nx_total][npad] and max |U| of every column (the split update's scales)
   int* piv = nullptr;          // [nx_total][npad]
   int* perm = nullptr;         // [nx_total][kMaxPanels][kPermStride] row permutation of every panel
   double* E = nullptr;         // [nx_total]
@@ -236,14 +238,18 @@ void launch_panel_f64(double* LU, double* linv, void* xscr, int* piv, int* perm,
                       int rend, int nmat, hipStream_t s);
 void launch_lu_factor(const DevOps& d, int precision, hipStream_t s, LuTimer* timer = nullptr, int m0 = 0,
                       int count = -1, const LuLookAhead* la = nullptr);
-// A22 -= L21 U12 of the kd = 128 (one panel) or 256 (two panels) columns from
-// k0 for nmat matrices (mtr x mtc tiles of 128, column tiles tj0 .. tj0 + mtc - 1
-// of the trailing matrix from k0 + kd): kind 0 FP64, 1 FP32, 2 FP32 with bf16
-// operands, 3 FP32 with split bf16 operands; alt_kc: K chunk 32 (FP32) / 8
-// (FP64) instead of 16.  lrow: that many more tiles in the first tile row, after
-// the rectangle's mtc columns (an L-shaped tile set in one launch).
+// A22 -= L21 U12 of the kd = 128 j (j panels) columns from k0 for nmat matrices
+// (mtr x mtc tiles of 128, column tiles tj0 .. tj0 + mtc - 1 of the trailing
+// matrix from k0 + kd): kind 0 FP64, 1 FP32, 2 FP32 with bf16 operands, 3 FP32
+// with split bf16 operands; alt_kc: K chunk 32 (FP32) / 8 (FP64) instead of 16.
+// lrow: that many more tiles in the first tile row, after the rectangle's mtc
+// columns (an L-shaped tile set in one launch).  rmax, cmax ([nmat][npad], kind
+// 1): max |L| of every row and max |U| of every column over those kd columns
+// and rows, with which the FP32 products run on split f16 operands (kinds 0 and
+// 1 without them: kd <= 256).
 void launch_update(int kind, void* LU, int npad, int k0, int mtr, int mtc, int tj0, int nmat, bool alt_kc,
-                   hipStream_t s, int kd = kNB, int lrow = 0);
+                   hipStream_t s, int kd = kNB, int lrow = 0, const float* rmax = nullptr,
+                   const float* cmax = nullptr);
 // X = LU^-1 B (or LU^-T B with transpose), rows of length npad, FP64 right-hand sides.
 void launch_lu_solve(const DevOps& d, int precision, bool transpose, const double* Bin, double* Xout,
                      bool accumulate, bool check_done, hipStream_t s);

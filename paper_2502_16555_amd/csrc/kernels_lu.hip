@@ -843,8 +843,11 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
   if (__syncthreads_or(nonfinite) && tid == 0) atomicOr(status, kStNonFinite);
 }
 
+// lmax (may be NULL): max |L21| of every row, over this panel (first) or with
+// the value there (the group's earlier panels)
 __global__ __launch_bounds__(256, 2) void k_l21_mfma(float* __restrict__ LU, const float* __restrict__ linv,
-                                                     int npad, int k0, int ntiles, int nmat) {
+                                                     int npad, int k0, int ntiles, int nmat,
+                                                     float* __restrict__ lmax, int first) {
   int mat, tile;
   xcd_map(blockIdx.x, ntiles, nmat, &mat, &tile);
   if (mat >= nmat) return;
@@ -893,6 +896,28 @@ __global__ __launch_bounds__(256, 2) void k_l21_mfma(float* __restrict__ LU, con
     for (int cb = 0; cb < 8; ++cb)
       *reinterpret_cast<float4*>(A + (size_t)(k0 + 16 * cb + li) * npad + r0 + 32 * w + 16 * rb + 4 * lk) =
           make_float4(acc[rb][cb][0], acc[rb][cb][1], acc[rb][cb][2], acc[rb][cb][3]);
+  if (lmax) {
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      float m[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        float v = 0.0f;
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) v = fmaxf(v, fabsf(acc[rb][cb][t]));
+        m[t] = row16_max(v);
+      }
+      if (li == 0) {
+        float4* o = reinterpret_cast<float4*>(lmax + (size_t)mat * npad + r0 + 32 * w + 16 * rb + 4 * lk);
+        float4 v = make_float4(m[0], m[1], m[2], m[3]);
+        if (!first) {
+          const float4 p = *o;
+          v = make_float4(fmaxf(v.x, p.x), fmaxf(v.y, p.y), fmaxf(v.z, p.z), fmaxf(v.w, p.w));
+        }
+        *o = v;
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1021,7 +1046,9 @@ __global__ __launch_bounds__(128) void k_l11inv(const T* __restrict__ LU, T* __r
 template <typename T, bool FROM_W = false>
 __global__ __launch_bounds__(256, 2) void k_u12(T* __restrict__ LU, const T* __restrict__ linv,
                                                const int* __restrict__ perm, T* __restrict__ xscr, int npad, int k0,
-                                               int nct, int nmat) {
+                                               int nct, int nmat, float* __restrict__ umax = nullptr, int first = 0) {
+  // umax (may be NULL, FP32): max |U12| of every column, over this panel (first)
+  // or with the value there (the group's earlier panels)
   using V = typename Vec4<T>::type;
   constexpr int PER = Vec4<T>::per;
   // LDS rows of the K chunk (64 banks of 4 bytes).  FP32: a pitch of 144 puts
@@ -1160,6 +1187,28 @@ __global__ __launch_bounds__(256, 2) void k_u12(T* __restrict__ LU, const T* __r
     if (ch + 1 < NCH) {
       store(buf ^ 1);
       __syncthreads();
+    }
+  }
+  if constexpr (F32 && !FROM_W) {
+    if (umax) {   // a column's four lane groups, then its two wave rows through LDS
+      __shared__ float s_max[2][128];
+#pragma unroll
+      for (int bj = 0; bj < 4; ++bj) {
+        float v = 0.0f;
+#pragma unroll
+        for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+          for (int it = 0; it < 4; ++it) v = fmaxf(v, fabsf(static_cast<float>(acc[bi][bj][it])));
+        v = fmaxf(v, __shfl_xor(v, 16));
+        v = fmaxf(v, __shfl_xor(v, 32));
+        if (lk == 0) s_max[rsel][wc + bj * 16 + li] = v;
+      }
+      __syncthreads();
+      if (tid < 128) {
+        float v = fmaxf(s_max[0][tid], s_max[1][tid]);
+        float* o = umax + (size_t)mat * npad + c0 + tid;
+        *o = first ? v : fmaxf(v, *o);
+      }
     }
   }
   // every gather of the tile's columns was consumed before the last barrier.
@@ -1775,11 +1824,11 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
     if (tm) ++tm->launches;
   };
   // statically pivoted FP32 panels: the diagonal block and L21 (on stream st)
-  auto static_panel = [&](int k0, int rend, hipStream_t st) {
+  auto static_panel = [&](int k0, int rend, hipStream_t st, float* lmax = nullptr, int first = 0) {
     if constexpr (std::is_same<T, float>::value) {
       k_diag_static<<<nmat, 256, 0, st>>>(LU, li, piv, perm, d.status, d.npad, k0);
       const int nt = (rend - k0 - NB) / NB;   // row tiles of L21 (rend, k0 multiples of 128)
-      if (nt > 0) k_l21_mfma<<<xcd_grid(nt, nmat), 256, 0, st>>>(LU, li, d.npad, k0, nt, nmat);
+      if (nt > 0) k_l21_mfma<<<xcd_grid(nt, nmat), 256, 0, st>>>(LU, li, d.npad, k0, nt, nmat, lmax, first);
     }
   };
   if (quads) {
@@ -1790,7 +1839,10 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
     // straight from its rows; after it, either the next panel gets the updates
     // of panels g0..p the same way, or, after the group's last panel, the
     // columns beyond the group get all four (K = 512).  A group that does not
-    // fit at the end takes single panels.
+    // fit at the end takes single panels.  The FP32 updates run on split f16
+    // operands, scaled by the largest entries of L's rows and U's columns.
+    float* lm = kind == 1 ? d.lmax + (size_t)m0 * d.npad : nullptr;
+    float* um = kind == 1 ? d.umax + (size_t)m0 * d.npad : nullptr;
     for (int p = 0; p < np; ++p) {
       const int k0 = p * NB;
       const int g0 = p / 4 * 4;
@@ -1798,7 +1850,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
       const int j = full ? p - g0 : 0;
       const bool rec = tm && p < P;
       if (rec) mark(1, p, 0, s);
-      static_panel(k0, d.npad, s);
+      static_panel(k0, d.npad, s, lm, j == 0);
       const int rest = d.npad - k0 - NB;
       const int nct = rest / 128;
       if (rec) {
@@ -1807,22 +1859,21 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
         mark(2, p, 1, s);
         mark(3, p, 0, s);
       }
-      if (rest > 0) k_u12<T><<<xcd_grid(nct, nmat), 256, 0, s>>>(LU, li, perm, xs, d.npad, k0, nct, nmat);
+      if (rest > 0)
+        k_u12<T><<<xcd_grid(nct, nmat), 256, 0, s>>>(LU, li, perm, xs, d.npad, k0, nct, nmat, um, j == 0);
       if (rec) {
         mark(3, p, 1, s);
         mark(0, p, 0, s);
       }
       const int mtr = rest / 128;
       if (mtr > 0) {
-        if (full && j < 3) {
-          // the next panel's columns, and its top rows beyond it (first tile row)
-          launch_update(kind, LU, d.npad, g0 * NB, mtr, 1, 0, nmat, alt_kc, s, (j + 1) * NB, nct - 1);
-          if (tm) ++tm->launches;
-        } else if (full) {
-          update(g0 * NB, mtr, nct, 4 * NB);       // the columns beyond the group
-        } else {
-          update(k0, mtr, nct, NB);
-        }
+        // a group's first three panels: the next panel's columns, and its top
+        // rows beyond it (first tile row); then the columns beyond the group; a
+        // panel after the last full group by itself
+        const bool part = full && j < 3;
+        launch_update(kind, LU, d.npad, full ? g0 * NB : k0, mtr, part ? 1 : nct, 0, nmat, alt_kc, s, (j + 1) * NB,
+                      part ? nct - 1 : 0, lm, um);
+        if (tm) ++tm->launches;
       }
       if (rec) {
         mark(0, p, 1, s);

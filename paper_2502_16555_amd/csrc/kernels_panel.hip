@@ -46,11 +46,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// v max of the lane that DPP control CTRL names (0 for none)
-template <int CTRL>
-__device__ __forceinline__ unsigned dpp_max(unsigned v) {
-  return max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false)));
-}
 // maximum over the wavefront of 32-bit unsigned keys; uniform result
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   v = dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(v))));

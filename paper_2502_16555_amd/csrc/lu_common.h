@@ -96,6 +96,17 @@ __device__ inline double wave_max(double v) {
   const double m0 = r1 > r0 ? r1 : r0, m1 = r3 > r2 ? r3 : r2;
   return m1 > m0 ? m1 : m0;
 }
+// v max of the lane that DPP control CTRL names (0 for none)
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp_max(unsigned v) {
+  return max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false)));
+}
+// maximum over the 16 lanes of a DPP row of non-negative floats (whose bits
+// order like the values)
+__device__ __forceinline__ float row16_max(float v) {
+  const unsigned u = __float_as_uint(v);
+  return __uint_as_float(dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(u)))));
+}
 // maximum over the wavefront of 64-bit unsigned keys; uniform result
 template <int CTRL>
 __device__ inline unsigned long long dpp_u64(unsigned long long v) {

@@ -867,6 +867,31 @@ def test_static_pivoting_factors_match_restatement(torch):
     s.close()
 
 
+@pytest.mark.parametrize("nr,nth", [(20, 32), (36, 32)])
+def test_split_operand_updates_reproduce_the_matrix(torch, nr, nth):
+    """Statically pivoted FP32 factors with the trailing updates on split f16 operands, for five
+    panels (a group of four, then one) and nine (two groups, then one), both field signs, at the
+    usual step and at 50 times it (U entries over two decades larger): L U gives back the matrix to
+    FP32 rounding.  Every entry takes the rounding at formation and at most one per panel, each
+    2^-24 of the entries met on the way (below 4 here: no growth), and inner roundings of the same
+    size; in the Frobenius norm 32 of them bound it."""
+    for dt_frac in (1e-3, 0.05):
+        cfg = workloads.small_config(nx=3, nr=nr, nth=nth, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                     field_kind="rf", dt_frac=dt_frac)
+        ops = oracle.build_operators(cfg)
+        s = solver(cfg, precision="mixed_fp32")
+        E = np.array([1.2e4, -6e3, 0.0])
+        Eg = cuda(torch, E)
+        for x in range(3):
+            lu, _ = s.factor_export(Eg, x)
+            A = np.eye(len(lu))
+            n = ops.nr * ops.nth
+            A[:n, :n] = S.v_matrix(ops, abs(E[x]))   # negative fields as their angular mirror image
+            R = A - (np.tril(lu, -1) + np.eye(len(lu))) @ np.triu(lu)
+            assert np.linalg.norm(R) < 32 * 2.0 ** -24 * np.linalg.norm(A), (dt_frac, x)
+        s.close()
+
+
 def test_static_pivoting_is_rejected_for_fp64(torch):
     from paper_2502_16555_amd import _lib
     s = solver(CASES["ragged"](), precision="fp64")
