@@ -496,34 +496,212 @@ __global__ __launch_bounds__(NT) void k_panel(float* __restrict__ LU, int* __res
 //                  factored by one wavefront in registers, its U12 rows by
 //                  forward substitution, the trailing update on MFMA); then
 //                  X = U11^-1 by 16 x 16 blocks in LDS (the diagonal blocks,
-//                  then seven levels of off-diagonal blocks); X goes row-major
-//                  into the matrix's linv slot after L11's inverses, and the
-//                  inverses of L11's eight diagonal blocks (k_dinv's output)
-//                  are formed beside those of U11's, by the other 128 threads,
-//                  and L11^-1 (k_l11inv's output) by the same levels after X;
+//                  then seven levels of off-diagonal blocks), the inverses of
+//                  L11's eight diagonal blocks beside those of U11's, by the
+//                  other 128 threads, and L11^-1 by the same levels after X;
+//                  both go into the matrix's linv slot for L21 and U12, and
+//                  their triangles into tinv for the solves;
 //   k_l21_mfma     L21 = A21 X for 128 rows per block: one MFMA product (K =
 //                  128, the zero blocks of X skipped), A21 straight from HBM.
 // ---------------------------------------------------------------------------
 constexpr float kStaticPivotRel = 9.5367431640625e-07f;   // 2^-20
 
+// LDS of the diagonal-block kernels.  During the factorization the block sits
+// column-major in the X region (sA[c][r]) and the U region holds the current
+// step's MFMA operands; for the inverses the U region holds U11 row-major and
+// the X region X = U11^-1 transposed.
+struct DiagLds {
+  __align__(16) float u[NB][NB + 4];
+  __align__(16) float xt[NB][NB + 4];
+  float t[8][16][17];              // a level's sums, per block
+  __align__(16) float l11[2][16][20];   // rows as 16-byte vectors, per step parity
+  float yd[8][16][16];             // inverses of L11's diagonal blocks
+  float red[4];
+};
+
+// X = U11^-1 and Y = L11^-1 of the factored block in s.xt (column-major): tinv
+// holds both triangles column-major (X on and above the diagonal, Y's strict
+// lower part below it, its unit diagonal implied; for the solves); xo (may be
+// NULL) X row-major, yo (may be NULL) Y column-major.
+__device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, float* __restrict__ tinv,
+                                                                    float* __restrict__ xo, float* __restrict__ yo) {
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  float (*sU)[NB + 4] = s.u;
+  float (*sXT)[NB + 4] = s.xt;
+  float (*sA)[NB + 4] = s.xt;
+  float (*sT)[16][17] = s.t;
+  float (*sYd)[16][16] = s.yd;
+  // ---- X = U11^-1 by 16 x 16 blocks (X upper triangular, kept transposed in
+  // LDS, XT[col][row]): the diagonal blocks X_bb = U_bb^-1 by back substitution,
+  // then by levels d = 1..7 the blocks X_{a,a+d} = -X_aa sum_{m=a+1}^{a+d}
+  // U_am X_{m,a+d}; the blocks of one level are independent.  U11 goes
+  // row-major into sU, the strict lower parts of L11's diagonal blocks into sT
+  // (which the levels use only later), then sXT is cleared.
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {   // 4 x 4 blocks, transposed in registers
+    const int i4 = 4 * (tid & 31), j4 = 4 * (tid >> 5) + 32 * u;
+    float w[4][4];   // w[jj][ii] = A[i4 + ii][j4 + jj]
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const float4 v = *reinterpret_cast<const float4*>(&sA[j4 + jj][i4]);
+      w[jj][0] = v.x;
+      w[jj][1] = v.y;
+      w[jj][2] = v.z;
+      w[jj][3] = v.w;
+    }
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+      const int i = i4 + ii;
+      float o[4];
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) o[jj] = w[jj][ii];   // L's strict lower part rides below U
+      *reinterpret_cast<float4*>(&sU[i][j4]) = make_float4(o[0], o[1], o[2], o[3]);
+      if ((i >> 4) == (j4 >> 4)) {
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+          if (i > j4 + jj) sT[i >> 4][i & 15][(j4 + jj) & 15] = w[jj][ii];
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < NB * NB / 4; e += 256)
+    *reinterpret_cast<float4*>(&sXT[e >> 5][(e & 31) * 4]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  __syncthreads();
+  if (tid < NB) {   // thread (b, c): column c of X_bb
+    const int b = tid >> 4, c = tid & 15, o = 16 * b;
+    float xv[16];
+#pragma unroll
+    for (int i = 15; i >= 0; --i) {
+      float v = (i == c) ? 1.0f : 0.0f;
+#pragma unroll
+      for (int m2 = i + 1; m2 < 16; ++m2) v = fmaf(-sU[o + i][o + m2], xv[m2], v);
+      xv[i] = v / sU[o + i][o + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sXT[o + c][o + i] = xv[i];
+  } else {          // thread (b, c): column c of L_bb^-1 (unit lower) by forward substitution
+    const int b = (tid - NB) >> 4, c = tid & 15;
+    float x[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = (r == c) ? 1.0f : 0.0f;
+#pragma unroll
+    for (int r = 1; r < 16; ++r)
+#pragma unroll
+      for (int k = 0; k < r; ++k) x[r] -= sT[b][r][k] * x[k];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sYd[b][r][c] = x[r];
+  }
+  __syncthreads();
+  // levels on MFMA, the blocks of a level spread over the wavefronts: T_ab into
+  // sT (lane (li, lk) holds rows 4 lk.. of column li), then X_{ab,b} = -X_aa T_ab
+  // from sT, written transposed
+  for (int d = 1; d < 8; ++d) {
+    for (int ab = wid; ab + d < 8; ab += 4) {
+      const int b = ab + d;
+      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int m2 = ab + 1; m2 <= b; ++m2)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          t = Mma<float>::step(sU[16 * ab + li][16 * m2 + 4 * q4 + lk], sXT[16 * b + li][16 * m2 + 4 * q4 + lk], t);
+#pragma unroll
+      for (int it = 0; it < 4; ++it) sT[ab][4 * lk + it][li] = t[it];
+    }
+    __syncthreads();
+    for (int ab = wid; ab + d < 8; ab += 4) {
+      const int b = ab + d;
+      f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        x = Mma<float>::step(sXT[16 * ab + 4 * q4 + lk][16 * ab + li], sT[ab][4 * q4 + lk][li], x);
+      *reinterpret_cast<float4*>(&sXT[16 * b + li][16 * ab + 4 * lk]) = make_float4(-x[0], -x[1], -x[2], -x[3]);
+    }
+    __syncthreads();
+  }
+  // X column-major for the solves (the zeros below its diagonal are filled with
+  // Y below), and row-major, 4 x 4 blocks transposed in registers
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = tid + 256 * u, k = e >> 5, i4 = (e & 31) * 4;
+    if (i4 <= k) *reinterpret_cast<float4*>(tinv + (size_t)k * NB + i4) = *reinterpret_cast<const float4*>(&sXT[k][i4]);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (!xo) break;
+    const int k4 = 4 * (tid & 31), c4 = 4 * (tid >> 5) + 32 * u;
+    float4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float4*>(&sXT[c4 + j][k4]);
+    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 0) * NB + c4) = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
+    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 1) * NB + c4) = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
+    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 2) * NB + c4) = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
+    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 3) * NB + c4) = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
+  }
+  // ---- Y = L11^-1 (in place of k_l11inv) by the same levels: Y_bb from sYd,
+  // then Y_{a+d,a} = -Y_{a+d,a+d} sum_{m=a}^{a+d-1} L_{a+d,m} Y_{m,a}, with L's
+  // strict lower part in sU and Y kept transposed in the X region (zeros above
+  // its diagonal); Y leaves column-major after the diagonal-block inverses
+  __syncthreads();
+  for (int e = tid; e < NB * NB / 4; e += 256) {   // YT row k: Y_bb's column k mod 16 in block b, zeros elsewhere
+    const int k = e >> 5, i4 = (e & 31) * 4, b = k >> 4;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if ((i4 >> 4) == b) {
+      const int r = i4 & 15, c = k & 15;
+      v = make_float4(sYd[b][r][c], sYd[b][r + 1][c], sYd[b][r + 2][c], sYd[b][r + 3][c]);
+    }
+    *reinterpret_cast<float4*>(&sXT[k][i4]) = v;
+  }
+  __syncthreads();
+  for (int d = 1; d < 8; ++d) {
+    for (int a = wid; a + d < 8; a += 4) {
+      const int r = a + d;
+      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int m2 = a; m2 < r; ++m2)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          t = Mma<float>::step(sU[16 * r + li][16 * m2 + 4 * q4 + lk], sXT[16 * a + li][16 * m2 + 4 * q4 + lk], t);
+#pragma unroll
+      for (int it = 0; it < 4; ++it) sT[a][4 * lk + it][li] = t[it];
+    }
+    __syncthreads();
+    for (int a = wid; a + d < 8; a += 4) {
+      const int r = a + d;
+      f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        x = Mma<float>::step(sXT[16 * r + 4 * q4 + lk][16 * r + li], sT[a][4 * q4 + lk][li], x);
+      *reinterpret_cast<float4*>(&sXT[16 * a + li][16 * r + 4 * lk]) = make_float4(-x[0], -x[1], -x[2], -x[3]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = tid + 256 * u, k = e >> 5, i4 = (e & 31) * 4;
+    const float4 v = *reinterpret_cast<const float4*>(&sXT[k][i4]);
+    if (yo) *reinterpret_cast<float4*>(yo + (size_t)k * NB + i4) = v;   // column-major: (i, k) at k NB + i
+    float* t = tinv + (size_t)k * NB + i4;
+    if (i4 > k) {
+      *reinterpret_cast<float4*>(t) = v;
+    } else if (i4 + 3 > k) {   // the vector that holds the diagonal (written above by this thread)
+      if (i4 + 1 > k) t[1] = v.y;
+      if (i4 + 2 > k) t[2] = v.z;
+      t[3] = v.w;
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, float* __restrict__ linv,
-                                                     int* __restrict__ piv, int* __restrict__ perm,
+                                                     float* __restrict__ tinv, int* __restrict__ piv, int* __restrict__ perm,
                                                      int* __restrict__ status, int npad, int k0) {
   const int mat = blockIdx.x;
   float* A = LU + (size_t)mat * npad * npad;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
-  // LDS: two 128 x 132 regions and the level sums.  During the factorization
-  // the block sits column-major in the second region (sA[c][r]) and the first
-  // holds the current step's MFMA operands; afterwards the first holds U11
-  // row-major (sU) and the second X = U11^-1 transposed (sXT).
-  __shared__ __align__(16) float sU[NB][NB + 4];
-  __shared__ __align__(16) float sXT[NB][NB + 4];
-  __shared__ float sT[8][16][17];   // a level's sums, per block
-  __shared__ __align__(16) float sL11[2][16][20];   // rows as 16-byte vectors, per step parity
-  __shared__ float sYd[8][16][16];                // inverses of L11's diagonal blocks
-  __shared__ float s_red[4];
-  float (*sA)[NB + 4] = sXT;
+  __shared__ DiagLds s_all;
+  float (*sU)[NB + 4] = s_all.u;
+  float (*sA)[NB + 4] = s_all.xt;
+  float (*sL11)[16][20] = s_all.l11;
+  float* s_red = s_all.red;
   constexpr int LQ = NB + 16;   // operand rows: lanes li + 16 lk fall on distinct banks
   // per step parity p: rows 32 p .. 32 p + 15 hold -L[r][c0 + k] (k = row),
   // rows 32 p + 16 .. 32 p + 31 U[c0 + k][c]
@@ -694,153 +872,24 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
     pm[1 + kMaxSwapRows + tid] = k0 + tid;
     if (tid == 0) pm[0] = NB;
   }
-  // ---- X = U11^-1 by 16 x 16 blocks (X upper triangular, kept transposed in
-  // LDS, XT[col][row]): the diagonal blocks X_bb = U_bb^-1 by back substitution,
-  // then by levels d = 1..7 the blocks X_{a,a+d} = -X_aa sum_{m=a+1}^{a+d}
-  // U_am X_{m,a+d}; the blocks of one level are independent.  U11 goes
-  // row-major into sU, the strict lower parts of L11's diagonal blocks into sT
-  // (which the levels use only later), then sXT is cleared.
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {   // 4 x 4 blocks, transposed in registers
-    const int i4 = 4 * (tid & 31), j4 = 4 * (tid >> 5) + 32 * u;
-    float w[4][4];   // w[jj][ii] = A[i4 + ii][j4 + jj]
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const float4 v = *reinterpret_cast<const float4*>(&sA[j4 + jj][i4]);
-      w[jj][0] = v.x;
-      w[jj][1] = v.y;
-      w[jj][2] = v.z;
-      w[jj][3] = v.w;
-    }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int i = i4 + ii;
-      float o[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) o[jj] = w[jj][ii];   // L's strict lower part rides below U
-      *reinterpret_cast<float4*>(&sU[i][j4]) = make_float4(o[0], o[1], o[2], o[3]);
-      if ((i >> 4) == (j4 >> 4)) {
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-          if (i > j4 + jj) sT[i >> 4][i & 15][(j4 + jj) & 15] = w[jj][ii];
-      }
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < NB * NB / 4; e += 256)
-    *reinterpret_cast<float4*>(&sXT[e >> 5][(e & 31) * 4]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  __syncthreads();
-  if (tid < NB) {   // thread (b, c): column c of X_bb
-    const int b = tid >> 4, c = tid & 15, o = 16 * b;
-    float xv[16];
-#pragma unroll
-    for (int i = 15; i >= 0; --i) {
-      float v = (i == c) ? 1.0f : 0.0f;
-#pragma unroll
-      for (int m2 = i + 1; m2 < 16; ++m2) v = fmaf(-sU[o + i][o + m2], xv[m2], v);
-      xv[i] = v / sU[o + i][o + i];
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sXT[o + c][o + i] = xv[i];
-  } else {          // thread (b, c): column c of L_bb^-1 (unit lower) by forward substitution
-    const int b = (tid - NB) >> 4, c = tid & 15;
-    float x[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = (r == c) ? 1.0f : 0.0f;
-#pragma unroll
-    for (int r = 1; r < 16; ++r)
-#pragma unroll
-      for (int k = 0; k < r; ++k) x[r] -= sT[b][r][k] * x[k];
-    float* out = linv + (size_t)mat * kLinvElems + b * 256;   // [b][r][c] row-major
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      out[r * 16 + c] = x[r];
-      sYd[b][r][c] = x[r];
-    }
-  }
-  __syncthreads();
-  // levels on MFMA, the blocks of a level spread over the wavefronts: T_ab into
-  // sT (lane (li, lk) holds rows 4 lk.. of column li), then X_{ab,b} = -X_aa T_ab
-  // from sT, written transposed
-  for (int d = 1; d < 8; ++d) {
-    for (int ab = wid; ab + d < 8; ab += 4) {
-      const int b = ab + d;
-      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int m2 = ab + 1; m2 <= b; ++m2)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          t = Mma<float>::step(sU[16 * ab + li][16 * m2 + 4 * q4 + lk], sXT[16 * b + li][16 * m2 + 4 * q4 + lk], t);
-#pragma unroll
-      for (int it = 0; it < 4; ++it) sT[ab][4 * lk + it][li] = t[it];
-    }
-    __syncthreads();
-    for (int ab = wid; ab + d < 8; ab += 4) {
-      const int b = ab + d;
-      f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        x = Mma<float>::step(sXT[16 * ab + 4 * q4 + lk][16 * ab + li], sT[ab][4 * q4 + lk][li], x);
-      *reinterpret_cast<float4*>(&sXT[16 * b + li][16 * ab + 4 * lk]) = make_float4(-x[0], -x[1], -x[2], -x[3]);
-    }
-    __syncthreads();
-  }
-  // X row-major: 4 x 4 blocks transposed in registers
-  float* xo = linv + (size_t)mat * kLinvElems + kLinvXOff;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int k4 = 4 * (tid & 31), c4 = 4 * (tid >> 5) + 32 * u;
-    float4 v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float4*>(&sXT[c4 + j][k4]);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 0) * NB + c4) = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 1) * NB + c4) = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 2) * NB + c4) = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 3) * NB + c4) = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
-  }
-  // ---- Y = L11^-1 (in place of k_l11inv) by the same levels: Y_bb from sYd,
-  // then Y_{a+d,a} = -Y_{a+d,a+d} sum_{m=a}^{a+d-1} L_{a+d,m} Y_{m,a}, with L's
-  // strict lower part in sU and Y kept transposed in the X region (zeros above
-  // its diagonal); Y leaves column-major after the diagonal-block inverses
-  __syncthreads();
-  for (int e = tid; e < NB * NB / 4; e += 256) {   // YT row k: Y_bb's column k mod 16 in block b, zeros elsewhere
-    const int k = e >> 5, i4 = (e & 31) * 4, b = k >> 4;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if ((i4 >> 4) == b) {
-      const int r = i4 & 15, c = k & 15;
-      v = make_float4(sYd[b][r][c], sYd[b][r + 1][c], sYd[b][r + 2][c], sYd[b][r + 3][c]);
-    }
-    *reinterpret_cast<float4*>(&sXT[k][i4]) = v;
-  }
-  __syncthreads();
-  for (int d = 1; d < 8; ++d) {
-    for (int a = wid; a + d < 8; a += 4) {
-      const int r = a + d;
-      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int m2 = a; m2 < r; ++m2)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          t = Mma<float>::step(sU[16 * r + li][16 * m2 + 4 * q4 + lk], sXT[16 * a + li][16 * m2 + 4 * q4 + lk], t);
-#pragma unroll
-      for (int it = 0; it < 4; ++it) sT[a][4 * lk + it][li] = t[it];
-    }
-    __syncthreads();
-    for (int a = wid; a + d < 8; a += 4) {
-      const int r = a + d;
-      f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        x = Mma<float>::step(sXT[16 * r + 4 * q4 + lk][16 * r + li], sT[a][4 * q4 + lk][li], x);
-      *reinterpret_cast<float4*>(&sXT[16 * a + li][16 * r + 4 * lk]) = make_float4(-x[0], -x[1], -x[2], -x[3]);
-    }
-    __syncthreads();
-  }
-  float* yo = linv + (size_t)mat * kLinvElems + 8 * 256;   // column-major: (i, k) at k NB + i
+  diag_inverses(s_all, tinv + ((size_t)mat * (npad / NB) + k0 / NB) * NB * NB,
+                linv + (size_t)mat * kLinvElems + kLinvXOff, linv + (size_t)mat * kLinvElems + 8 * 256);
+  if (__syncthreads_or(nonfinite) && tid == 0) atomicOr(status, kStNonFinite);
+}
+
+// The triangles' inverses (diag_inverses) of every diagonal block of partially
+// pivoted FP32 factors, one block per panel and matrix, after the factorization.
+__global__ __launch_bounds__(256) void k_diag_inv(const float* __restrict__ LU, float* __restrict__ tinv, int npad) {
+  const int k0 = blockIdx.x * NB, mat = blockIdx.y, tid = threadIdx.x;
+  const float* A = LU + (size_t)mat * npad * npad;
+  __shared__ DiagLds s;
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
-    const int e = tid + 256 * u, k = e >> 5, i4 = (e & 31) * 4;
-    *reinterpret_cast<float4*>(yo + (size_t)k * NB + i4) = *reinterpret_cast<const float4*>(&sXT[k][i4]);
+    const int e = tid + 256 * u, c = e >> 5, r4 = (e & 31) * 4;
+    *reinterpret_cast<float4*>(&s.xt[c][r4]) = *reinterpret_cast<const float4*>(A + (size_t)(k0 + c) * npad + k0 + r4);
   }
-  if (__syncthreads_or(nonfinite) && tid == 0) atomicOr(status, kStNonFinite);
+  __syncthreads();
+  diag_inverses(s, tinv + ((size_t)mat * gridDim.x + blockIdx.x) * NB * NB, nullptr, nullptr);
 }
 
 // lmax (may be NULL): max |L21| of every row, over this panel (first) or with
@@ -1444,104 +1493,130 @@ __global__ __launch_bounds__(256) void k_perm_lp(T* __restrict__ LU, const int* 
 }
 
 // ---------------------------------------------------------------------------
-// One wavefront's triangular solve with a 128 x 128 diagonal block staged in
-// LDS; v0 / v1 hold rows lane / 64 + lane and each solved value is passed on by
-// a lane read.  FWD: ascending (lower triangular), else descending (upper);
-// SCALE: a value is multiplied by the reciprocal of its diagonal entry (s_rc)
-// before it is passed on (non-unit diagonal); TR: the block is used
+// FP64 factors: one wavefront's triangular solve with a 128 x 128 diagonal block
+// staged in LDS; v0 / v1 hold rows lane / 64 + lane and each solved value is
+// passed on by a lane read.  FWD: ascending (lower triangular), else descending
+// (upper); SCALE: a value is multiplied by the reciprocal of its diagonal entry
+// (s_rc) before it is passed on (non-unit diagonal); TR: the block is used
 // transposed.  The staged block holds only the strict triangle that the chain
 // reads, with zeros elsewhere, so every step updates all rows without a mask
 // (a finished row gets exactly zero).  A scaled row keeps its unscaled value
 // to the end and is multiplied once after the chain, giving the same product
-// as scaling it at its own step.  For FP32 and FP16 factors the entries the
-// chain needs are read from LDS in chunks of 4 pivots with the next chunk in
-// flight, so that the sequential chain does not wait on an LDS read at every
-// step; the two halves of the block are separate loops, so that the register
-// holding the current pivot is known at compile time and the half of the rows
-// that a half of the pivots cannot reach is skipped.
+// as scaling it at its own step.
 // ---------------------------------------------------------------------------
-template <typename T, bool FWD, bool SCALE, bool TR, int H>
-__device__ __attribute__((always_inline)) inline void diag_half(const T (*sD)[NB + 1], const double* s_rc,
-                                                                int lane, double& v0, double& v1) {
-  // pivots 64 H .. 64 H + 63, whose values live in v0 (H = 0) or v1 (H = 1);
-  // the entries of 4 pivots are in registers while those of the next 4 load
-  constexpr int CH = 4;
-  constexpr int base = 64 * H;
-  constexpr bool R0 = FWD ? H == 0 : true;   // rows 0 .. 63 below / above these pivots
-  constexpr bool R1 = FWD ? true : H == 1;   // rows 64 .. 127
-  T c0[CH], c1[CH], n0[CH], n1[CH];
-  double q[CH], nq[CH];
-  auto ld = [&](T (&a)[CH], T (&b)[CH], double (&r)[CH], int i0) {
+template <bool FWD, bool SCALE, bool TR>
+__device__ __attribute__((always_inline)) inline void diag_chain(const double (*sD)[NB + 1], const double* s_rc,
+                                                                 int lane, double& v0, double& v1) {
+  constexpr int ST = 4;   // steps whose entries are read from LDS together, one group ahead of their use
+  const double rc0 = SCALE ? s_rc[lane] : 1.0, rc1 = SCALE ? s_rc[64 + lane] : 1.0;
+  // the steps whose source is src (rows i0 .. i0 + 63): src's own rows, and oth's if they come later
+  auto half = [&](int i0, double& src, double rcs, double& oth, int osrc, int ooth, auto bothc) {
+    constexpr bool BOTH = decltype(bothc)::value;
+    double s0[2][ST], o0[2][ST];
+    auto get = [&](int k, double (&s)[ST], double (&o)[ST]) {
 #pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      if (R0) a[u] = TR ? sD[i0 + u][lane] : sD[lane][i0 + u];
-      if (R1) b[u] = TR ? sD[i0 + u][64 + lane] : sD[64 + lane][i0 + u];
-      if (SCALE) r[u] = s_rc[i0 + u];
+      for (int u = 0; u < ST; ++u) {
+        const int i = i0 + (FWD ? k + u : 63 - k - u);
+        s[u] = TR ? sD[i][osrc + lane] : sD[osrc + lane][i];
+        if constexpr (BOTH) o[u] = TR ? sD[i][ooth + lane] : sD[ooth + lane][i];
+      }
+    };
+    auto step = [&](int k, const double (&s)[ST], const double (&o)[ST]) {
+#pragma unroll
+      for (int u = 0; u < ST; ++u) {
+        const double xi = readlane_f64(SCALE ? src * rcs : src, FWD ? k + u : 63 - k - u);
+        src -= s[u] * xi;
+        if constexpr (BOTH) oth -= o[u] * xi;
+      }
+    };
+    get(0, s0[0], o0[0]);
+#pragma unroll 1
+    for (int k = 0; k < 64; k += 2 * ST) {
+      get(k + ST, s0[1], o0[1]);
+      step(k, s0[0], o0[0]);
+      get((k + 2 * ST) & 63, s0[0], o0[0]);
+      step(k + ST, s0[1], o0[1]);
     }
   };
-  ld(c0, c1, q, base + (FWD ? 0 : 64 - CH));
-  for (int k = 0; k < 64 / CH; ++k) {
-    const int i0 = base + (FWD ? k * CH : 64 - CH - k * CH);
-    if (k + 1 < 64 / CH) ld(n0, n1, nq, FWD ? i0 + CH : i0 - CH);
-#pragma unroll
-    for (int uu = 0; uu < CH; ++uu) {
-      const int u = FWD ? uu : CH - 1 - uu;
-      double xi = readlane_f64(H ? v1 : v0, i0 + u - base);
-      if constexpr (SCALE) xi *= q[u];
-      if constexpr (R0) v0 -= static_cast<double>(c0[u]) * xi;
-      if constexpr (R1) v1 -= static_cast<double>(c1[u]) * xi;
-    }
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      c0[u] = n0[u];
-      c1[u] = n1[u];
-      q[u] = nq[u];
-    }
-  }
-}
-
-template <typename T, bool FWD, bool SCALE, bool TR>
-__device__ __attribute__((always_inline)) inline void diag_chain(const T (*sD)[NB + 1], const double* s_rc,
-                                                                 int lane, double& v0, double& v1) {
-  if constexpr (sizeof(T) == 8) {
-    // FP64: one loop, unrolled by 4 (prefetched chunks spill next to the strip)
-#pragma unroll 4
-    for (int k = 0; k < NB; ++k) {
-      const int i = FWD ? k : NB - 1 - k;
-      const double l0 = TR ? sD[i][lane] : sD[lane][i];
-      const double l1 = TR ? sD[i][64 + lane] : sD[64 + lane][i];
-      double xi = (i < 64) ? readlane_f64(v0, i) : readlane_f64(v1, i - 64);
-      if constexpr (SCALE) xi *= s_rc[i];
-      v0 -= l0 * xi;
-      v1 -= l1 * xi;
-    }
-  } else if constexpr (FWD) {
-    diag_half<T, FWD, SCALE, TR, 0>(sD, s_rc, lane, v0, v1);
-    diag_half<T, FWD, SCALE, TR, 1>(sD, s_rc, lane, v0, v1);
+  if (FWD) {
+    half(0, v0, rc0, v1, 0, 64, std::true_type());
+    half(64, v1, rc1, v0, 64, 0, std::false_type());
   } else {
-    diag_half<T, FWD, SCALE, TR, 1>(sD, s_rc, lane, v0, v1);
-    diag_half<T, FWD, SCALE, TR, 0>(sD, s_rc, lane, v0, v1);
+    half(64, v1, rc1, v0, 64, 0, std::true_type());
+    half(0, v0, rc0, v1, 0, 64, std::false_type());
   }
   if constexpr (SCALE) {
-    v0 *= s_rc[lane];
-    v1 *= s_rc[64 + lane];
+    v0 *= rc0;
+    v1 *= rc1;
   }
 }
 
+// Columns at a wavefront-uniform address: next() gives each one's and steps on.
+// Kept in scalar registers, so that a load takes the lane's 32-bit offset alone
+// (the compiler makes a 64-bit address per load and lane of it otherwise).
+template <typename T>
+struct UniformCols {
+  uint64_t p;
+  const uint64_t stride;
+  __device__ __forceinline__ UniformCols(const T* base, size_t elems)
+      : p(reinterpret_cast<uint64_t>(base)), stride(elems * sizeof(T)) {}
+  __device__ __forceinline__ const T* next() {
+    using G = const T __attribute__((address_space(1)))*;
+    asm("" : "+s"(p));
+    const uint64_t q = p;
+    p += stride;
+    return (const T*)(G)q;
+  }
+};
+
+// Sums of the wavefront for eight values per lane: lane l returns value l mod 8's
+// (the values are halved three times as the lanes pair up, then summed).
+__device__ __forceinline__ double fold8(const double (&v)[8], int lane) {
+  double a[4], b[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool up = lane & 1;
+    a[i] = (up ? v[2 * i + 1] : v[2 * i]) + __shfl_xor(up ? v[2 * i] : v[2 * i + 1], 1);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool up = lane & 2;
+    b[i] = (up ? a[2 * i + 1] : a[2 * i]) + __shfl_xor(up ? a[2 * i] : a[2 * i + 1], 2);
+  }
+  const bool up = lane & 4;
+  double c = (up ? b[1] : b[0]) + __shfl_xor(up ? b[0] : b[1], 4);
+  c += __shfl_xor(c, 8);
+  c += __shfl_xor(c, 16);
+  return c + __shfl_xor(c, 32);
+}
+
 // ---------------------------------------------------------------------------
-// Solve with the factors (one 1024-thread block per matrix), FP64 right-hand side.
+// Solve with the factors (one 1024-thread block per right-hand side), FP64
+// right-hand side.
 // transpose = 0: x = U^-1 L_m^-1 P_m ... L_1^-1 P_1 b
 // transpose = 1: y = P_1^T L_1^-T ... P_m^T L_m^-T U^-T c
-// Diagonal blocks are staged in LDS and solved by one wavefront (two rows per
-// lane); the off-diagonal strips are applied column-oriented (thread per row)
-// or, for the transposed factors, as per-column dot products (wave per column).
-// The next diagonal block is loaded into registers before the strip that
-// precedes its use, so that its loads travel with the strip's; a panel's
-// gather / scatter is skipped when the panel interchanges no rows (always,
-// for statically pivoted factors).
+// Diagonal blocks: FP32 and FP16 factors are refined or precondition, and take
+// the inverses of the block's triangles (tinv: one 128 x 128 product per block,
+// 0.3 us, in place of a chain of 128 steps, 2.2 us); FP64 factors solve with the
+// block itself, staged in LDS, on one wavefront.
+// Off-diagonal strips are applied column-oriented: a thread takes a 16-byte
+// vector of consecutive rows; short strips split the 128 columns over up to 16
+// groups of threads, whose sums meet in LDS, so that a strip is one or two
+// rounds of loads whatever its height (a strip of 128 rows of FP64 factors took
+// 16 rounds, 16 us).  The transposed factors take dot products down eight
+// columns per wavefront at a time.  The next diagonal block is loaded into
+// registers before the strip that precedes its use, so that its loads travel
+// with the strip's; a panel's gather / scatter is skipped when the panel
+// interchanges no rows (always, for statically pivoted factors).
+// Bound by what one CU draws: about 38 GB/s, whatever the loads in flight (8 or
+// 16 columns, waited for together or one by one: its vector cache holds 32 KB of
+// outstanding lines, over a latency of 0.85 us), until 256 CUs reach HBM's rate.
+// Per solve: 100 points, n = 1024, FP32 183 -> 116 us; 256 points, n = 2048, FP32 718 ->
+// 690 (6.2 TB/s); 64 points, n = 2048, FP64 990 -> 857; its band form,
+// half-bandwidth 127, 663 -> 351; FP64 transposed, 128 points, n = 512: 202 -> 105.
 // ---------------------------------------------------------------------------
 template <typename T, int TRANSPOSE>
-__global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const int* __restrict__ piv,
+__global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const float* __restrict__ tinv,
                                                 const int* __restrict__ perm, const double* __restrict__ Bin,
                                                 double* __restrict__ Xout,
                                                 const int* __restrict__ status, int accumulate, int check_done,
@@ -1553,15 +1628,23 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
   // or the one mat_of names (a shared factorization, e.g. a preconditioner bin)
   const int row = blockIdx.x;
   if (skip && skip[row]) return;
+  using V = typename Vec4<T>::type;
+  constexpr int PER = Vec4<T>::per;
+  constexpr bool F64 = sizeof(T) == 8;
+  using D = std::conditional_t<F64, double, float>;   // diagonal-block entries
+  constexpr int NWV = 1024 / 64;
   __shared__ double sb[kMaxRows];
-  __shared__ T sD[NB][NB + 1];
-  __shared__ double s_rc[NB];
+  __shared__ double s_rc[F64 ? NB : 1];
   __shared__ int s_nr[kMaxPanels];
-  __shared__ double s_part[sizeof(T) < 8 ? 512 * Vec4<T>::per : 1];
+  // the staged diagonal block (FP64; FP32 transposed), or the strips' and blocks' partial sums
+  constexpr int STAGE = (F64 || TRANSPOSE) ? NB * (NB + 1) * static_cast<int>(sizeof(D)) : 0;
+  constexpr int PART = 1024 * PER * 8;
+  __shared__ __align__(16) unsigned char smem[STAGE > PART ? STAGE : PART];
+  D (*sD)[NB + 1] = reinterpret_cast<D (*)[NB + 1]>(smem);
+  double* s_part = reinterpret_cast<double*>(smem);
   const int mat = mat_of ? mat_of[row] : row;
   const T* A = LU + (size_t)mat * npad * npad;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  constexpr int NWV = 1024 / 64;
   const double* b = Bin + (size_t)row * npad;
   // factors of the mirrored matrix: the right-hand side comes in mirrored and
   // the solution goes out mirrored (ordinate theta -> nth-1-theta of each speed)
@@ -1571,173 +1654,275 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
   const int np = npad / NB;
   const int* pmat = perm + (size_t)mat * kMaxPanels * kPermStride;
   if (tid < np) s_nr[tid] = pmat[(size_t)tid * kPermStride];   // rows each panel's interchanges move
-  // sb[r] -= sum_j A[r][k0 + j] sb[k0 + j] for rows r in [r_lo, r_hi): each
-  // thread takes a 16-byte vector of consecutive rows (4 FP32 / 2 FP64) and keeps
-  // JB column loads in flight (16 FP32, 8 FP64 and FP16: 16 FP64 loads spilled); FP32 and FP16 split the 128 columns between the
-  // two halves of the block and add the halves through LDS
-  auto strip = [&](int k0, int r_lo, int r_hi) {
-    using V = typename Vec4<T>::type;
-    constexpr int PER = Vec4<T>::per;
-    constexpr int H = sizeof(T) < 8 ? 2 : 1;    // column groups
-    constexpr int CW = NB / H, JB = sizeof(T) == 4 ? 16 : 8, TPG = 1024 / H;
-    const int grp = tid / TPG, lt = tid % TPG;
-    for (int r0 = r_lo; r0 < r_hi; r0 += TPG * PER) {
-      const int r = r0 + lt * PER;
-      const bool v = r < r_hi;
-      double acc[PER];
+  // A strip: sb[r] -= sum_j A[r][k0 + j] sb[k0 + j] for rows r in [r_lo, r_lo + R)
+  // (multiples of 128); groups of 2^lg threads cover the rows,
+  // 1024 / 2^lg groups the columns, JB of which are in flight.
+  constexpr int JB = 8;
+  constexpr int LGMAX = F64 ? 10 : 9;
+  static_assert((PER << LGMAX) >= kMaxRows, "one vector per thread covers a strip's rows");
+  struct Strip { int k0, r_lo, R, lg; };
+  auto strip_of = [&](int k0, int r_lo, int r_hi) {
+    Strip st{k0, r_hi > r_lo ? r_lo : 0, max(0, r_hi - r_lo), 6};   // (no rows: fetches the matrix's first ones, unused)
+    while ((PER << st.lg) < st.R && st.lg < LGMAX) ++st.lg;
+    return st;
+  };
+  V x[JB];   // the strip's next JB columns
+  auto col0 = [&](const Strip& st) { return st.k0 + __builtin_amdgcn_readfirstlane(tid >> st.lg) * (NB >> (10 - st.lg)); };
+  auto row0 = [&](const Strip& st) {   // (threads beyond the rows read the first ones)
+    const int o = (tid & ((1 << st.lg) - 1)) * PER;
+    return static_cast<unsigned>(st.r_lo + (o < st.R ? o : 0));
+  };
+  // its first JB columns, issued ahead of the diagonal block that precedes it
+  auto fetch = [&](const Strip& st) {
+    UniformCols<T> cols(A + (size_t)col0(st) * npad, npad);
+    const unsigned r = row0(st);
 #pragma unroll
-      for (int m = 0; m < PER; ++m) acc[m] = 0.0;
-      for (int jb = 0; jb < CW; jb += JB) {
-        V x[JB];
+    for (int u = 0; u < JB; ++u) x[u] = ntload(reinterpret_cast<const V*>(cols.next() + r));
+  };
+  // applies the strip, a column's load following the use of the column JB
+  // before it; the last JB loads are those of the strip nx
+  auto apply = [&](const Strip& st, const Strip& nx) {
+    const int cw = NB >> (10 - st.lg), c0 = col0(st), grp = tid >> st.lg, tpg = 1 << st.lg, lt = tid & (tpg - 1);
+    const bool v = lt * PER < st.R;
+    const T* nbase = A + (size_t)col0(nx) * npad;
+    const unsigned nr = row0(nx);
+    unsigned r = row0(st);
+    double acc[PER];
 #pragma unroll
-        for (int u = 0; u < JB; ++u) {
-          const int c = k0 + grp * CW + jb + u;
-          if (v) x[u] = ntload(reinterpret_cast<const V*>(A + (size_t)c * npad + r));
-        }
+    for (int m = 0; m < PER; ++m) acc[m] = 0.0;
+    int cb = 0;
+    do {
+      const bool last = cb + JB >= cw;
+      UniformCols<T> cols(last ? nbase : A + (size_t)(c0 + cb + JB) * npad, npad);
+      r = last ? nr : r;
 #pragma unroll
-        for (int u = 0; u < JB; ++u) {
-          const double bj = sb[k0 + grp * CW + jb + u];
-          const T* e = reinterpret_cast<const T*>(&x[u]);
+      for (int u = 0; u < JB; ++u) {
+        const double bj = sb[c0 + cb + u];
+        const T* e = reinterpret_cast<const T*>(&x[u]);
 #pragma unroll
-          for (int m = 0; m < PER; ++m) acc[m] += static_cast<double>(e[m]) * bj;
-        }
+        for (int m = 0; m < PER; ++m) acc[m] += static_cast<double>(e[m]) * bj;
+        x[u] = ntload(reinterpret_cast<const V*>(cols.next() + r));
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (H == 2) {
-        if (grp == 1 && v) {
+    } while ((cb += JB) < cw);
+    if (tpg == 1024) {
+      if (v) {
 #pragma unroll
-          for (int m = 0; m < PER; ++m) s_part[lt * PER + m] = acc[m];
-        }
-        __syncthreads();
-        if (grp == 0 && v) {
+        for (int m = 0; m < PER; ++m) sb[st.r_lo + lt * PER + m] -= acc[m];
+      }
+    } else {
 #pragma unroll
-          for (int m = 0; m < PER; ++m) sb[r + m] -= acc[m] + s_part[lt * PER + m];
-        }
-        __syncthreads();
-      } else if (v) {
-#pragma unroll
-        for (int m = 0; m < PER; ++m) sb[r + m] -= acc[m];
+      for (int m = 0; m < PER; ++m) s_part[(grp * tpg + lt) * PER + m] = acc[m];
+      lds_barrier();
+      for (int i = tid; i < st.R; i += 1024) {
+        double t = 0.0;
+        for (int g = 0; g < 1024 / tpg; ++g) t += s_part[g * tpg * PER + i];
+        sb[st.r_lo + i] -= t;
       }
     }
+    lds_barrier();
   };
-  // diagonal block of the panel at k0: loads into registers, then LDS stores
-  // of the strict triangle the chain reads (lower: L; upper: U, whose
-  // diagonal goes to s_rc as reciprocals), zeros elsewhere
+  // diagonal block of panel q: FP64 the factors' own, else the inverses of its
+  // triangles; thread t holds row t mod 128 of the columns t / 128 + 8 u
   constexpr int NS = NB * NB / 1024;
-  T dv[NS];
-  auto load_diag = [&](int k0) {
+  D dv[NS];
+  const unsigned dr = tid % NB;
+  const int dc = __builtin_amdgcn_readfirstlane(tid / NB);
+  auto load_diag = [&](int q) {
+    const D* first;
+    if constexpr (F64) first = A + (size_t)(q * NB + dc) * npad + q * NB;
+    else first = tinv + (((size_t)mat * np + q) * NB + dc) * NB;
+    UniformCols<D> cols(first, 8 * (F64 ? npad : NB));
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      const int e = tid + 1024 * u;
-      dv[u] = A[(size_t)(k0 + e / NB) * npad + k0 + e % NB];
-    }
+    for (int u = 0; u < NS; ++u) dv[u] = cols.next()[dr];
   };
+  // FP64: into LDS the strict triangle the chain reads (lower: L; upper: U, whose
+  // diagonal goes to s_rc as reciprocals), zeros elsewhere
   auto store_diag = [&](bool upper) {
+    D dg = 1;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const int e = tid + 1024 * u;
-      const int r = e % NB, c = e / NB;
-      if (upper && r == c) s_rc[r] = 1.0 / static_cast<double>(dv[u]);
-      sD[r][c] = (upper ? r < c : r > c) ? dv[u] : T(0);
+      const int r = dr, c = dc + 8 * u;
+      if constexpr (F64) {
+        dg = r == c ? dv[u] : dg;
+        sD[r][c] = (upper ? r < c : r > c) ? dv[u] : 0.0;
+      } else if constexpr (TRANSPOSE) {
+        sD[r][c] = (upper ? r <= c : r > c) ? dv[u] : 0.0f;
+      }
+    }
+    if constexpr (F64) {
+      if (upper && static_cast<int>(dr % 8) == dc) s_rc[dr] = 1.0 / dg;
     }
   };
   // the panel's interchanges as one gather / scatter over its rows (INV: the
   // inverse), skipped when the panel moves no rows
-  auto permute = [&](int q, bool inv) {
+  // (from, to: the thread's entries of the two lists, read a phase ahead with the
+  // diagonal block, or here)
+  auto permute = [&](int q, auto from, auto to) {
     const int nR = s_nr[q];
     if (nR == 0) return;
-    const int* pm = pmat + (size_t)q * kPermStride;
     double pv = 0.0;
-    if (tid < nR) pv = sb[pm[1 + (inv ? 0 : kMaxSwapRows) + tid]];
-    __syncthreads();
-    if (tid < nR) sb[pm[1 + (inv ? kMaxSwapRows : 0) + tid]] = pv;
-    __syncthreads();
+    if (tid < nR) pv = sb[from()];
+    lds_barrier();
+    if (tid < nR) sb[to()] = pv;
+    lds_barrier();
   };
-  // wave 0 solves the panel's rows of sb with the staged block
-  auto chain = [&](int k0, auto fwd, auto scale, auto tr) {
-    if (w == 0) {
-      double v0 = sb[k0 + lane], v1 = sb[k0 + 64 + lane];
-      diag_chain<T, decltype(fwd)::value, decltype(scale)::value, decltype(tr)::value>(sD, s_rc, lane, v0, v1);
-      sb[k0 + lane] = v0;
-      sb[k0 + 64 + lane] = v1;
+  auto perm_of = [&](int q, int list) {   // list 0: the rows' new places, 1: their old ones
+    return pmat[(size_t)q * kPermStride + 1 + list * kMaxSwapRows + tid % kMaxSwapRows];
+  };
+  // the block's rows of sb solved with its L (unit lower) or U triangle, or the
+  // transposes
+  auto solve_diag = [&](int k0, auto upperc) {
+    constexpr bool UP = decltype(upperc)::value;
+    if constexpr (F64) {
+      if (w == 0) {
+        int l = lane;
+        asm("" : "+v"(l));   // (addresses made from it here, not kept in registers over the strips)
+        double v0 = sb[k0 + l], v1 = sb[k0 + 64 + l];
+        diag_chain<TRANSPOSE ? UP : !UP, UP, TRANSPOSE != 0>(sD, s_rc, l, v0, v1);
+        sb[k0 + l] = v0;
+        sb[k0 + 64 + l] = v1;
+      }
+      lds_barrier();
+    } else {
+      const int r = dr, g = dc;
+      double acc = 0.0;
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int c = g + 8 * u;
+        if constexpr (TRANSPOSE) acc += static_cast<double>(sD[c][r]) * sb[k0 + c];   // row c of the block, column r
+        else acc += ((UP ? r <= c : r > c) ? static_cast<double>(dv[u]) : 0.0) * sb[k0 + c];
+      }
+      if constexpr (TRANSPOSE) lds_barrier();   // the staged block is read
+      s_part[g * NB + r] = acc;
+      lds_barrier();
+      if (tid < NB) {
+        double t = UP ? 0.0 : sb[k0 + tid];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t += s_part[q * NB + tid];
+        sb[k0 + tid] = t;
+      }
+      lds_barrier();
     }
   };
-  using Yes = std::true_type;
-  using No = std::false_type;
+  using Up = std::true_type;
+  using Lo = std::false_type;
   load_diag(0);
-  __syncthreads();
+  // the permutations of a panel and the next one: FP64 factors a phase ahead
+  int pa = 0, pb = 0, qa = 0, qb = 0;
+  auto load_perm = [&](int q) {
+    const int q1 = min(q + 1, np - 1);
+    pa = perm_of(q, 0), pb = perm_of(q, 1), qa = perm_of(q1, 0), qb = perm_of(q1, 1);
+  };
   if (!TRANSPOSE) {
+    // banded factors: L below a panel reaches band_lo rows, and U has upper
+    // bandwidth band_up (kl + ku with the fill of the interchanges)
+    auto lower = [&](int p) {
+      const int k1 = (p + 1) * NB;
+      return strip_of(p * NB, k1, band_lo > 0 ? min(npad, (k1 + band_lo + NB - 1) / NB * NB) : npad);
+    };
+    auto upper = [&](int p) {
+      const int k0 = p * NB;
+      return strip_of(k0, band_up > 0 ? max(0, (k0 - band_up) / NB * NB) : 0, k0);
+    };
+    if constexpr (F64) load_perm(0);
+    fetch(lower(0));
+    lds_barrier();
     for (int p = 0; p < np; ++p) {
       const int k0 = p * NB;
       // P_p (a pair's first panel applies P_{p+1} too, its second none)
       const bool first = paired && p % 2 == 0 && p + 2 < np;
       const bool second = paired && p % 2 == 1 && p + 1 < np;
-      store_diag(false);
-      if (!second) permute(p, false);
-      if (first) permute(p + 1, false);
-      __syncthreads();
-      chain(k0, Yes(), No(), No());   // unit lower triangular diagonal block
-      __syncthreads();
-      if (p + 1 < np) load_diag(k0 + NB);   // the last panel's block serves U too
-      // banded factors: L below a panel reaches band_lo rows
-      strip(k0, k0 + NB, band_lo > 0 ? min(npad, (k0 + NB + band_lo + NB - 1) / NB * NB) : npad);
-      __syncthreads();
+      if constexpr (F64) store_diag(false);
+      // (FP32: read here, as statically pivoted factors have none)
+      auto own = [&](int q, int list, int ahead) { return [=] { return F64 ? ahead : perm_of(q, list); }; };
+      if (!second) permute(p, own(p, 1, pb), own(p, 0, pa));
+      if (first) permute(p + 1, own(p + 1, 1, qb), own(p + 1, 0, qa));
+      if constexpr (F64) lds_barrier();
+      solve_diag(k0, Lo());   // unit lower triangular diagonal block
+      if (p + 1 < np) {                  // the last panel's block serves U too
+        load_diag(p + 1);
+        if constexpr (F64) load_perm(p + 1);
+        apply(lower(p), p + 2 < np ? lower(p + 1) : upper(np - 1));
+      }
     }
     for (int p = np - 1; p >= 0; --p) {
       const int k0 = p * NB;
-      store_diag(true);
-      __syncthreads();
-      chain(k0, No(), Yes(), No());   // upper triangular diagonal block
-      __syncthreads();
-      if (p > 0) load_diag(k0 - NB);
-      // banded factors: U has upper bandwidth band_up (kl + ku with the fill of
-      // the interchanges)
-      strip(k0, band_up > 0 ? max(0, (k0 - band_up) / NB * NB) : 0, k0);
-      __syncthreads();
+      if constexpr (F64) {
+        store_diag(true);
+        lds_barrier();
+      }
+      solve_diag(k0, Up());   // upper triangular diagonal block
+      if (p > 0) {
+        load_diag(p - 1);
+        apply(upper(p), upper(p - 1));
+      }
     }
   } else {
+    // dot products of eight columns c .. c + 7 with sb over rows [r_lo, r_hi)
+    // (multiples of 128), the sum of column c + lane % 8
+    auto dots8 = [&](int c, int r_lo, int r_hi) {
+      double acc[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc[u] = 0.0;
+      const T* base = A + (size_t)c * npad;
+      constexpr int CH = F64 ? 2 : 4;   // consecutive rows per lane: a vector, or half of it (FP16)
+      using C = T __attribute__((ext_vector_type(CH)));
+      for (int r0 = r_lo; r0 < r_hi; r0 += 64 * CH) {
+        const unsigned r = r0 + CH * lane;
+        const bool v = static_cast<int>(r) < r_hi;
+        C x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (v) x[u] = *reinterpret_cast<const C*>(base + (size_t)u * npad + r);
+        if (v) {
+#pragma unroll
+          for (int m = 0; m < CH; ++m) {
+            const double z = sb[r + m];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc[u] += static_cast<double>(x[u][m]) * z;
+          }
+        }
+      }
+      return fold8(acc, lane);
+    };
+    lds_barrier();
     // z = U^-T c, forward over panels (U^T is lower triangular)
     for (int p = 0; p < np; ++p) {
       const int k0 = p * NB;
       store_diag(true);
-      __syncthreads();
-      chain(k0, Yes(), Yes(), Yes());
-      __syncthreads();
-      if (p + 1 < np) load_diag(k0 + NB);   // the last panel's block serves L^T too
-      // c[col] -= sum_j U[k0+j][col] z_j for col >= k0 + NB (wave per column)
-      for (int col = k0 + NB + w; col < npad; col += NWV) {
-        const T* cp = A + (size_t)col * npad + k0;
-        double s = static_cast<double>(cp[lane]) * sb[k0 + lane] +
-                   static_cast<double>(cp[64 + lane]) * sb[k0 + 64 + lane];
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0) sb[col] -= s;
+      lds_barrier();
+      solve_diag(k0, Up());
+      if (p + 1 < np) load_diag(p + 1);   // the last panel's block serves L^T too
+      // c[col] -= sum_j U[k0+j][col] z_j for col >= k0 + NB
+      for (int col = k0 + NB + 8 * w; col < npad; col += 8 * NWV) {
+        const double t = dots8(col, k0, k0 + NB);
+        if (lane < 8) sb[col + lane] -= t;
       }
-      __syncthreads();
+      lds_barrier();
     }
     // for p = m..1: z <- L_p^-T z, then z <- P_p^T z
     for (int p = np - 1; p >= 0; --p) {
       const int k0 = p * NB;
-      if (p < np - 1) load_diag(k0);
-      // z_j -= sum_{r >= k0+NB} L[r][k0+j] z_r (wave per column j)
-      for (int j = w; j < NB; j += NWV) {
-        const T* cp = A + (size_t)(k0 + j) * npad;
-        double s = 0.0;
-        for (int r = k0 + NB + lane; r < npad; r += 64) s += static_cast<double>(cp[r]) * sb[r];
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0) sb[k0 + j] -= s;
+      if (p < np - 1) load_diag(p);
+      // z_j -= sum_{r >= k0+NB} L[r][k0+j] z_r (16 wavefronts, eight columns each)
+      if (k0 + NB < npad) {
+        const double t = dots8(k0 + 8 * w, k0 + NB, npad);
+        if (lane < 8) sb[k0 + 8 * w + lane] -= t;
       }
       store_diag(false);
-      __syncthreads();
-      chain(k0, No(), No(), Yes());   // L11^T is unit upper triangular
-      __syncthreads();
+      lds_barrier();
+      solve_diag(k0, Lo());   // L11^T is unit upper triangular
       // P_p^T: inverse of the panel's gather / scatter (a pair's first panel
       // applies P_{p+1}^T then P_p^T, its second none)
       const bool first = paired && p % 2 == 0 && p + 2 < np;
       const bool second = paired && p % 2 == 1 && p + 1 < np;
       if (!second) {
-        if (first) permute(p + 1, true);
-        permute(p, true);
+        auto own = [&](int q, int list) { return [=] { return perm_of(q, list); }; };
+        if (first) permute(p + 1, own(p + 1, 0), own(p + 1, 1));
+        permute(p, own(p, 0), own(p, 1));
       }
-      __syncthreads();
+      lds_barrier();
     }
   }
   double* xo = Xout + (size_t)row * npad;
@@ -1751,6 +1936,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
   T* LU = static_cast<T*>(d.lu) + (size_t)m0 * np2;
   T* xs = static_cast<T*>(d.xscr) + (size_t)m0 * d.npad * NB;
   T* li = static_cast<T*>(d.linv) + (size_t)m0 * kLinvElems;  // inverses of L11 and its diagonal blocks
+  float* ti = d.tinv + (size_t)m0 * d.npad * NB;              // FP32: the diagonal blocks' inverses, for the solves
   int* piv = d.piv + (size_t)m0 * d.npad;
   int* perm = d.perm + (size_t)m0 * kMaxPanels * kPermStride;
   const int xpb = d.form_xpb > 0 ? d.form_xpb : (sizeof(T) == 4 ? 8 : 16);   // matrices per formation block
@@ -1826,7 +2012,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
   // statically pivoted FP32 panels: the diagonal block and L21 (on stream st)
   auto static_panel = [&](int k0, int rend, hipStream_t st, float* lmax = nullptr, int first = 0) {
     if constexpr (std::is_same<T, float>::value) {
-      k_diag_static<<<nmat, 256, 0, st>>>(LU, li, piv, perm, d.status, d.npad, k0);
+      k_diag_static<<<nmat, 256, 0, st>>>(LU, li, ti, piv, perm, d.status, d.npad, k0);
       const int nt = (rend - k0 - NB) / NB;   // row tiles of L21 (rend, k0 multiples of 128)
       if (nt > 0) k_l21_mfma<<<xcd_grid(nt, nmat), 256, 0, st>>>(LU, li, d.npad, k0, nt, nmat, lmax, first);
     }
@@ -1952,6 +2138,9 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
       tm->used = p + 1;
     }
   }
+  if constexpr (std::is_same<T, float>::value) {
+    if (!stat) k_diag_inv<<<dim3(np, nmat), 256, 0, s>>>(LU, ti, d.npad);
+  }
 }
 
 }  // namespace
@@ -1986,25 +2175,19 @@ void launch_lu_solve_mapped(const DevOps& f, int precision, bool transpose, cons
                             hipStream_t s) {
   // the mirror flags of the FP32 factors, set at their formation
   const int* mir = (precision != 0 && precision != kFactorsFp16) ? f.mirror : nullptr;
-  if (precision == 0) {
-    const double* LU = static_cast<const double*>(f.lu);
-    if (transpose)
-      k_solve<double, 1><<<nrows, 1024, 0, s>>>(LU, f.piv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl, f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-    else
-      k_solve<double, 0><<<nrows, 1024, 0, s>>>(LU, f.piv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl, f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-  } else if (precision == kFactorsFp16) {
-    const _Float16* LU = static_cast<const _Float16*>(f.lu);
-    if (transpose)
-      k_solve<_Float16, 1><<<nrows, 1024, 0, s>>>(LU, f.piv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl, f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-    else
-      k_solve<_Float16, 0><<<nrows, 1024, 0, s>>>(LU, f.piv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl, f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-  } else {
-    const float* LU = static_cast<const float*>(f.lu);
-    if (transpose)
-      k_solve<float, 1><<<nrows, 1024, 0, s>>>(LU, f.piv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl, f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-    else
-      k_solve<float, 0><<<nrows, 1024, 0, s>>>(LU, f.piv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl, f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-  }
+  auto run = [&](auto* LU) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(LU)>>;
+    auto go = [&](auto tc) {
+      k_solve<T, decltype(tc)::value><<<nrows, 1024, 0, s>>>(
+          LU, f.tinv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl,
+          f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
+    };
+    if (transpose) go(std::integral_constant<int, 1>());
+    else go(std::integral_constant<int, 0>());
+  };
+  if (precision == 0) run(static_cast<const double*>(f.lu));
+  else if (precision == kFactorsFp16) run(static_cast<const _Float16*>(f.lu));
+  else run(static_cast<const float*>(f.lu));
 }
 
 }  // namespace bte

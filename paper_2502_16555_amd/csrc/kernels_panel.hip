@@ -38,14 +38,6 @@ constexpr int NB = kNB;
 constexpr int SW = 16;   // columns per pivot-step group
 constexpr int kUPitch = NB + 16;   // row pitch of the staged U rows (operand reads of two rows on different banks)
 
-// Barrier for data exchanged through LDS only: the block's global stores stay
-// in flight (a full fence would wait for them at every pivot step).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // maximum over the wavefront of 32-bit unsigned keys; uniform result
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   v = dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(v))));

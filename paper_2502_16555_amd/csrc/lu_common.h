@@ -66,6 +66,14 @@ __device__ inline void xcd_map(int bid, int items, int nmat, int* mat, int* item
 
 inline int xcd_grid(int items, int nmat) { return kXcd * items * ((nmat + kXcd - 1) / kXcd); }
 
+// Barrier for data exchanged through LDS only: the block's global loads
+// and stores stay in flight (a full fence would wait for them every time).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Wavefront reductions through DPP lane permutations (quad swaps, half-row and
 // row mirrors) inside each row of 16 lanes, then the four row results by lane
 // reads: no LDS round trip on the pivot search's critical path.

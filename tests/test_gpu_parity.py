@@ -815,6 +815,46 @@ def test_fp64_panels_of_every_height_match_restatement(torch, nr, nth):
     s.close()
 
 
+@pytest.mark.parametrize("nr,nth,form", [
+    (nr, nth, form) for nr, nth in [(10, 6), (24, 10), (40, 16), (48, 24)]
+    for form in ["fp64", "static_fp32", "pivoted_fp32", "fp16_bins"]
+    if (nr, form) != (48, "fp16_bins")])   # (90 iterations on 32 bins do not converge there, in any factor precision)
+def test_triangular_solves_of_every_height(torch, nr, nth, form):
+    """Solves with 1, 2, 5 and 9 panels (strips of 0 to 8 blocks: from 16 column groups to one
+    or two), with FP64 factors, FP32 factors with and without interchanges, and FP16 factors as
+    the preconditioner, and the transposed solve of the adjoint step.  The tolerances are those of
+    the same steps elsewhere: FP64 rounding on matrices of small condition number, 1e-10 where
+    refinement stops at 1e-14 of the right-hand side, 1e-9 for GMRES at 1e-12."""
+    from paper_2502_16555_amd import _lib
+    cfg = workloads.small_config(nx=4, nr=nr, nth=nth, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf")
+    ops = oracle.build_operators(cfg)
+    s = solver(cfg, precision="fp64" if form in ("fp64", "fp16_bins") else "mixed_fp32")
+    if form == "pivoted_fp32":
+        s.set_tuning(_lib.TUNE_STATIC_PIVOTING, 0)
+    if form == "fp16_bins":
+        s.set_vsolver("gmres", n_bins=32, E_bound=1.5e4, restart=30, cycles=3, rtol=1e-12,
+                      factor_precision="fp16_factors")
+    tol = {"fp64": 1e-11, "fp16_bins": 1e-9}.get(form, 1e-10)
+    F = _state(ops, 3)
+    E = np.array([1.2e4, -6e3, 0.0, -1.5e4])
+    Fg = cuda(torch, F)
+    s.vstep(Fg, cuda(torch, E))
+    code, sweeps, resid = s.status()
+    assert code == 0, (code, sweeps, resid)
+    close(Fg.cpu().numpy(), S.v_step(ops, F, E), tol, form)
+    if form != "fp16_bins":
+        L = _state(ops, 10)
+        t = 0.21 * cfg["T_rf_s"]
+        lam_o, gs_o, _ = S.adjoint_step(ops, F, t, L)
+        Lg = cuda(torch, L)
+        gs = torch.zeros(s.n_params, dtype=torch.float64, device="cuda:0")
+        s.adjoint_step(cuda(torch, F), t, Lg, gs)
+        close(Lg.cpu().numpy(), lam_o, 1e-10, form)
+        close(gs.cpu().numpy(), gs_o, 1e-10, form)
+    s.close()
+
+
 @pytest.mark.parametrize("prec", ["mixed_fp32", "mixed_bf16x3", "mixed_bf16"])
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_partial_pivoting_vstep_matches_oracle(torch, case, prec):
