@@ -7,6 +7,7 @@
 #include <cmath>
 
 #include "internal.h"
+#include "lu_common.h"
 
 namespace bte {
 namespace {
@@ -82,163 +83,196 @@ __global__ __launch_bounds__(256) void k_from_harm(const double* __restrict__ Xh
 
 // ---------------------------------------------------------------------------
 // FP64 residual R = B - X + dt n0_x (X C^T) + dt E_x (X A^T)  (TRANSPOSE: C, A)
-// rows = collocation points, 32 x 64 output tiles, MFMA f64 16x16x4; eight
-// wavefronts per tile, each 16 points x 16 outputs, two per SIMD so that one
-// wave's LDS reads overlap the other's products.
+// rows = collocation points.  MODE 0: the refinement residual, with the
+// per-point maxima (skipped once the refinement is done); MODE 1: R = B - M X
+// only; MODE 2: R = M X (operator action of Alg. vspace_action, for the Krylov
+// solver); MODE 3: R = B - dt E (X A^T) (the field-coupling term of the fully
+// implicit Jacobian, eq. 1dbte_jac_action).
+//
+// A block computes 16 PT points x 16 OT outputs; its NW wavefronts share the
+// sum over k (a wavefront takes every NW-th chunk of 16), with the operands
+// straight from memory in 16-byte vectors, and their partial tiles meet in LDS.
+// Bound by the FP64 matrix rate (64 cycles per 16 x 16 x 4 product and SIMD)
+// where the tiles fill the chip: hence two shapes.  64 x 32 tiles of four
+// wavefronts load half as much per product, and run where they give every CU a
+// block; otherwise 32 x 16 tiles of eight wavefronts make eight times as many
+// blocks' worth of parallel work from a small grid.  The blocks of one output
+// tile run on one XCD, so that its rows of C and A come from HBM once.
+// Per residual (32 x 64 tiles staged in LDS, one barrier pair per 64 of k, no
+// split before): 100 points, n = 1024 57 -> 19 us; 200 points, n = 512 33 -> 11; 256
+// points, n = 2048 122 -> 83 (53 us at 69 TFLOP/s).  Three chunks in flight took
+// 22 us at the first, five 28: they push each other out of the 32 KB vector cache.
 // ---------------------------------------------------------------------------
-// MODE 0: the refinement residual above, with the per-point maxima (skipped once
-// the refinement is done); MODE 1: R = B - M X only; MODE 2: R = M X (operator
-// action of Alg. vspace_action, for the Krylov solver); MODE 3: R = B - dt E (X A^T)
-// (the field-coupling term of the fully implicit Jacobian, eq. 1dbte_jac_action).
-constexpr int kResThreads = 512;
-
-template <int TRANSPOSE, int MODE = 0>
-__global__ __launch_bounds__(kResThreads) void k_residual(const double* __restrict__ Bv, const double* __restrict__ Xv,
-                                                  double* __restrict__ Rv, const double* __restrict__ C,
-                                                  const double* __restrict__ Aop, const double* __restrict__ E,
-                                                  const double* __restrict__ n0x, unsigned long long* __restrict__ rmax,
-                                                  unsigned long long* __restrict__ bmax,
-                                                  unsigned long long* __restrict__ xmax, const int* __restrict__ status,
-                                                  double dt, int n, int npad, int nx, const int* __restrict__ skip) {
+template <int TRANSPOSE, int MODE, int PT, int OT, int NW>
+__global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__ Bv, const double* __restrict__ Xv,
+                                                      double* __restrict__ Rv, const double* __restrict__ C,
+                                                      const double* __restrict__ Aop, const double* __restrict__ E,
+                                                      const double* __restrict__ n0x,
+                                                      unsigned long long* __restrict__ rmax,
+                                                      unsigned long long* __restrict__ bmax,
+                                                      unsigned long long* __restrict__ xmax,
+                                                      const int* __restrict__ status, double dt, int n, int npad,
+                                                      int nx, const int* __restrict__ skip) {
   if (MODE == 0 && status[1]) return;
-  constexpr int BM = 32, BN = 64, BK = 64;
+  constexpr int BM = 16 * PT, BN = 16 * OT, CK = 16;
+  constexpr int NOP = MODE == 3 ? 1 : 2;         // operators: A, then C
+  constexpr int DEPTH = 2;                       // chunks in registers: one in use, one on its way
+  using V2 = double __attribute__((ext_vector_type(2)));
+  int bx, by;
+  xcd_map(blockIdx.x, (nx + BM - 1) / BM, (n + BN - 1) / BN, &bx, &by);
+  if (bx * BN >= n) return;
+  const int x0 = by * BM, i0 = bx * BN;
   if (MODE != 0 && skip) {  // points already converged need no operator action
     bool all = true;
-    for (int u = 0; u < BM; ++u) {
-      const int x = blockIdx.y * BM + u;
-      if (x < nx && !skip[x]) all = false;
-    }
+    for (int u = 0; u < BM && x0 + u < nx; ++u)
+      if (!skip[x0 + u]) all = false;
     if (all) return;
   }
-  constexpr int NT = kResThreads;
-  constexpr int LX = BM * BK / NT, LO = BN * BK / NT;  // loads per thread and tile
-  __shared__ double sX[BM][BK + 1];
-  __shared__ double sC[BN][BK + 1];
-  __shared__ double sA[BN][BK + 1];
-  __shared__ unsigned long long s_rm[4][BM], s_bm[4][BM], s_xm[4][BM];
-  const int x0 = blockIdx.y * BM, i0 = blockIdx.x * BN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = (tid >> 6) & 3, b = tid >> 8;   // outputs 16 w.., points 16 b..
+  __shared__ double s_part[NW][NOP][BM][BN];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  // operator element e of a tile: row r (output index i), column c (k); the
-  // transposed form walks i fastest so that its loads stay coalesced
-  auto op_rc = [&](int e, int* r, int* c) {
-    if (TRANSPOSE) {
-      *r = e % BN;
-      *c = e / BN;
-    } else {
-      *r = e / BK;
-      *c = e % BK;
-    }
-  };
-  double px[LX], pc[LO], pa[LO];
-  auto fetch = [&](int k0) {
+  // operand rows of this lane (rows beyond the last repeat it; their results are dropped)
+  const double* xp[PT];
+  const double* op[NOP][OT];
 #pragma unroll
-    for (int u = 0; u < LX; ++u) {
-      const int e = tid + NT * u, r = e / BK, c = e % BK;
-      px[u] = (x0 + r < nx && k0 + c < n) ? Xv[(size_t)(x0 + r) * npad + k0 + c] : 0.0;
-    }
+  for (int p = 0; p < PT; ++p) xp[p] = Xv + (size_t)min(x0 + p * 16 + li, nx - 1) * npad;
 #pragma unroll
-    for (int u = 0; u < LO; ++u) {
-      int r, c;
-      op_rc(tid + NT * u, &r, &c);
-      const int i = i0 + r, k = k0 + c;
-      double cv = 0.0, av = 0.0;
-      if (i < n && k < n) {
-        const size_t o = TRANSPOSE ? (size_t)k * n + i : (size_t)i * n + k;
-        cv = C[o];
-        av = Aop[o];
-      }
-      pc[u] = cv;
-      pa[u] = av;
-    }
-  };
-  f64x4 accC = f64x4{0, 0, 0, 0}, accA = f64x4{0, 0, 0, 0};
-  fetch(0);
-  for (int k0 = 0; k0 < n; k0 += BK) {
-#pragma unroll
-    for (int u = 0; u < LX; ++u) {
-      const int e = tid + NT * u;
-      sX[e / BK][e % BK] = px[u];
-    }
-#pragma unroll
-    for (int u = 0; u < LO; ++u) {
-      int r, c;
-      op_rc(tid + NT * u, &r, &c);
-      sC[r][c] = pc[u];
-      sA[r][c] = pa[u];
-    }
-    __syncthreads();
-    if (k0 + BK < n) fetch(k0 + BK);  // next tile in flight during the products
-#pragma unroll 4
-    for (int k = 0; k < BK; k += 4) {
-      const double bc = sC[w * 16 + li][k + lk];
-      const double ba = sA[w * 16 + li][k + lk];
-      const double ax = sX[b * 16 + li][k + lk];
-      accC = __builtin_amdgcn_mfma_f64_16x16x4f64(ax, bc, accC, 0, 0, 0);
-      accA = __builtin_amdgcn_mfma_f64_16x16x4f64(ax, ba, accA, 0, 0, 0);
-    }
-    __syncthreads();
+  for (int o = 0; o < OT; ++o) {
+    const size_t i = min(i0 + o * 16 + li, n - 1);
+    op[0][o] = Aop + (TRANSPOSE ? i : i * n);
+    if constexpr (NOP == 2) op[1][o] = C + (TRANSPOSE ? i : i * n);
   }
-  // epilogue: residual, then max |r| and max |b| per point, reduced over the
-  // block before one atomic per point (bit patterns of non-negative doubles
-  // order like the values, and a NaN orders above +inf)
-  {
+  const int nch = (n + CK - 1) / CK, cnt = (nch - w + NW - 1) / NW;
+  struct Chunk {
+    V2 x[PT][2], m[NOP][OT][2];
+  } buf[DEPTH];
+  // k of a lane's vector j: 8 j + 2 lk, + 1 within the chunk
+  auto load = [&](Chunk& c, int it) {
+    const int kc = CK * (w + NW * min(it, cnt - 1)) + 2 * lk;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int xl = b * 16 + f64_row(lk, it);
-      const int x = x0 + xl;
-      const int i = i0 + w * 16 + li;
-      unsigned long long rb = 0ull, bb = 0ull, xb = 0ull;
-      if (MODE != 0) {
-        if (x < nx && i < n) {
-          const size_t o = (size_t)x * npad + i;
-          if (MODE == 3) {
-            Rv[o] = Bv[o] - dt * E[x] * accA[it];
-          } else {
-            const double mx = Xv[o] - dt * n0x[x] * accC[it] - dt * E[x] * accA[it];
-            Rv[o] = (MODE == 1) ? Bv[o] - mx : mx;
-          }
+    for (int j = 0; j < 2; ++j) {
+      const int k = kc + 8 * j, ko = min(k, n - 2);   // X's rows are padded to npad, the operators' are not
+#pragma unroll
+      for (int p = 0; p < PT; ++p) c.x[p][j] = *reinterpret_cast<const V2*>(xp[p] + k);
+#pragma unroll
+      for (int q = 0; q < NOP; ++q)
+#pragma unroll
+        for (int o = 0; o < OT; ++o) {
+          if constexpr (TRANSPOSE) c.m[q][o][j] = V2{op[q][o][(size_t)ko * n], op[q][o][(size_t)(ko + 1) * n]};
+          else c.m[q][o][j] = *reinterpret_cast<const V2*>(op[q][o] + ko);
         }
-        continue;
-      }
-      if (x < nx && i < n) {
-        const size_t o = (size_t)x * npad + i;
-        const double bv = Bv[o], xv = Xv[o];
-        const double r = bv - xv + dt * n0x[x] * accC[it] + dt * E[x] * accA[it];
-        Rv[o] = r;
-        rb = static_cast<unsigned long long>(__double_as_longlong(fabs(r)));
-        bb = static_cast<unsigned long long>(__double_as_longlong(fabs(bv)));
-        xb = static_cast<unsigned long long>(__double_as_longlong(fabs(xv)));
-      }
+    }
+  };
+  f64x4 acc[NOP][PT][OT];
 #pragma unroll
-      for (int off = 1; off < 16; off <<= 1) {
-        const unsigned long long orb = __shfl_xor(rb, off), obb = __shfl_xor(bb, off), oxb = __shfl_xor(xb, off);
+  for (int q = 0; q < NOP; ++q)
+#pragma unroll
+    for (int p = 0; p < PT; ++p)
+#pragma unroll
+      for (int o = 0; o < OT; ++o) acc[q][p][o] = f64x4{0, 0, 0, 0};
+  auto product = [&](Chunk& c, int it) {
+    if (CK * (w + NW * it) + CK > n) {   // the last chunk of an n that 16 does not divide
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        if (CK * (w + NW * it) + 2 * lk + 8 * j >= n) {
+#pragma unroll
+          for (int p = 0; p < PT; ++p) c.x[p][j] = V2{0.0, 0.0};
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < NOP; ++q)
+#pragma unroll
+          for (int p = 0; p < PT; ++p)
+#pragma unroll
+            for (int o = 0; o < OT; ++o)
+              acc[q][p][o] = __builtin_amdgcn_mfma_f64_16x16x4f64(c.x[p][j][e], c.m[q][o][j][e], acc[q][p][o], 0, 0, 0);
+  };
+  if (cnt > 0) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(buf[d], d);
+    for (int it = 0; it < cnt; it += DEPTH)
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        if (it + d < cnt) product(buf[d], it + d);
+        load(buf[d], it + d + DEPTH);
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < NOP; ++q)
+#pragma unroll
+    for (int p = 0; p < PT; ++p)
+#pragma unroll
+      for (int o = 0; o < OT; ++o)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) s_part[w][q][p * 16 + f64_row(lk, t)][o * 16 + li] = acc[q][p][o][t];
+  __syncthreads();
+  // sums, result, and (MODE 0) max |r|, |b| and |x| per point, reduced over the
+  // tile's outputs before one atomic per point (bit patterns of non-negative
+  // doubles order like the values, and a NaN orders above +inf)
+  using u64 = unsigned long long;
+#pragma unroll
+  for (int e = tid; e < BM * BN; e += NW * 64) {
+    const int xl = e / BN, il = e % BN, x = x0 + xl, i = i0 + il;
+    u64 rb = 0, bb = 0, xb = 0;
+    if (x < nx && i < n) {
+      double sA = 0.0, sC = 0.0;
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        sA += s_part[u][0][xl][il];
+        if constexpr (NOP == 2) sC += s_part[u][NOP - 1][xl][il];
+      }
+      const size_t o = (size_t)x * npad + i;
+      if (MODE == 0) {
+        const double bv = Bv[o], xv = Xv[o];
+        const double r = bv - xv + dt * n0x[x] * sC + dt * E[x] * sA;
+        Rv[o] = r;
+        rb = static_cast<u64>(__double_as_longlong(fabs(r)));
+        bb = static_cast<u64>(__double_as_longlong(fabs(bv)));
+        xb = static_cast<u64>(__double_as_longlong(fabs(xv)));
+      } else if (MODE == 3) {
+        Rv[o] = Bv[o] - dt * E[x] * sA;
+      } else {
+        const double mx = Xv[o] - dt * n0x[x] * sC - dt * E[x] * sA;
+        Rv[o] = (MODE == 1) ? Bv[o] - mx : mx;
+      }
+    }
+    if constexpr (MODE == 0) {
+#pragma unroll
+      for (int off = 1; off < BN; off <<= 1) {
+        const u64 orb = __shfl_xor(rb, off), obb = __shfl_xor(bb, off), oxb = __shfl_xor(xb, off);
         rb = orb > rb ? orb : rb;
         bb = obb > bb ? obb : bb;
         xb = oxb > xb ? oxb : xb;
       }
-      if (li == 0) {
-        s_rm[w][xl] = rb;
-        s_bm[w][xl] = bb;
-        s_xm[w][xl] = xb;
+      if (il == 0 && x < nx) {
+        atomicMax(&rmax[x], rb);
+        atomicMax(&bmax[x], bb);
+        atomicMax(&xmax[x], xb);
       }
     }
   }
-  if (MODE != 0) return;
-  __syncthreads();
-  if (tid < BM && x0 + tid < nx) {
-    unsigned long long rb = 0ull, bb = 0ull, xb = 0ull;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      rb = s_rm[u][tid] > rb ? s_rm[u][tid] : rb;
-      bb = s_bm[u][tid] > bb ? s_bm[u][tid] : bb;
-      xb = s_xm[u][tid] > xb ? s_xm[u][tid] : xb;
-    }
-    atomicMax(&rmax[x0 + tid], rb);
-    atomicMax(&bmax[x0 + tid], bb);
-    atomicMax(&xmax[x0 + tid], xb);
-  }
+}
+
+template <int TRANSPOSE, int MODE>
+void run_residual(const DevOps& d, const double* B, const double* X, double* R, const double* E, const int* skip,
+                  hipStream_t s) {
+  auto go = [&](auto pt, auto ot, auto nw) {
+    constexpr int PT = decltype(pt)::value, OT = decltype(ot)::value, NW = decltype(nw)::value;
+    const int grid = xcd_grid((d.nx_total + 16 * PT - 1) / (16 * PT), (d.n + 16 * OT - 1) / (16 * OT));
+    k_residual<TRANSPOSE, MODE, PT, OT, NW><<<grid, NW * 64, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x, d.rmax, d.bmax,
+                                                                    d.xmax, d.status, d.dt, d.n, d.npad, d.nx_total,
+                                                                    skip);
+  };
+  using std::integral_constant;
+  // one 64 x 32 tile per CU or more: the larger tiles
+  if (((d.nx_total + 63) / 64) * ((d.n + 31) / 32) >= 256)
+    go(integral_constant<int, 4>(), integral_constant<int, 2>(), integral_constant<int, 4>());
+  else
+    go(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, 8>());
 }
 
 // Stop test of the refinement: the normwise backward error of every point,
@@ -407,34 +441,19 @@ void launch_unpad_rows(const DevOps& d, const double* Bp, double* F, hipStream_t
 
 void launch_apply(const DevOps& d, int mode, const double* B, const double* X, double* R, const int* skip,
                   hipStream_t s) {
-  dim3 g((d.n + 63) / 64, (d.nx_total + 31) / 32);
-  if (mode == 1)
-    k_residual<0, 1><<<g, kResThreads, 0, s>>>(B, X, R, d.Cord, d.Aord, d.E, d.n0x, d.rmax, d.bmax, d.xmax, d.status, d.dt,
-                                       d.n, d.npad, d.nx_total, skip);
-  else
-    k_residual<0, 2><<<g, kResThreads, 0, s>>>(B, X, R, d.Cord, d.Aord, d.E, d.n0x, d.rmax, d.bmax, d.xmax, d.status, d.dt,
-                                       d.n, d.npad, d.nx_total, skip);
+  if (mode == 1) run_residual<0, 1>(d, B, X, R, d.E, skip, s);
+  else run_residual<0, 2>(d, B, X, R, d.E, skip, s);
 }
 
 void launch_apply_field(const DevOps& d, int mode, const double* B, const double* X, double* R, const double* E,
                         hipStream_t s) {
-  dim3 g((d.n + 63) / 64, (d.nx_total + 31) / 32);
-  if (mode == 3)
-    k_residual<0, 3><<<g, kResThreads, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x, d.rmax, d.bmax, d.xmax, d.status, d.dt,
-                                       d.n, d.npad, d.nx_total, nullptr);
-  else
-    k_residual<0, 2><<<g, kResThreads, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x, d.rmax, d.bmax, d.xmax, d.status, d.dt,
-                                       d.n, d.npad, d.nx_total, nullptr);
+  if (mode == 3) run_residual<0, 3>(d, B, X, R, E, nullptr, s);
+  else run_residual<0, 2>(d, B, X, R, E, nullptr, s);
 }
 
 void launch_residual(const DevOps& d, bool transpose, hipStream_t s) {
-  dim3 g((d.n + 63) / 64, (d.nx_total + 31) / 32);
-  if (transpose)
-    k_residual<1><<<g, kResThreads, 0, s>>>(d.B, d.X, d.R, d.Cord, d.Aord, d.E, d.n0x, d.rmax, d.bmax, d.xmax, d.status, d.dt, d.n,
-                                    d.npad, d.nx_total, nullptr);
-  else
-    k_residual<0><<<g, kResThreads, 0, s>>>(d.B, d.X, d.R, d.Cord, d.Aord, d.E, d.n0x, d.rmax, d.bmax, d.xmax, d.status, d.dt, d.n,
-                                    d.npad, d.nx_total, nullptr);
+  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, s);
+  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, s);
 }
 
 namespace {

@@ -932,6 +932,35 @@ def test_split_operand_updates_reproduce_the_matrix(torch, nr, nth):
         s.close()
 
 
+def test_residual_of_large_grids(torch):
+    """Refinement residuals by the 64 x 32 tiles (200 points, n = 2040: 256 tiles, the last of each
+    direction partly filled), against direct solves at points of the first, second and last tile
+    and, for the transposed residual, against the FP64 handle's adjoint step.  Tolerance: both
+    sides stop at 1e-14 of the right-hand side on matrices of small condition number."""
+    cfg = workloads.small_config(nx=200, nr=60, nth=34, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf")
+    ops = oracle.build_operators(cfg)
+    rng = np.random.default_rng(4)
+    F, L, E = _state(ops, 3), _state(ops, 10), rng.uniform(-1.2e4, 1.2e4, 200)
+    t = 0.21 * cfg["T_rf_s"]
+    lam = {}
+    for prec in ("mixed_fp32", "fp64"):
+        s = solver(cfg, precision=prec)
+        if prec != "fp64":
+            Fg = cuda(torch, F)
+            s.vstep(Fg, cuda(torch, E))
+            code, _, resid = s.status()
+            assert code == 0 and resid <= 1e-14
+            got = Fg.cpu().numpy().reshape(200, -1)
+            for x in (0, 63, 64, 199):
+                close(got[x], np.linalg.solve(S.v_matrix(ops, E[x]), F[x].ravel()), 1e-10, x)
+        Lg = cuda(torch, L)
+        s.adjoint_step(cuda(torch, F), t, Lg, torch.zeros(s.n_params, dtype=torch.float64, device="cuda:0"))
+        lam[prec] = Lg.cpu().numpy()
+        s.close()
+    close(lam["mixed_fp32"], lam["fp64"], 1e-10, "adjoint")
+
+
 def test_static_pivoting_is_rejected_for_fp64(torch):
     from paper_2502_16555_amd import _lib
     s = solver(CASES["ragged"](), precision="fp64")
