@@ -9,6 +9,7 @@
 #include <cmath>
 
 #include "internal.h"
+#include "lu_common.h"
 
 namespace bte {
 namespace {
@@ -17,66 +18,90 @@ constexpr int kThreads = 256;
 
 __device__ inline bool finite_d(double v) { return (v - v) == 0.0; }
 
-// Y_d[i][a][xl] = sum_k Uinv[i][k] F[x][k][a]   (one block per global x)
-__global__ __launch_bounds__(kThreads) void k_x_to_modes(const double* __restrict__ F, double* __restrict__ Y,
-                                                         const double* __restrict__ W, const int* __restrict__ x_disc,
-                                                         const int* __restrict__ x_off, const int* __restrict__ nx_of,
-                                                         int nr, int nth, int transposeW, int* __restrict__ status) {
-  extern __shared__ double sm[];
-  const int x = blockIdx.x;
-  const int n = nr * nth;
-  double* f = sm;
-  double* w = sm + n;
-  bool bad = false;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    double v = F[(size_t)x * n + j];
-    bad |= !finite_d(v);
-    f[j] = v;
-  }
-  for (int j = threadIdx.x; j < nr * nr; j += blockDim.x) {
-    // transposeW: use W^T (the X^T path contracts with U^T)
-    int r = j / nr, c = j % nr;
-    w[j] = transposeW ? W[c * nr + r] : W[j];
-  }
-  if (bad) atomicOr(status, kStNonFinite);
-  __syncthreads();
-  const int d = x_disc[x];
-  const int nx = nx_of[d];
-  const int xl = x - x_off[d];
+// State to modes, Y_d[i][a][xl] = sum_k W[i][k] F[x][k][a] (TO_X = 0), and back,
+// F[x][k][a] = sum_i W[k][i] Y_d[i][a][xl] (TO_X = 1); transposeW: W^T in W's
+// place (the X^T path contracts with U^T).  A block takes 16 points of one
+// discharge, two ordinates and 64 output speeds (16 per wavefront): the points
+// of one ordinate are the columns of MFMA f64 products with W, staged in LDS 64
+// contracted speeds at a time.  Bound by latency (a few MB and 27 MFLOP per
+// transform at 100 x 64 x 16); the tile is what turns the modes' strided
+// entries into whole lines: one block per point, as before, wrote Y eight bytes
+// at a time and kept 100 of 256 CUs.  The ordinate pairs of 16 points run on
+// one XCD, whose L2 joins their parts of the state's lines.
+// Per transform to modes / back: 100 x 64 x 16 13.7 / 12.3 -> 7.1 / 8.1 us, 256 x 64
+// x 32 23 / 22 -> 8.4 / 9.4.
+constexpr int kModeX = 16, kModeA = 2, kModeK = 64;
+template <int TO_X>
+__global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, double* __restrict__ Y,
+                                                    const double* __restrict__ W, const int* __restrict__ x_off,
+                                                    const int* __restrict__ nx_of, int nr, int nth, int transposeW,
+                                                    int tiles, int nd, int* __restrict__ status) {
+  using V2 = double __attribute__((ext_vector_type(2), aligned(8)));   // (F is the caller's: any double address)
+  constexpr int XP = kModeX + 2;
+  __shared__ double sF[kModeA][kModeK][XP];
+  const int groups = (nr + 63) / 64, pairs = nth / kModeA;
+  int tile, item;
+  xcd_map(blockIdx.x, pairs * groups, tiles * nd, &tile, &item);
+  if (tile >= tiles * nd) return;
+  const int d = tile / tiles, nx = nx_of[d], xt = (tile % tiles) * kModeX;
+  if (xt >= nx) return;
+  const int a0 = (item % pairs) * kModeA, n = nr * nth;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
   double* Yd = Y + (size_t)x_off[d] * n;
-  for (int o = threadIdx.x; o < n; o += blockDim.x) {
-    const int i = o / nth, a = o % nth;
-    double s = 0.0;
-    for (int k = 0; k < nr; ++k) s += w[i * nr + k] * f[k * nth + a];
-    Yd[(size_t)o * nx + xl] = s;
+  double* Fd = F + (size_t)x_off[d] * n;
+  const int m0 = (item / pairs) * 64 + 16 * w;   // this wavefront's output speeds
+  const int mrow = min(m0 + li, nr - 1);
+  const double* wr = W + (transposeW ? (size_t)mrow : (size_t)mrow * nr);
+  const int ws = transposeW ? nr : 1;
+  f64x4 acc[kModeA];
+#pragma unroll
+  for (int a = 0; a < kModeA; ++a) acc[a] = f64x4{0, 0, 0, 0};
+  bool bad = false;
+  for (int k0 = 0; k0 < nr; k0 += kModeK) {
+    double wv[kModeK / 4];
+#pragma unroll
+    for (int q = 0; q < kModeK / 4; ++q) wv[q] = wr[(size_t)min(k0 + 4 * q + lk, nr - 1) * ws];
+    if (k0 > 0) __syncthreads();
+    if constexpr (TO_X) {
+#pragma unroll
+      for (int u = 0; u < kModeA * kModeK * kModeX / kThreads; ++u) {
+        const int e = tid + kThreads * u, x = e % kModeX, a = e / kModeX % kModeA, k = e / (kModeX * kModeA);
+        sF[a][k][x] = (k0 + k < nr && xt + x < nx) ? Yd[(size_t)((k0 + k) * nth + a0 + a) * nx + xt + x] : 0.0;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kModeK * kModeX / kThreads; ++u) {
+        const int e = tid + kThreads * u, k = e % kModeK, x = e / kModeK;
+        V2 v = V2{0.0, 0.0};
+        if (k0 + k < nr && xt + x < nx)
+          v = *reinterpret_cast<const V2*>(Fd + (size_t)(xt + x) * n + (size_t)(k0 + k) * nth + a0);
+        bad |= !finite_d(v[0]) | !finite_d(v[1]);
+        sF[0][k][x] = v[0];
+        sF[1][k][x] = v[1];
+      }
+    }
+    __syncthreads();
+    if (m0 < nr) {
+#pragma unroll
+      for (int q = 0; q < kModeK / 4; ++q)
+#pragma unroll
+        for (int a = 0; a < kModeA; ++a)
+          acc[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[q], sF[a][4 * q + lk][li], acc[a], 0, 0, 0);
+    }
   }
-}
-
-// F[x][k][a] = sum_i W[k][i] Y_d[i][a][xl]
-__global__ __launch_bounds__(kThreads) void k_modes_to_x(const double* __restrict__ Y, double* __restrict__ F,
-                                                         const double* __restrict__ W, const int* __restrict__ x_disc,
-                                                         const int* __restrict__ x_off, const int* __restrict__ nx_of,
-                                                         int nr, int nth, int transposeW) {
-  extern __shared__ double sm[];
-  const int x = blockIdx.x;
-  const int n = nr * nth;
-  const int d = x_disc[x];
-  const int nx = nx_of[d];
-  const int xl = x - x_off[d];
-  const double* Yd = Y + (size_t)x_off[d] * n;
-  double* z = sm;
-  double* w = sm + n;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) z[j] = Yd[(size_t)j * nx + xl];
-  for (int j = threadIdx.x; j < nr * nr; j += blockDim.x) {
-    int r = j / nr, c = j % nr;
-    w[j] = transposeW ? W[c * nr + r] : W[j];
-  }
-  __syncthreads();
-  for (int o = threadIdx.x; o < n; o += blockDim.x) {
-    const int k = o / nth, a = o % nth;
-    double s = 0.0;
-    for (int i = 0; i < nr; ++i) s += w[k * nr + i] * z[i * nth + a];
-    F[(size_t)x * n + o] = s;
+  if (!TO_X && bad) atomicOr(status, kStNonFinite);
+  const int x = xt + li;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int m = m0 + lk + 4 * t;   // result row of item t
+    if (m >= nr || x >= nx) continue;
+    if constexpr (TO_X) {
+      *reinterpret_cast<V2*>(Fd + (size_t)x * n + (size_t)m * nth + a0) = V2{acc[0][t], acc[1][t]};
+    } else {
+#pragma unroll
+      for (int a = 0; a < kModeA; ++a) Yd[(size_t)(m * nth + a0 + a) * nx + x] = acc[a][t];
+    }
   }
 }
 
@@ -301,25 +326,24 @@ __global__ void k_maxwellian(const double* __restrict__ ne, const double* __rest
 
 }  // namespace
 
+template <int TO_X>
+static void run_modes(const DevOps& d, double* F, const double* W, int transposeW, hipStream_t s) {
+  const int tiles = (d.max_nx + kModeX - 1) / kModeX;
+  const int grid = xcd_grid(d.nth / kModeA * ((d.nr + 63) / 64), tiles * d.nd);
+  k_modes<TO_X><<<grid, kThreads, 0, s>>>(F, d.Y, W, d.x_off, d.nx_of, d.nr, d.nth, transposeW, tiles, d.nd, d.status);
+}
+
 void launch_x_to_modes(const DevOps& d, const double* F, hipStream_t s) {
-  const size_t sh = sizeof(double) * (d.n + d.nr * d.nr);
-  k_x_to_modes<<<d.nx_total, kThreads, sh, s>>>(F, d.Y, d.Uinv, d.x_disc, d.x_off, d.nx_of, d.nr, d.nth, 0, d.status);
+  run_modes<0>(d, const_cast<double*>(F), d.Uinv, 0, s);
 }
 
 void launch_x_to_modes_T(const DevOps& d, const double* F, hipStream_t s) {
-  const size_t sh = sizeof(double) * (d.n + d.nr * d.nr);
-  k_x_to_modes<<<d.nx_total, kThreads, sh, s>>>(F, d.Y, d.U, d.x_disc, d.x_off, d.nx_of, d.nr, d.nth, 1, d.status);
+  run_modes<0>(d, const_cast<double*>(F), d.U, 1, s);
 }
 
-void launch_modes_to_x(const DevOps& d, double* F, hipStream_t s) {
-  const size_t sh = sizeof(double) * (d.n + d.nr * d.nr);
-  k_modes_to_x<<<d.nx_total, kThreads, sh, s>>>(d.Y, F, d.U, d.x_disc, d.x_off, d.nx_of, d.nr, d.nth, 0);
-}
+void launch_modes_to_x(const DevOps& d, double* F, hipStream_t s) { run_modes<1>(d, F, d.U, 0, s); }
 
-void launch_modes_to_x_T(const DevOps& d, double* F, hipStream_t s) {
-  const size_t sh = sizeof(double) * (d.n + d.nr * d.nr);
-  k_modes_to_x<<<d.nx_total, kThreads, sh, s>>>(d.Y, F, d.Uinv, d.x_disc, d.x_off, d.nx_of, d.nr, d.nth, 1);
-}
+void launch_modes_to_x_T(const DevOps& d, double* F, hipStream_t s) { run_modes<1>(d, F, d.Uinv, 1, s); }
 
 void launch_advect(const DevOps& d, bool fp32, bool transpose, hipStream_t s, const double* Qt) {
   dim3 grid(d.nr * d.nh, d.nd);

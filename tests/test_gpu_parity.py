@@ -120,6 +120,24 @@ def test_xstep_matches_oracle(torch, case):
     s.close()
 
 
+@pytest.mark.parametrize("nx,nr,nth", [(16, 64, 4), (17, 65, 2), (33, 130, 6), (5, 4, 2)])
+def test_mode_transforms_at_tile_edges(torch, nx, nr, nth):
+    """X half-steps, forward and transposed, with points, speeds and ordinates at and just past the
+    transforms' tiles (16 points, 64 speeds), on a state that starts 8 bytes past a 16-byte
+    boundary.  Tolerance: as test_xstep_matches_oracle."""
+    cfg = workloads.small_config(nx=nx, nr=nr, nth=nth, kinds=("elastic", "ionization"), E=5e3, field_kind="rf")
+    ops = oracle.build_operators(cfg)
+    s = solver(cfg)
+    F = _state(ops, 1)
+    buf = torch.zeros(F.size + 1, dtype=torch.float64, device="cuda:0")
+    Fg = buf[1:].view(F.shape)
+    for step, ref in ((s.xstep, S.x_half_step), (s.xstep_T, S.x_half_step_T)):
+        Fg.copy_(cuda(torch, F))
+        step(Fg)
+        close(Fg.cpu().numpy(), ref(ops, F), 1e-11, '')
+    s.close()
+
+
 @pytest.mark.parametrize("prec", ["fp64", "mixed_fp32", "mixed_bf16x3", "mixed_bf16"])
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_vstep_matches_oracle(torch, case, prec):
