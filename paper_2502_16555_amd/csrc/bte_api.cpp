@@ -40,9 +40,8 @@ struct HipError : std::runtime_error {
 struct ImplicitWs {
   int m = 0;                    // Krylov vectors per cycle the basis holds
   size_t N = 0;                 // unknowns (sum Nx * n)
-  double *Fn = nullptr, *R = nullptr, *Rt = nullptr, *dlt = nullptr, *tmp = nullptr, *z = nullptr, *u = nullptr;
+  double *Fn = nullptr, *R = nullptr, *Rt = nullptr, *dlt = nullptr, *z = nullptr, *u = nullptr;
   double *V = nullptr;          // [m + 1][N]
-  double *Pa = nullptr, *Pb = nullptr, *Pc = nullptr;   // padded rows
   double *El = nullptr, *zeros = nullptr;               // [sum Nx]
   double *partial = nullptr, *coef = nullptr;
   double* hcol = nullptr;       // [m + 1] the Hessenberg column of the current Arnoldi step
@@ -558,10 +557,10 @@ void v_solve(bte_handle* h, double* F, bool transpose, hipStream_t s, bool allow
 // refine = false: one solve with the stored (possibly FP32) factors, no
 // refinement -- a fixed linear map, as a preconditioner needs, accurate to the
 // factors' precision.
-void v_solve_again(bte_handle* h, double* F, bool transpose, hipStream_t s, bool refine = true) {
+void v_solve_again(bte_handle* h, const double* in, double* out, bool transpose, hipStream_t s, bool refine = true) {
   DevOps& d = h->d;
   const int prec = h->cfg.precision;
-  bte::launch_pad_rows(d, F, d.B, s);
+  bte::launch_pad_rows(d, in, d.B, s);
   bte::launch_lu_solve(d, prec, transpose, d.B, d.X, false, false, s);
   if (prec != BTE_FP64 && refine) {
     bte::launch_reset_refine(d, s);
@@ -573,7 +572,7 @@ void v_solve_again(bte_handle* h, double* F, bool transpose, hipStream_t s, bool
     bte::launch_residual(d, transpose, s);
     bte::launch_refine_check(d, transpose, h->refine_rtol, h->refine_max_iter, true, s);
   }
-  bte::launch_unpad_rows(d, d.X, F, s);
+  bte::launch_unpad_rows(d, d.X, out, s);
 }
 
 bool field_ok(const bte_handle* h, const bte_field& f) {
@@ -593,22 +592,15 @@ void eval_field(bte_handle* h, const double* Fh, double t_s, const bte_field& f,
 void implicit_alloc(bte_handle* h, int m, int precond) {
   ImplicitWs& w = h->iw;
   const DevOps& d = h->d;
-  const size_t N = (size_t)d.nx_total * d.n, P = (size_t)d.nx_total * d.npad;
+  const size_t N = (size_t)d.nx_total * d.n;
   if (w.N == 0) {
     w.N = N;
     w.Fn = h->alloc<double>(N);
     w.R = h->alloc<double>(N);
     w.Rt = h->alloc<double>(N);
     w.dlt = h->alloc<double>(N);
-    w.tmp = h->alloc<double>(N);
     w.z = h->alloc<double>(N);
     w.u = h->alloc<double>(N);
-    w.Pa = h->alloc<double>(P);
-    w.Pb = h->alloc<double>(P);
-    w.Pc = h->alloc<double>(P);
-    HIP_OK(hipMemset(w.Pa, 0, P * sizeof(double)));
-    HIP_OK(hipMemset(w.Pb, 0, P * sizeof(double)));
-    HIP_OK(hipMemset(w.Pc, 0, P * sizeof(double)));
     w.El = h->alloc<double>(d.nx_total);
     w.zeros = h->alloc<double>(d.nx_total);
     HIP_OK(hipMemset(w.zeros, 0, d.nx_total * sizeof(double)));
@@ -669,11 +661,11 @@ void imp_field(bte_handle* h, const double* F, double t1, const double* ni, doub
   bte::launch_field(h->d, c.field_mode, t1, c.field_freq_hz, c.field_a1, c.poisson_V0, F, nullptr, ni, E, s);
 }
 
-// out = A_x X D_x^T
-void imp_xop(bte_handle* h, const double* X, double* out, hipStream_t s) {
+// out <- out + dt A_x X D_x^T - Fn (Fn may be NULL), out = X at the inflow entries
+void imp_xop(bte_handle* h, const double* X, const double* Fn, double* out, hipStream_t s) {
   bte::launch_x_to_modes(h->d, X, s);
   bte::launch_x_forward(h->d, s);
-  bte::launch_modes_to_x(h->d, out, s);
+  bte::launch_modes_to_rows(h->d, out, X, Fn, s);
 }
 
 // R = F - F^n + dt A_x F D_x^T - dt (n0 C + E(F) A) F, R = F at the inflow entries; d.E <- E(F)
@@ -681,13 +673,8 @@ void imp_residual(bte_handle* h, const double* F, const double* ni, double t1, d
   DevOps& d = h->d;
   ImplicitWs& iw = h->iw;
   imp_field(h, F, t1, ni, d.E, s);
-  bte::launch_pad_rows(d, F, iw.Pa, s);
-  bte::launch_apply_field(d, 2, nullptr, iw.Pa, iw.Pb, d.E, s);
-  bte::launch_unpad_rows(d, iw.Pb, R, s);
-  imp_xop(h, F, iw.tmp, s);
-  bte::launch_axpby(R, iw.tmp, 1.0, d.dt, iw.N, s);
-  bte::launch_axpby(R, iw.Fn, 1.0, -1.0, iw.N, s);
-  bte::launch_wall_rows(d, R, F, s);
+  bte::launch_apply_field(d, 2, nullptr, F, R, d.E, s);
+  imp_xop(h, F, iw.Fn, R, s);
 }
 
 // out = J_F X (eq. 1dbte_jac_action in residual form), with d.E = E(F); without
@@ -697,18 +684,13 @@ void imp_jac(bte_handle* h, const double* F, const double* X, double* out, bool 
   DevOps& d = h->d;
   ImplicitWs& iw = h->iw;
   const bte_config& c = h->cfg;
-  bte::launch_pad_rows(d, X, iw.Pa, s);
-  bte::launch_apply_field(d, 2, nullptr, iw.Pa, iw.Pb, d.E, s);
+  bte::launch_apply_field(d, 2, nullptr, X, out, d.E, s);
   if (coupling && c.field_mode == BTE_FIELD_POISSON) {
     // E_lin(X) = L (0 - u^T X): the derivative of the affine field map
     bte::launch_field(d, BTE_FIELD_POISSON, 0.0, c.field_freq_hz, c.field_a1, 0.0, X, nullptr, iw.zeros, iw.El, s);
-    bte::launch_pad_rows(d, F, iw.Pc, s);
-    bte::launch_apply_field(d, 3, iw.Pb, iw.Pc, iw.Pb, iw.El, s);
+    bte::launch_apply_field(d, 3, out, F, out, iw.El, s);
   }
-  bte::launch_unpad_rows(d, iw.Pb, out, s);
-  imp_xop(h, X, iw.tmp, s);
-  bte::launch_axpby(out, iw.tmp, 1.0, d.dt, iw.N, s);
-  bte::launch_wall_rows(d, out, X, s);
+  imp_xop(h, X, nullptr, out, s);
 }
 
 // z = S v with the field frozen (factors of d.E).  BTE_PRECOND_SPLIT:
@@ -718,14 +700,14 @@ void imp_jac(bte_handle* h, const double* F, const double* X, double* out, bool 
 // BTE_PRECOND_SEMI_IMPLICIT: the semi-implicit step X(dt/2) V(dt) X(dt/2), whose
 // inverse differs from J by dt^2 X^2 / 4 + ..., large on the stiff x modes.
 void imp_precond(bte_handle* h, const double* v, double* z, int kind, hipStream_t s) {
-  HIP_OK(hipMemcpyAsync(z, v, sizeof(double) * h->iw.N, hipMemcpyDeviceToDevice, s));
   if (kind == BTE_PRECOND_SEMI_IMPLICIT) {
+    HIP_OK(hipMemcpyAsync(z, v, sizeof(double) * h->iw.N, hipMemcpyDeviceToDevice, s));
     x_half(h, z, false, s);
-    v_solve_again(h, z, false, s, false);
+    v_solve_again(h, z, z, false, s, false);
     x_half(h, z, false, s);
     return;
   }
-  v_solve_again(h, z, false, s, false);
+  v_solve_again(h, v, z, false, s, false);
   bte::launch_x_to_modes(h->d, z, s);
   bte::launch_advect(h->d, false, false, s, h->iw.Qx);
   bte::launch_modes_to_x(h->d, z, s);
@@ -764,8 +746,7 @@ int imp_gmres(bte_handle* h, const double* F, double rtol, int m, int maxit, int
         bte::launch_comb(w, 1.0, V, iw.coef, j + 1, N, N, s);
       }
       bte::launch_dots(w, w, 1, N, N, iw.partial, s);
-      bte::launch_norm_reduce(iw.partial, iw.hcol + j + 1, s);
-      bte::launch_scale_inv(w, iw.hcol + j + 1, N, s);
+      bte::launch_normalize(w, iw.partial, iw.hcol + j + 1, N, s);
       HIP_OK(hipMemcpyAsync(hc.data(), iw.hcol, sizeof(double) * (j + 2), hipMemcpyDeviceToHost, s));
       HIP_OK(hipStreamSynchronize(s));
       const double hn = hc[j + 1];
@@ -1262,7 +1243,7 @@ bte_status bte_adjoint_step(bte_handle* h, const double* F_n, double t_s, bte_fi
     // mu = A^-T X^T lam
     HIP_OK(hipMemcpyAsync(d.mu, lam, nb, hipMemcpyDeviceToDevice, s));
     x_half(h, d.mu, true, s);
-    v_solve_again(h, d.mu, true, s);
+    v_solve_again(h, d.mu, d.mu, true, s);
     // gradients
     bte::launch_adjoint_grads(d, grad_scal, h->d_gE, s);
     if (grad_E) HIP_OK(hipMemcpyAsync(grad_E, h->d_gE, sizeof(double) * d.nx_total, hipMemcpyDeviceToDevice, s));

@@ -160,8 +160,9 @@ hipError_t ion_scratch(double** out);
 // ---- fully implicit step (kernels_implicit.hip) -------------------------------
 // d.Y <- A_x applied mode by mode (lambda_i cos theta_a D_x) to the modes in d.Y.
 void launch_x_forward(const DevOps& d, hipStream_t s);
-// out = X at the inflow entries of every discharge's walls.
-void launch_wall_rows(const DevOps& d, double* out, const double* X, hipStream_t s);
+// Modes back into the rows of the fully implicit system: R <- R + dt (U (x) I) Y - Fn
+// (Fn may be NULL), and R = X at the inflow entries of every discharge's walls.
+void launch_modes_to_rows(const DevOps& d, double* R, const double* X, const double* Fn, hipStream_t s);
 int dot_blocks();
 // partial[b][v] (b < dot_blocks()) = partial sums of w . V_v, v < nvec.
 void launch_dots(const double* w, const double* V, int nvec, size_t stride, size_t N, double* partial,
@@ -170,13 +171,12 @@ void launch_dots(const double* w, const double* V, int nvec, size_t stride, size
 void launch_comb(double* y, double beta, const double* V, const double* coef, int nvec, size_t stride, size_t N,
                  hipStream_t s);
 void launch_axpby(double* y, const double* x, double a, double b, size_t N, hipStream_t s);
-// One Gram-Schmidt pass from launch_dots' partials (block order): h[v] = t_v, or
+// One Gram-Schmidt pass from launch_dots' partials (fixed order): h[v] = t_v, or
 // h[v] += t_v with accumulate, and coef[v] = -t_v, v < nvec.
 void launch_gs_reduce(const double* partial, int nvec, int accumulate, double* h, double* coef, hipStream_t s);
 // *h = ||w|| from launch_dots(w, w, 1, ...) partials; y /= *h where *h > 0.
-void launch_norm_reduce(const double* partial, double* h, hipStream_t s);
-void launch_scale_inv(double* y, const double* h, size_t N, hipStream_t s);
-// Operator action on padded rows with a given field: mode 2: R = (I - dt (n0 C + E A)) X;
+void launch_normalize(double* y, const double* partial, double* h, size_t N, hipStream_t s);
+// Operator action on rows of n with a given field: mode 2: R = (I - dt (n0 C + E A)) X;
 // mode 3: R = B - dt E (X A^T).
 void launch_apply_field(const DevOps& d, int mode, const double* B, const double* X, double* R, const double* E,
                         hipStream_t s);
@@ -275,7 +275,7 @@ void launch_unpad_rows(const DevOps& d, const double* Bp, double* F, hipStream_t
 // FP64 residual R = B - (I - dt (n0 C + E A)) X (or with A^T for transpose) + per-x norms.
 void launch_residual(const DevOps& d, bool transpose, hipStream_t s);
 // Operator M = I - dt (n0 C + E A) on padded rows: mode 1: R = B - M X; mode 2: R = M X.
-// Tiles of 32 points that all have skip[x] != 0 are left out (skip may be NULL).
+// Tiles of 32 or 64 points that all have skip[x] != 0 are left out (skip may be NULL).
 void launch_apply(const DevOps& d, int mode, const double* B, const double* X, double* R, const int* skip,
                   hipStream_t s);
 void launch_refine_check(const DevOps& d, bool transpose, double rtol, int sweep, bool final_sweep, hipStream_t s);

@@ -1,11 +1,11 @@
 // Pieces of the fully implicit electron step (eq. bte_fully_implicit) that the
 // semi-implicit kernels do not already provide: the forward spatial operator
-// A_x F D_x^T in the speed eigenbasis, the wall rows of the implicit system,
-// and the vector kernels of the Newton-Krylov driver (batched dot products with
+// A_x F D_x^T in the speed eigenbasis and the vector kernels of the Newton-Krylov driver (batched dot products with
 // deterministic two-stage sums, linear combinations).
 #include <stdexcept>
 
 #include "internal.h"
+#include "lu_common.h"
 
 namespace bte {
 namespace {
@@ -16,53 +16,56 @@ constexpr int kDotBlocks = 256;
 // Y_ia <- lambda_i cos(theta_a) D_x Y_ia for every mode of every discharge
 // (mode-major Y of the X step: the modes of discharge d at Y + x_off[d] n, one
 // row of nx_d per mode); A_x = U Lambda U^-1 (x) diag(cos theta).  D_x is read
-// column-major (entry (x, k) at k nx + x), so that a load over the threads' x is
-// one coalesced row of D_x^T, and each loaded entry serves the MB modes of the
-// block; every output takes its products in ascending k.
-template <int MB>
-__global__ __launch_bounds__(kThreads) void k_x_fwd(double* __restrict__ Y, const double* __restrict__ DT,
-                                                    const size_t* __restrict__ dx_off, const double* __restrict__ lam,
-                                                    const double* __restrict__ mu, const int* __restrict__ x_off,
-                                                    const int* __restrict__ nx_of, int nth, int n) {
-  extern __shared__ double sy[];   // [MB][nx]
-  const int o0 = blockIdx.x * MB, d = blockIdx.y;
-  const int nx = nx_of[d], nm = min(MB, n - o0);
+// column-major (entry (x, k) at k nx + x).  A block takes 16 modes, the rows of
+// MFMA f64 products with D_x^T; its eight wavefronts take the tiles of 16 points
+// in turn (TW tiles each at most, held until all have read their modes).  Bound
+// by latency and D_x's way through the vector cache: 100 points x 1024 modes
+// 14 -> 10.7 us (a thread per point and eight modes before: 100 threads of 256).
+template <int TW>
+__global__ __launch_bounds__(512) void k_x_fwd(double* __restrict__ Y, const double* __restrict__ DT,
+                                               const size_t* __restrict__ dx_off, const double* __restrict__ lam,
+                                               const double* __restrict__ mu, const int* __restrict__ x_off,
+                                               const int* __restrict__ nx_of, int nth, int n) {
+  constexpr int NW = 512 / 64;
+  const int o0 = blockIdx.x * 16, d = blockIdx.y, nx = nx_of[d];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
   double* y0 = Y + (size_t)x_off[d] * n;
-  for (int m = 0; m < MB; ++m)
-    for (int j = threadIdx.x; j < nx; j += blockDim.x) sy[m * nx + j] = m < nm ? y0[(size_t)(o0 + m) * nx + j] : 0.0;
-  __syncthreads();
   const double* D = DT + dx_off[d];
-  for (int x = threadIdx.x; x < nx; x += blockDim.x) {
-    double acc[MB];
+  const double* yr = y0 + (size_t)min(o0 + li, n - 1) * nx;
+  int xc[TW];   // this lane's point in each tile (beyond the last: repeated, dropped below)
 #pragma unroll
-    for (int m = 0; m < MB; ++m) acc[m] = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < nx; ++k) {
-      const double dk = D[(size_t)k * nx + x];
+  for (int t = 0; t < TW; ++t) xc[t] = min(16 * (w + NW * t) + li, nx - 1);
+  f64x4 acc[TW];
 #pragma unroll
-      for (int m = 0; m < MB; ++m) acc[m] += dk * sy[m * nx + k];
+  for (int t = 0; t < TW; ++t) acc[t] = f64x4{0, 0, 0, 0};
+  const int steps = (nx + 3) / 4;
+  constexpr int UN = 16 / TW;   // steps whose loads are on their way together
+  for (int q0 = 0; q0 < steps; q0 += UN) {
+    double yv[UN], dv[UN][TW];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int k = 4 * (q0 + u) + lk, kc = min(k, nx - 1);
+      yv[u] = yr[kc];
+#pragma unroll
+      for (int t = 0; t < TW; ++t) dv[u][t] = D[(size_t)kc * nx + xc[t]];
     }
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
-      if (m < nm) {
-        const int o = o0 + m;
-        y0[(size_t)o * nx + x] = lam[o / nth] * mu[o % nth] * acc[m];
-      }
+    for (int u = 0; u < UN; ++u) {
+      const double y = 4 * (q0 + u) + lk < nx ? yv[u] : 0.0;
+#pragma unroll
+      for (int t = 0; t < TW; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, dv[u][t], acc[t], 0, 0, 0);
     }
   }
-}
-
-// out = X at the inflow entries (x = 0 for cos theta > 0, x = L for cos theta < 0)
-__global__ __launch_bounds__(kThreads) void k_wall_rows(double* __restrict__ out, const double* __restrict__ X,
-                                                        const int* __restrict__ x_disc, const int* __restrict__ x_off,
-                                                        const int* __restrict__ nx_of, const double* __restrict__ mu,
-                                                        int nth, int n) {
-  const int x = blockIdx.x, d = x_disc[x];
-  const int xl = x - x_off[d], nx = nx_of[d];
-  if (xl != 0 && xl != nx - 1) return;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const double m = mu[e % nth];
-    if ((xl == 0 && m > 0.0) || (xl == nx - 1 && m < 0.0)) out[(size_t)x * n + e] = X[(size_t)x * n + e];
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    const int x = 16 * (w + NW * t) + li;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int o = o0 + lk + 4 * i;   // result row of item i
+      if (x < nx && o < n) y0[(size_t)o * nx + x] = lam[o / nth] * mu[o % nth] * acc[t][i];
+    }
   }
 }
 
@@ -99,34 +102,37 @@ __global__ __launch_bounds__(kThreads) void k_comb(double* __restrict__ y, doubl
   }
 }
 
-// The Gram-Schmidt coefficients of one pass from k_dots' partial sums, summed
-// over the blocks in block order (the same order on every call): h[v] = t_v
-// (first pass) or h[v] + t_v (second pass), coef[v] = -t_v for k_comb.
-__global__ __launch_bounds__(kThreads) void k_gs_reduce(const double* __restrict__ partial, int nvec, int nb,
-                                                        int accumulate, double* __restrict__ h,
-                                                        double* __restrict__ coef) {
-  for (int v = threadIdx.x; v < nvec; v += blockDim.x) {
-    double t = 0.0;
-    for (int b = 0; b < nb; ++b) t += partial[(size_t)b * nvec + v];
+// Sum of k_dots' partial sums of one vector, one thread per block of k_dots, in a
+// fixed order (a serial sum of the 256 took 27 us of latency); on every thread.
+__device__ inline double dot_sum(const double* __restrict__ partial, int stride) {
+  static_assert(kDotBlocks == kThreads, "one partial sum per thread");
+  __shared__ double red[kThreads / 64];
+  double t = partial[(size_t)threadIdx.x * stride];
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// The Gram-Schmidt coefficients of one pass from k_dots' partial sums, a block
+// per vector: h[v] = t_v (first pass) or h[v] + t_v (second pass), coef[v] =
+// -t_v for k_comb.
+__global__ __launch_bounds__(kThreads) void k_gs_reduce(const double* __restrict__ partial, int nvec, int accumulate,
+                                                        double* __restrict__ h, double* __restrict__ coef) {
+  const int v = blockIdx.x;
+  const double t = dot_sum(partial + v, nvec);
+  if (threadIdx.x == 0) {
     h[v] = accumulate ? h[v] + t : t;
     coef[v] = -t;
   }
 }
 
-// *h = sqrt of k_dots' single partial sums (w . w), summed in block order
-__global__ __launch_bounds__(64) void k_norm_reduce(const double* __restrict__ partial, int nb,
-                                                    double* __restrict__ h) {
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int b = 0; b < nb; ++b) t += partial[b];
-    *h = sqrt(t);
-  }
-}
-
-// y = y / *h where *h > 0 (else y is left as it is)
-__global__ __launch_bounds__(kThreads) void k_scale_inv(double* __restrict__ y, const double* __restrict__ h,
-                                                        size_t N) {
-  const double hv = *h;
+// *h = sqrt(t), t = w . w from k_dots' partial sums; y = y / *h where *h > 0
+// (else y is left as it is).  Every block sums the partials itself.
+__global__ __launch_bounds__(kThreads) void k_normalize(double* __restrict__ y, const double* __restrict__ partial,
+                                                        double* __restrict__ h, size_t N) {
+  const double hv = sqrt(dot_sum(partial, 1));
+  if (blockIdx.x == 0 && threadIdx.x == 0) *h = hv;
   if (!(hv > 0.0)) return;
   const double a = 1.0 / hv;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
@@ -143,16 +149,16 @@ __global__ __launch_bounds__(kThreads) void k_axpby(double* __restrict__ y, cons
 }  // namespace
 
 void launch_x_forward(const DevOps& d, hipStream_t s) {
-  // eight modes per block: their rows take at most 64 KB of LDS (Nx <= 1024)
-  constexpr int MB = 8;
-  if ((size_t)MB * d.max_nx * sizeof(double) > 65536) throw std::invalid_argument("Nx above 1024");
-  dim3 g((d.n + MB - 1) / MB, d.nd);
-  k_x_fwd<MB><<<g, kThreads, sizeof(double) * MB * d.max_nx, s>>>(d.Y, d.dxT, d.p_off, d.lam, d.mu_th, d.x_off,
-                                                                   d.nx_of, d.nth, d.n);
-}
-
-void launch_wall_rows(const DevOps& d, double* out, const double* X, hipStream_t s) {
-  k_wall_rows<<<d.nx_total, kThreads, 0, s>>>(out, X, d.x_disc, d.x_off, d.nx_of, d.mu_th, d.nth, d.n);
+  if (d.max_nx > 1024) throw std::invalid_argument("Nx above 1024");
+  dim3 g((d.n + 15) / 16, d.nd);
+  auto go = [&](auto tw) {
+    k_x_fwd<decltype(tw)::value><<<g, 512, 0, s>>>(d.Y, d.dxT, d.p_off, d.lam, d.mu_th, d.x_off, d.nx_of, d.nth, d.n);
+  };
+  // 16-point tiles per wavefront
+  if (d.max_nx <= 128) go(std::integral_constant<int, 1>());
+  else if (d.max_nx <= 256) go(std::integral_constant<int, 2>());
+  else if (d.max_nx <= 512) go(std::integral_constant<int, 4>());
+  else go(std::integral_constant<int, 8>());
 }
 
 int dot_blocks() { return kDotBlocks; }
@@ -168,15 +174,11 @@ void launch_comb(double* y, double beta, const double* V, const double* coef, in
 }
 
 void launch_gs_reduce(const double* partial, int nvec, int accumulate, double* h, double* coef, hipStream_t s) {
-  k_gs_reduce<<<1, kThreads, 0, s>>>(partial, nvec, kDotBlocks, accumulate, h, coef);
+  k_gs_reduce<<<nvec, kThreads, 0, s>>>(partial, nvec, accumulate, h, coef);
 }
 
-void launch_norm_reduce(const double* partial, double* h, hipStream_t s) {
-  k_norm_reduce<<<1, 64, 0, s>>>(partial, kDotBlocks, h);
-}
-
-void launch_scale_inv(double* y, const double* h, size_t N, hipStream_t s) {
-  k_scale_inv<<<1024, kThreads, 0, s>>>(y, h, N);
+void launch_normalize(double* y, const double* partial, double* h, size_t N, hipStream_t s) {
+  k_normalize<<<1024, kThreads, 0, s>>>(y, partial, h, N);
 }
 
 void launch_axpby(double* y, const double* x, double a, double b, size_t N, hipStream_t s) {

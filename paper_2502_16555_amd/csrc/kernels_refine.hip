@@ -17,22 +17,21 @@ using f64x4 = double __attribute__((ext_vector_type(4)));
 // Result row of item t of lane group lk for MFMA f64 16x16x4 (measured layout).
 __device__ inline int f64_row(int lk, int t) { return lk + 4 * t; }
 
-__global__ void k_pad(const double* __restrict__ F, double* __restrict__ Bp, int n, int npad, int nx) {
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < (size_t)nx * npad;
-       idx += (size_t)gridDim.x * blockDim.x) {
-    const size_t x = idx / npad;
-    const int j = static_cast<int>(idx % npad);
-    Bp[idx] = (j < n) ? F[x * n + j] : 0.0;
-  }
+// Rows of n entries (the caller's, at any double address) <-> rows padded with
+// zeros to npad, a block per row (n is even: two ordinates per mu).
+using V2u = double __attribute__((ext_vector_type(2), aligned(8)));
+__global__ __launch_bounds__(256) void k_pad(const double* __restrict__ F, double* __restrict__ Bp, int n, int npad) {
+  const double* f = F + (size_t)blockIdx.x * n;
+  double* b = Bp + (size_t)blockIdx.x * npad;
+  for (int j = 2 * threadIdx.x; j < npad; j += 512)
+    *reinterpret_cast<V2u*>(b + j) = j < n ? *reinterpret_cast<const V2u*>(f + j) : V2u{0.0, 0.0};
 }
 
-__global__ void k_unpad(const double* __restrict__ Bp, double* __restrict__ F, int n, int npad, int nx) {
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < (size_t)nx * n;
-       idx += (size_t)gridDim.x * blockDim.x) {
-    const size_t x = idx / n;
-    const int j = static_cast<int>(idx % n);
-    F[idx] = Bp[x * npad + j];
-  }
+__global__ __launch_bounds__(256) void k_unpad(const double* __restrict__ Bp, double* __restrict__ F, int n, int npad) {
+  const double* b = Bp + (size_t)blockIdx.x * npad;
+  double* f = F + (size_t)blockIdx.x * n;
+  for (int j = 2 * threadIdx.x; j < n; j += 512)
+    *reinterpret_cast<V2u*>(f + j) = *reinterpret_cast<const V2u*>(b + j);
 }
 
 // Ordinates <-> harmonics of every point: harmonic coefficients
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(256) void k_from_harm(const double* __restrict__ Xh
 
 // ---------------------------------------------------------------------------
 // FP64 residual R = B - X + dt n0_x (X C^T) + dt E_x (X A^T)  (TRANSPOSE: C, A)
-// rows = collocation points.  MODE 0: the refinement residual, with the
+// rows = collocation points, ld doubles apart.  MODE 0: the refinement residual, with the
 // per-point maxima (skipped once the refinement is done); MODE 1: R = B - M X
 // only; MODE 2: R = M X (operator action of Alg. vspace_action, for the Krylov
 // solver); MODE 3: R = B - dt E (X A^T) (the field-coupling term of the fully
@@ -111,7 +110,7 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
                                                       unsigned long long* __restrict__ rmax,
                                                       unsigned long long* __restrict__ bmax,
                                                       unsigned long long* __restrict__ xmax,
-                                                      const int* __restrict__ status, double dt, int n, int npad,
+                                                      const int* __restrict__ status, double dt, int n, int ld,
                                                       int nx, const int* __restrict__ skip) {
   if (MODE == 0 && status[1]) return;
   constexpr int BM = 16 * PT, BN = 16 * OT, CK = 16;
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
   const double* xp[PT];
   const double* op[NOP][OT];
 #pragma unroll
-  for (int p = 0; p < PT; ++p) xp[p] = Xv + (size_t)min(x0 + p * 16 + li, nx - 1) * npad;
+  for (int p = 0; p < PT; ++p) xp[p] = Xv + (size_t)min(x0 + p * 16 + li, nx - 1) * ld;
 #pragma unroll
   for (int o = 0; o < OT; ++o) {
     const size_t i = min(i0 + o * 16 + li, n - 1);
@@ -151,15 +150,15 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
     const int kc = CK * (w + NW * min(it, cnt - 1)) + 2 * lk;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int k = kc + 8 * j, ko = min(k, n - 2);   // X's rows are padded to npad, the operators' are not
+      const int k = min(kc + 8 * j, n - 2);
 #pragma unroll
-      for (int p = 0; p < PT; ++p) c.x[p][j] = *reinterpret_cast<const V2*>(xp[p] + k);
+      for (int p = 0; p < PT; ++p) c.x[p][j] = *reinterpret_cast<const V2u*>(xp[p] + k);
 #pragma unroll
       for (int q = 0; q < NOP; ++q)
 #pragma unroll
         for (int o = 0; o < OT; ++o) {
-          if constexpr (TRANSPOSE) c.m[q][o][j] = V2{op[q][o][(size_t)ko * n], op[q][o][(size_t)(ko + 1) * n]};
-          else c.m[q][o][j] = *reinterpret_cast<const V2*>(op[q][o] + ko);
+          if constexpr (TRANSPOSE) c.m[q][o][j] = V2{op[q][o][(size_t)k * n], op[q][o][(size_t)(k + 1) * n]};
+          else c.m[q][o][j] = *reinterpret_cast<const V2*>(op[q][o] + k);
         }
     }
   };
@@ -225,7 +224,7 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
         sA += s_part[u][0][xl][il];
         if constexpr (NOP == 2) sC += s_part[u][NOP - 1][xl][il];
       }
-      const size_t o = (size_t)x * npad + i;
+      const size_t o = (size_t)x * ld + i;
       if (MODE == 0) {
         const double bv = Bv[o], xv = Xv[o];
         const double r = bv - xv + dt * n0x[x] * sC + dt * E[x] * sA;
@@ -259,12 +258,12 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
 
 template <int TRANSPOSE, int MODE>
 void run_residual(const DevOps& d, const double* B, const double* X, double* R, const double* E, const int* skip,
-                  hipStream_t s) {
+                  int ld, hipStream_t s) {
   auto go = [&](auto pt, auto ot, auto nw) {
     constexpr int PT = decltype(pt)::value, OT = decltype(ot)::value, NW = decltype(nw)::value;
     const int grid = xcd_grid((d.nx_total + 16 * PT - 1) / (16 * PT), (d.n + 16 * OT - 1) / (16 * OT));
     k_residual<TRANSPOSE, MODE, PT, OT, NW><<<grid, NW * 64, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x, d.rmax, d.bmax,
-                                                                    d.xmax, d.status, d.dt, d.n, d.npad, d.nx_total,
+                                                                    d.xmax, d.status, d.dt, d.n, ld, d.nx_total,
                                                                     skip);
   };
   using std::integral_constant;
@@ -432,28 +431,28 @@ void launch_from_harm(const DevOps& d, int nl, int npad_h, const double* Xh, con
 }
 
 void launch_pad_rows(const DevOps& d, const double* F, double* Bp, hipStream_t s) {
-  k_pad<<<1024, 256, 0, s>>>(F, Bp, d.n, d.npad, d.nx_total);
+  k_pad<<<d.nx_total, 256, 0, s>>>(F, Bp, d.n, d.npad);
 }
 
 void launch_unpad_rows(const DevOps& d, const double* Bp, double* F, hipStream_t s) {
-  k_unpad<<<1024, 256, 0, s>>>(Bp, F, d.n, d.npad, d.nx_total);
+  k_unpad<<<d.nx_total, 256, 0, s>>>(Bp, F, d.n, d.npad);
 }
 
 void launch_apply(const DevOps& d, int mode, const double* B, const double* X, double* R, const int* skip,
                   hipStream_t s) {
-  if (mode == 1) run_residual<0, 1>(d, B, X, R, d.E, skip, s);
-  else run_residual<0, 2>(d, B, X, R, d.E, skip, s);
+  if (mode == 1) run_residual<0, 1>(d, B, X, R, d.E, skip, d.npad, s);
+  else run_residual<0, 2>(d, B, X, R, d.E, skip, d.npad, s);
 }
 
 void launch_apply_field(const DevOps& d, int mode, const double* B, const double* X, double* R, const double* E,
                         hipStream_t s) {
-  if (mode == 3) run_residual<0, 3>(d, B, X, R, E, nullptr, s);
-  else run_residual<0, 2>(d, B, X, R, E, nullptr, s);
+  if (mode == 3) run_residual<0, 3>(d, B, X, R, E, nullptr, d.n, s);
+  else run_residual<0, 2>(d, B, X, R, E, nullptr, d.n, s);
 }
 
 void launch_residual(const DevOps& d, bool transpose, hipStream_t s) {
-  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, s);
-  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, s);
+  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s);
+  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s);
 }
 
 namespace {

@@ -20,7 +20,9 @@ __device__ inline bool finite_d(double v) { return (v - v) == 0.0; }
 
 // State to modes, Y_d[i][a][xl] = sum_k W[i][k] F[x][k][a] (TO_X = 0), and back,
 // F[x][k][a] = sum_i W[k][i] Y_d[i][a][xl] (TO_X = 1); transposeW: W^T in W's
-// place (the X^T path contracts with U^T).  A block takes 16 points of one
+// place (the X^T path contracts with U^T).  TO_X = 2 adds the sums to the rows of
+// the fully implicit system: F <- F + dt sum - Fn (Fn may be NULL), and F = X at
+// the inflow entries (x = 0 for cos theta > 0, x = L for cos theta < 0).  A block takes 16 points of one
 // discharge, two ordinates and 64 output speeds (16 per wavefront): the points
 // of one ordinate are the columns of MFMA f64 products with W, staged in LDS 64
 // contracted speeds at a time.  Bound by latency (a few MB and 27 MFLOP per
@@ -35,7 +37,9 @@ template <int TO_X>
 __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, double* __restrict__ Y,
                                                     const double* __restrict__ W, const int* __restrict__ x_off,
                                                     const int* __restrict__ nx_of, int nr, int nth, int transposeW,
-                                                    int tiles, int nd, int* __restrict__ status) {
+                                                    int tiles, int nd, int* __restrict__ status,
+                                                    const double* __restrict__ X, const double* __restrict__ Fn,
+                                                    const double* __restrict__ mu, double dt) {
   using V2 = double __attribute__((ext_vector_type(2), aligned(8)));   // (F is the caller's: any double address)
   constexpr int XP = kModeX + 2;
   __shared__ double sF[kModeA][kModeK][XP];
@@ -97,7 +101,19 @@ __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, doub
     const int m = m0 + lk + 4 * t;   // result row of item t
     if (m >= nr || x >= nx) continue;
     if constexpr (TO_X) {
-      *reinterpret_cast<V2*>(Fd + (size_t)x * n + (size_t)m * nth + a0) = V2{acc[0][t], acc[1][t]};
+      const size_t o = (size_t)x * n + (size_t)m * nth + a0, og = (size_t)x_off[d] * n + o;
+      V2 v = V2{acc[0][t], acc[1][t]};
+      if constexpr (TO_X == 2) {
+        const V2 f = *reinterpret_cast<const V2*>(Fd + o), xv = *reinterpret_cast<const V2*>(X + og);
+        const V2 fn = Fn ? *reinterpret_cast<const V2*>(Fn + og) : V2{0.0, 0.0};
+#pragma unroll
+        for (int a = 0; a < kModeA; ++a) {
+          const double c = mu[a0 + a];
+          const bool inflow = (x == 0 && c > 0.0) | (x == nx - 1 && c < 0.0);
+          v[a] = inflow ? xv[a] : f[a] + dt * v[a] - fn[a];
+        }
+      }
+      *reinterpret_cast<V2*>(Fd + o) = v;
     } else {
 #pragma unroll
       for (int a = 0; a < kModeA; ++a) Yd[(size_t)(m * nth + a0 + a) * nx + x] = acc[a][t];
@@ -327,10 +343,12 @@ __global__ void k_maxwellian(const double* __restrict__ ne, const double* __rest
 }  // namespace
 
 template <int TO_X>
-static void run_modes(const DevOps& d, double* F, const double* W, int transposeW, hipStream_t s) {
+static void run_modes(const DevOps& d, double* F, const double* W, int transposeW, hipStream_t s,
+                      const double* X = nullptr, const double* Fn = nullptr) {
   const int tiles = (d.max_nx + kModeX - 1) / kModeX;
   const int grid = xcd_grid(d.nth / kModeA * ((d.nr + 63) / 64), tiles * d.nd);
-  k_modes<TO_X><<<grid, kThreads, 0, s>>>(F, d.Y, W, d.x_off, d.nx_of, d.nr, d.nth, transposeW, tiles, d.nd, d.status);
+  k_modes<TO_X><<<grid, kThreads, 0, s>>>(F, d.Y, W, d.x_off, d.nx_of, d.nr, d.nth, transposeW, tiles, d.nd, d.status,
+                                         X, Fn, d.mu_th, d.dt);
 }
 
 void launch_x_to_modes(const DevOps& d, const double* F, hipStream_t s) {
@@ -342,6 +360,10 @@ void launch_x_to_modes_T(const DevOps& d, const double* F, hipStream_t s) {
 }
 
 void launch_modes_to_x(const DevOps& d, double* F, hipStream_t s) { run_modes<1>(d, F, d.U, 0, s); }
+
+void launch_modes_to_rows(const DevOps& d, double* R, const double* X, const double* Fn, hipStream_t s) {
+  run_modes<2>(d, R, d.U, 0, s, X, Fn);
+}
 
 void launch_modes_to_x_T(const DevOps& d, double* F, hipStream_t s) { run_modes<1>(d, F, d.Uinv, 1, s); }
 

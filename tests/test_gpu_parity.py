@@ -575,6 +575,23 @@ def test_implicit_step_at_largest_nx_solves_oracle_equations(torch):
     s.close()
 
 
+@pytest.mark.parametrize("nx,nr,nth", [(17, 5, 2), (129, 4, 2), (257, 6, 4), (513, 4, 2)])
+def test_implicit_step_at_tile_edges(torch, nx, nr, nth):
+    """The forward x operator with one to eight tiles of 16 points per wavefront and partly filled
+    tiles of modes (n = 10, 8, 24, 8); as the test above."""
+    from oracle import implicit as I
+    cfg = workloads.small_config(nx=nx, nr=nr, nth=nth, kinds=("elastic",), E=2e3, field_kind="const", n_bins=1)
+    ops = oracle.build_operators(cfg)
+    F0 = S.initial_state(ops, workloads.density_profile(ops.xhat, 1e16), 2.0)
+    s = solver(cfg, precision="fp64")
+    F = cuda(torch, F0)
+    st = s.implicit_step(F, 0.0, newton_rtol=1e-12, gmres_rtol=1e-10, restart=60, max_gmres=600)
+    assert st["status"] == 0, st
+    r = I.residual(ops, F.cpu().numpy(), F0, ops.dt)
+    assert np.linalg.norm(r) <= 1e-11 * np.linalg.norm(F0), (np.linalg.norm(r), st)
+    s.close()
+
+
 def test_implicit_rejects_unknown_preconditioner(torch):
     cfg = workloads.small_config(nx=9, nr=10, nth=6, field_kind="rf")
     ops = oracle.build_operators(cfg)
