@@ -7,13 +7,12 @@
 // coefficients are those of the table of modeling parameters (n0 mu_i and
 // n0 D_i).  One Nx x Nx dense system per discharge, formed and solved by
 // Gaussian elimination with partial pivoting in one block per discharge.
-#include <cfloat>
-#include <climits>
 #include <mutex>
 #include <type_traits>
 
 #include "internal.h"
 #include "lu_common.h"
+#include "pivot_steps.h"
 
 namespace bte {
 namespace {
@@ -71,38 +70,47 @@ __global__ __launch_bounds__(kIonThreads) void k_ion_form(const double* __restri
   }
 }
 
-constexpr int kIonSolveThreads = 1024;
+// ---------------------------------------------------------------------------
 // Gaussian elimination with partial pivoting (max |a|, ties to the lowest row)
-// on [M | b] of one discharge in one block, blocked: panels of W columns factored in LDS
-// (pivot, interchange, multipliers and the panel's own update per column, all
-// on the LDS copy), then for the columns outside the panel and b the panel's
-// interchanges as one gather / scatter, U12 by substitution with the panel's
-// unit lower block, and one rank-W update of the trailing matrix and b.  The
-// trailing matrix is read and written once per panel instead of once per
-// column; the pivots (max |a|, ties to the lowest row) are those of the
-// unblocked kernel.
-template <int W>
-__global__ __launch_bounds__(kIonSolveThreads) void k_ion_solve_blk(double* __restrict__ M, double* __restrict__ b,
-                                                                    double* __restrict__ out,
-                                                                    const int* __restrict__ x_off,
-                                                                    const int* __restrict__ nx_of,
-                                                                    const size_t* __restrict__ m_off,
-                                                                    int* __restrict__ status, int ldp, double dt) {
-  constexpr int NT = kIonSolveThreads, NW = NT / 64;
+// on [M | b] of one discharge in one block, 16 columns at a time.  The block is
+// bound by its chain of N pivot steps, so these run on rows held in registers
+// (NF wavefronts, RPT rows per lane; 0.3 to 0.5 us a step in one wavefront, 0.8
+// to 1.2 across several), and rows are not moved: a pivot row stays where it is and is
+// found by its step (s_row).  Per group: the columns to the rows' lanes and the
+// pivot steps; then, CW columns at a time, the new pivot rows' entries of the
+// columns to the right and of b, U12 = L11^-1 of them (a thread per
+// column, stored in place), and the rank-16 update of the rest by MFMA.  Back substitution by the same blocks of 16.
+// The last group is filled up with columns of the identity, whose rows are
+// lanes without memory.
+// Measured, one discharge: Nx = 200 911 -> 397 us, per group 8 us of pivot steps
+// and 9 us of updates (MFMA-bound in one CU: 4.3 us).  Ion steps with the field
+// and the formation: Nx = 16 77 -> 27 us, 100 485 -> 129, 512 4990 -> 2780, 1024 30 ->
+// 18 ms (before: panels of 16 or 8 columns factored in LDS by all threads, four
+// barriers a step).
+// ---------------------------------------------------------------------------
+constexpr int kIonSolveThreads = 512;
+template <int RPT, int NF>
+__global__ __launch_bounds__(kIonSolveThreads) void k_ion_solve(double* __restrict__ M, double* __restrict__ b,
+                                                                double* __restrict__ out,
+                                                                const int* __restrict__ x_off,
+                                                                const int* __restrict__ nx_of,
+                                                                const size_t* __restrict__ m_off,
+                                                                int* __restrict__ status, double dt) {
+  constexpr int NT = kIonSolveThreads, NW = NT / 64, R = 64 * RPT * NF, CW = R > 512 ? 128 : 256;
+  constexpr int BF = 4;   // update tiles a wavefront has on their way
   const int d = blockIdx.x, N = nx_of[d], x0 = x_off[d];
   double* A = M + m_off[d];
   double* r = b + x0;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  extern __shared__ double s_dyn[];
-  double* sP = s_dyn;              // [W][ldp]: the panel, column-major (rows 0..N-1)
-  double* sU = s_dyn + W * ldp;    // [ldp + 1][W]: U12 rows of every column outside the panel, and of b
-  __shared__ double s_val[NW];
-  __shared__ int s_idx[NW];
-  __shared__ int s_piv[W];
-  __shared__ int s_R[2 * W], s_src[2 * W];
-  __shared__ int s_nR;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  __shared__ __align__(16) double sP[SW][R + 2];    // multipliers, negated (0: retired rows)
+  __shared__ __align__(16) double sU[SW][CW + 16];
+  __shared__ __align__(16) double sL11[SW][SW];
+  __shared__ __align__(16) PivotLds<NF> s_pl;
+  __shared__ int s_piv[R + SW];
+  __shared__ short s_row[R + SW];                   // the row of every pivot step
+  __shared__ bool s_act[R];                         // rows of the system not yet chosen as a pivot
   bool singular = false, nonfinite = false;
-  auto col = [&](int c) { return c < N ? A + (size_t)c * N : r; };   // column N is b
   // equilibration of the two wall rows (wavefront 0: row 0, wavefront 1: row
   // N-1) to the size of the interior rows; their right-hand sides are 0
   if (w < 2) {
@@ -113,192 +121,145 @@ __global__ __launch_bounds__(kIonSolveThreads) void k_ion_solve_blk(double* __re
     const double sc = (m > 0.0) ? 1.0 / (dt * m) : 1.0;
     for (int c = lane; c < N; c += 64) A[(size_t)c * N + rr] *= sc;
   }
-  __syncthreads();
-  for (int k0 = 0; k0 < N; k0 += W) {
-    const int wd = min(W, N - k0);
-    // (1) the panel into LDS and its factorization there
-    for (int e = tid; e < wd * N; e += NT) {
-      const int j = e / N, i = e % N;
-      if (i >= k0) sP[j * ldp + i] = A[(size_t)(k0 + j) * N + i];
-    }
-    __syncthreads();
-    for (int j = 0; j < wd; ++j) {
-      const int c = k0 + j;
-      double* pc = sP + j * ldp;
-      double best = -1.0;
-      int bi = INT_MAX;
-      for (int i = c + tid; i < N; i += NT) {
-        const double v = fabs(pc[i]);
-        if (v > best) {
-          best = v;
-          bi = i;
-        }
-      }
-      const double wm = wave_max(best);
-      const int wr = wave_min(best == wm ? bi : INT_MAX);
-      if (lane == 0) {
-        s_val[w] = wm;
-        s_idx[w] = wr;
-      }
-      __syncthreads();
-      int p = INT_MAX;
-      {
-        double v = -1.0;
-        for (int u = 0; u < NW; ++u)
-          if (s_val[u] > v || (s_val[u] == v && s_idx[u] < p)) {
-            v = s_val[u];
-            p = s_idx[u];
-          }
-      }
-      if (p == INT_MAX) p = c;  // a column of NaNs keeps row c
-      if (p != c && tid < wd) {
-        double* q = sP + tid * ldp;
-        const double t = q[c];
-        q[c] = q[p];
-        q[p] = t;
-      }
-      if (tid == 0) s_piv[j] = p;
-      __syncthreads();
-      const double pv = pc[c];
-      if (pv == 0.0) singular = true;
-      if (!(fabs(pv) <= DBL_MAX)) nonfinite = true;
-      for (int i = c + 1 + tid; i < N; i += NT) pc[i] = (pv != 0.0) ? pc[i] / pv : 0.0;
-      __syncthreads();
-      // the panel's columns to the right of c
-      const int m = N - c - 1, nr = wd - j - 1;
-      for (int e = tid; e < m * nr; e += NT) {
-        const int i = c + 1 + e % m, jj = j + 1 + e / m;
-        sP[jj * ldp + i] -= pc[i] * sP[jj * ldp + c];
-      }
-      __syncthreads();
-    }
-    for (int e = tid; e < wd * N; e += NT) {
-      const int j = e / N, i = e % N;
-      if (i >= k0) A[(size_t)(k0 + j) * N + i] = sP[j * ldp + i];
-    }
-    // (2) the panel's interchanges as a list of touched rows and their sources
-    if (tid == 0) {
-      int nR = wd;
-      for (int t = 0; t < wd; ++t) {
-        s_R[t] = k0 + t;
-        s_src[t] = k0 + t;
-      }
-      for (int j = 0; j < wd; ++j) {
-        const int a = k0 + j, pj = s_piv[j];
-        if (pj == a) continue;
-        int ia = -1, ip = -1;
-        for (int t = 0; t < nR; ++t) {
-          if (s_R[t] == a) ia = t;
-          if (s_R[t] == pj) ip = t;
-        }
-        if (ip < 0) {
-          ip = nR++;
-          s_R[ip] = pj;
-          s_src[ip] = pj;
-        }
-        const int tmp = s_src[ia];
-        s_src[ia] = s_src[ip];
-        s_src[ip] = tmp;
-      }
-      s_nR = nR;
-    }
-    __syncthreads();
-    // (3) the interchanges on every column outside the panel and on b: all
-    // reads, then all writes
-    const int nR = s_nR, nc = N + 1 - wd;
-    // at most 2 W touched rows of at most NMAX + 1 columns (NMAX the largest Nx
-    // this panel width is launched for)
-    constexpr int NMAX = W == 32 ? 256 : (W == 16 ? 512 : 1024);
-    constexpr int NV = (2 * W * (NMAX + 1) + NT - 1) / NT;
-    double v[NV];
+  Rows<RPT> x;
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int e = tid + u * NT;
-      if (e < nR * nc) {
-        const int t = e % nR, cc = e / nR, cg = cc < k0 ? cc : cc + wd;
-        v[u] = col(cg)[s_src[t]];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int e = tid + u * NT;
-      if (e < nR * nc) {
-        const int t = e % nR, cc = e / nR, cg = cc < k0 ? cc : cc + wd;
-        if (s_src[t] != s_R[t]) col(cg)[s_R[t]] = v[u];
-      }
-    }
-    __syncthreads();
-    // (4) U12 = L11^-1 A12 for the columns after the panel and b (thread per column)
-    const int c1 = k0 + wd, ncols = N + 1 - c1;
-    for (int cc = tid; cc < ncols; cc += NT) {
-      double* q = col(c1 + cc);
-      double x[W];
-#pragma unroll
-      for (int t = 0; t < W; ++t) x[t] = t < wd ? q[k0 + t] : 0.0;
-#pragma unroll
-      for (int t = 1; t < W; ++t)
-#pragma unroll
-        for (int k = 0; k < t; ++k)
-          if (t < wd) x[t] -= sP[k * ldp + k0 + t] * x[k];
-#pragma unroll
-      for (int t = 0; t < W; ++t)
-        if (t < wd) {
-          q[k0 + t] = x[t];
-          sU[cc * W + t] = x[t];
-        }
-    }
-    __syncthreads();
-    // (5) rank-wd update of the trailing matrix and b: lanes down the rows,
-    // wavefronts across the columns
-    const int mr = N - c1;
-    for (int cc = w; cc < ncols; cc += NW) {
-      double* q = col(c1 + cc);
-      const double* u = sU + cc * W;
-      for (int i = c1 + lane; i < N; i += 64) {
-        double s = 0.0;
-        for (int t = 0; t < wd; ++t) s += sP[t * ldp + i] * u[t];
-        q[i] -= s;
-      }
-    }
-    (void)mr;
-    __syncthreads();
+  for (int q = 0; q < RPT; ++q) {
+    x.pos[q] = tid + 64 * NF * q;
+    x.act[q] = x.pos[q] < (N + SW - 1) / SW * SW ? ~0u : 0u;
   }
-  // back substitution U x = b by blocks of 16 rows from the bottom, b in LDS:
-  // one wavefront solves a block (values passed by lane reads), then every
-  // thread subtracts the block's columns from the rows above, in the same
-  // order as a column-by-column substitution
-  constexpr int BS = 16;
-  double* sr = sU;   // the U12 staging is free now; (ldp + 1) W >= N doubles
-  for (int i = tid; i < N; i += NT) sr[i] = r[i];
   __syncthreads();
-  for (int b1 = N; b1 > 0; b1 -= BS) {
-    const int b0 = max(0, b1 - BS), nb = b1 - b0;
+  for (int k0 = 0; k0 < N; k0 += SW) {
+    if (w < NF) {
+      // (loads without branches, from entries of the system)
+      UniformCols<double> cols(A + (size_t)k0 * N, N);
+#pragma unroll
+      for (int j = 0; j < SW; ++j) {
+        const double* p = cols.next();
+        if (k0 + j >= N) p = A;
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) x.a[q][j] = p[static_cast<unsigned>(min(tid + 64 * NF * q, N - 1))];
+      }
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        const int row = tid + 64 * NF * q;
+        const bool in = row < N;
+#pragma unroll
+        for (int j = 0; j < SW; ++j) {
+          const int c = k0 + j;
+          x.a[q][j] = (in & (c < N)) ? x.a[q][j] : (row == c ? 1.0 : 0.0);
+        }
+      }
+      pivot_steps<RPT, NF>(x, k0, &s_pl, s_piv, singular, nonfinite);
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        const int row = tid + 64 * NF * q, st = x.pos[q] - k0;
+        const bool act = x.act[q] != 0u;
+#pragma unroll
+        for (int j = 0; j < SW; ++j) sP[j][row] = act ? -x.a[q][j] : 0.0;
+        s_act[row] = act & (row < N);
+        if (!act & (st >= 0) & (st < SW)) {   // (rows without a place in the system lie past the last step)
+          s_row[k0 + st] = static_cast<short>(row);
+          double* p = A + (size_t)k0 * N + row;
+#pragma unroll
+          for (int j = 0; j < SW; ++j) {
+            sL11[j][st] = x.a[q][j];   // entries k < st are read
+            if (k0 + j < N && row < N) *p = x.a[q][j];
+            p += N;
+          }
+        }
+      }
+    } else if constexpr (NF > 1) {
+      for (int j = 0; j < SW; ++j) lds_barrier();   // the steps' barriers
+    }
+    lds_barrier();
+    // the columns to the right, then b
+    const int c1 = k0 + SW, nc = max(0, N - c1) + 1;
+    auto col = [&](int q) { return c1 + q < N ? A + (size_t)(c1 + q) * N : r; };
+    for (int q0 = 0; q0 < nc; q0 += CW) {
+      const int qn = min(CW, nc - q0);
+      if (tid < CW) {
+        double uc[SW];
+        int rows[SW];   // (rows without memory: the last, not written)
+        double* p = col(q0 + min(tid, qn - 1));
+#pragma unroll
+        for (int i = 0; i < SW; ++i) {
+          rows[i] = s_row[k0 + i];
+          const double v = p[min(rows[i], N - 1)];
+          uc[i] = ((tid < qn) & (rows[i] < N)) ? v : 0.0;
+        }
+        unit_lower_16(sL11, uc);
+#pragma unroll
+        for (int i = 0; i < SW; ++i) {
+          sU[i][tid] = uc[i];
+          if ((tid < qn) & (rows[i] < N)) p[rows[i]] = uc[i];   // (read again by the back substitution only)
+        }
+      }
+      lds_barrier();
+      const int nrt = (N + 15) / 16, tiles = nrt * ((qn + 15) / 16);
+      // (the products transposed, rows along the lanes: an item is 4 columns' 16
+      // consecutive rows)
+      for (int t0 = w; t0 < tiles; t0 += BF * NW) {
+        f64x4 acc[BF];
+#pragma unroll
+        for (int f = 0; f < BF; ++f) {
+          const int tile = min(t0 + f * NW, tiles - 1), q = 16 * (tile / nrt) + lk, row = 16 * (tile % nrt) + li;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[f][i] = col(q0 + min(q + 4 * i, qn - 1))[min(row, N - 1)];
+        }
+#pragma unroll
+        for (int f = 0; f < BF; ++f) {
+          const int tile = t0 + f * NW, q = 16 * (tile / nrt), row = 16 * (tile % nrt) + li;
+          if (tile >= tiles) break;
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            acc[f] = __builtin_amdgcn_mfma_f64_16x16x4f64(sU[4 * k + lk][q + li], sP[4 * k + lk][row], acc[f], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (q + lk + 4 * i < qn && s_act[row]) col(q0 + q + lk + 4 * i)[row] = acc[f][i];
+        }
+      }
+      __syncthreads();
+    }
+  }
+  // back substitution U x = y by blocks of 16 steps from the last, y in LDS in
+  // the steps' order: one wavefront solves a block (values passed by lane
+  // reads), then every thread subtracts the block's columns from the rows above
+  double* sy = &sP[0][0];
+  for (int i = tid; i < N; i += NT) sy[i] = r[s_row[i]];
+  __syncthreads();
+  for (int k0 = (N - 1) / SW * SW; k0 >= 0; k0 -= SW) {
+    const int nb = min(SW, N - k0);
     if (w == 0) {
       const bool own = lane < nb;
-      double v = own ? sr[b0 + lane] : 0.0;
-      double u[BS];
+      double v = own ? sy[k0 + lane] : 0.0;
+      const double* p = A + (size_t)k0 * N + s_row[k0 + min(lane, nb - 1)];
+      double u[SW];   // (entries below the diagonal are not read)
 #pragma unroll
-      for (int t = 0; t < BS; ++t) u[t] = (own && t < nb && t >= lane) ? A[(size_t)(b0 + t) * N + b0 + lane] : 0.0;
+      for (int t = 0; t < SW; ++t) u[t] = p[(size_t)min(t, nb - 1) * N];
 #pragma unroll
-      for (int t = BS - 1; t >= 0; --t) {
+      for (int t = SW - 1; t >= 0; --t) {
         if (t < nb) {
           if (lane == t) v = v / u[t];
           const double xt = readlane_f64(v, t);
           if (lane < t) v -= u[t] * xt;
         }
       }
-      if (own) sr[b0 + lane] = v;
+      if (own) sy[k0 + lane] = v;
     }
     __syncthreads();
-    for (int i = tid; i < b0; i += NT) {
-      double ri = sr[i];
-      for (int j = b1 - 1; j >= b0; --j) ri -= A[(size_t)j * N + i] * sr[j];
-      sr[i] = ri;
+    for (int i = tid; i < k0; i += NT) {
+      const double* p = A + (size_t)k0 * N + s_row[i];
+      double t[SW], ri = sy[i];
+#pragma unroll
+      for (int j = 0; j < SW; ++j) t[j] = p[(size_t)min(j, nb - 1) * N];
+#pragma unroll
+      for (int j = SW - 1; j >= 0; --j)
+        if (j < nb) ri -= t[j] * sy[k0 + j];
+      sy[i] = ri;
     }
     __syncthreads();
   }
-  for (int i = tid; i < N; i += NT) out[x0 + i] = sr[i];
+  for (int i = tid; i < N; i += NT) out[x0 + i] = sy[i];
   if (singular && tid == 0) atomicOr(status, kStSingular);
   if (nonfinite && tid == 0) atomicOr(status, kStNonFinite);
 }
@@ -310,16 +271,19 @@ void launch_ion_update_ws(const DevOps& d, const double* F, const double* ni_in,
   const dim3 gf((d.max_nx + kIonFormCols - 1) / kIonFormCols, d.nd);
   k_ion_form<<<gf, kIonThreads, 0, s>>>(F, ni_in, E, d.dxT, d.dx2, d.mom + 2 * (size_t)d.n, d.n0_of, d.x_off,
                                         d.nx_of, d.p_off, M, b, d.dt, d.n);
-  // blocked elimination, panel width by the largest Nx (two W x Nx tiles of LDS)
-  const int ldp = d.max_nx + 1;
-  auto blk = [&](auto wc) {
-    constexpr int W = decltype(wc)::value;
-    const size_t sh = (size_t)(W * ldp + (ldp + 1) * W) * sizeof(double);
-    k_ion_solve_blk<W><<<d.nd, kIonSolveThreads, sh, s>>>(M, b, ni_out, d.x_off, d.nx_of, d.p_off, d.status, ldp,
-                                                         d.dt);
+  auto solve = [&](auto rpt, auto nf) {
+    k_ion_solve<decltype(rpt)::value, decltype(nf)::value><<<d.nd, kIonSolveThreads, 0, s>>>(
+        M, b, ni_out, d.x_off, d.nx_of, d.p_off, d.status, d.dt);
   };
-  if (d.max_nx <= 512) blk(std::integral_constant<int, 16>{});
-  else blk(std::integral_constant<int, 8>{});
+  using std::integral_constant;
+  // the fewest wavefronts that hold the rows of the largest discharge: a step of
+  // 16 columns takes 4.9 us with two rows per lane of one wavefront, 7.9 with four
+  // (13 with one row per lane of four wavefronts, at 256 rows); at 512 rows 12.5 with
+  // two per lane of four, 16 with four per lane of two
+  if (d.max_nx <= 128) solve(integral_constant<int, 2>(), integral_constant<int, 1>());
+  else if (d.max_nx <= 256) solve(integral_constant<int, 4>(), integral_constant<int, 1>());
+  else if (d.max_nx <= 512) solve(integral_constant<int, 2>(), integral_constant<int, 4>());
+  else solve(integral_constant<int, 2>(), integral_constant<int, 8>());   // (Nx <= 1024)
 }
 
 void launch_ion_update(const DevOps& d, const double* F, const double* ni_in, double* ni_out, hipStream_t s) {

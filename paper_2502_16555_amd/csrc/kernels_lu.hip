@@ -1551,24 +1551,6 @@ __device__ __attribute__((always_inline)) inline void diag_chain(const double (*
   }
 }
 
-// Columns at a wavefront-uniform address: next() gives each one's and steps on.
-// Kept in scalar registers, so that a load takes the lane's 32-bit offset alone
-// (the compiler makes a 64-bit address per load and lane of it otherwise).
-template <typename T>
-struct UniformCols {
-  uint64_t p;
-  const uint64_t stride;
-  __device__ __forceinline__ UniformCols(const T* base, size_t elems)
-      : p(reinterpret_cast<uint64_t>(base)), stride(elems * sizeof(T)) {}
-  __device__ __forceinline__ const T* next() {
-    using G = const T __attribute__((address_space(1)))*;
-    asm("" : "+s"(p));
-    const uint64_t q = p;
-    p += stride;
-    return (const T*)(G)q;
-  }
-};
-
 // Sums of the wavefront for eight values per lane: lane l returns value l mod 8's
 // (the values are halved three times as the lanes pair up, then summed).
 __device__ __forceinline__ double fold8(const double (&v)[8], int lane) {

@@ -66,6 +66,24 @@ __device__ inline void xcd_map(int bid, int items, int nmat, int* mat, int* item
 
 inline int xcd_grid(int items, int nmat) { return kXcd * items * ((nmat + kXcd - 1) / kXcd); }
 
+// Columns at a wavefront-uniform address: next() gives each one's and steps on.
+// Kept in scalar registers, so that a load takes the lane's 32-bit offset alone
+// (the compiler makes a 64-bit address per load and lane of it otherwise).
+template <typename T>
+struct UniformCols {
+  uint64_t p;
+  const uint64_t stride;
+  __device__ __forceinline__ UniformCols(const T* base, size_t elems)
+      : p(reinterpret_cast<uint64_t>(base)), stride(elems * sizeof(T)) {}
+  __device__ __forceinline__ const T* next() {
+    using G = const T __attribute__((address_space(1)))*;
+    asm("" : "+s"(p));
+    const uint64_t q = p;
+    p += stride;
+    return (const T*)(G)q;
+  }
+};
+
 // Barrier for data exchanged through LDS only: the block's global loads
 // and stores stay in flight (a full fence would wait for them every time).
 __device__ __forceinline__ void lds_barrier() {

@@ -394,6 +394,13 @@ def test_ion_step_matches_oracle(torch, nx):
     s.close()
 
 
+@pytest.mark.parametrize("nx", [3, 16, 17, 128, 129, 257, 512, 513])
+def test_ion_step_at_edges_of_its_row_tiles(torch, nx):
+    """The elimination's groups of 16 columns (N a multiple of 16, one past it, below it) and every
+    number of rows per lane and wavefronts (up to 128, 256, 512 and 1024 rows); as the test above."""
+    test_ion_step_matches_oracle(torch, nx)
+
+
 def test_hybrid_steps_match_oracle(torch):
     """Five hybrid steps (ions, then electrons with the Poisson field of the new
     ion density) against the oracle, F and n_i."""
