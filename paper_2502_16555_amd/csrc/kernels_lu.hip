@@ -491,32 +491,39 @@ __global__ __launch_bounds__(NT) void k_panel(float* __restrict__ LU, int* __res
 // follows every FP32 solve works with the unperturbed matrix.  Pivots and
 // permutations are written as the identity, so that the U12, update and solve
 // kernels apply them as no-ops.
-//   k_diag_static  one 256-thread block per matrix, the 128 x 128 diagonal
+//   k_diag_static  one 512-thread block per matrix, the 128 x 128 diagonal
 //                  block in LDS: A11 = L11 U11 by 16-column steps (a panel
 //                  factored by one wavefront in registers, its U12 rows by
 //                  forward substitution, the trailing update on MFMA); then
-//                  X = U11^-1 by 16 x 16 blocks in LDS (the diagonal blocks,
-//                  then seven levels of off-diagonal blocks), the inverses of
-//                  L11's eight diagonal blocks beside those of U11's, by the
-//                  other 128 threads, and L11^-1 by the same levels after X;
-//                  both go into the matrix's linv slot for L21 and U12, and
-//                  their triangles into tinv for the solves;
+//                  X = U11^-1 and Y = L11^-1 by 16 x 16 blocks (the diagonal
+//                  blocks, then seven levels of off-diagonal blocks), half of
+//                  the wavefronts each; both go into the matrix's linv slot
+//                  for L21 and U12, and their triangles into tinv for the
+//                  solves.  A chain of latencies throughout: 56 -> 45 us for up to
+//                  256 matrices (X, then Y, on 256 threads before);
 //   k_l21_mfma     L21 = A21 X for 128 rows per block: one MFMA product (K =
 //                  128, the zero blocks of X skipped), A21 straight from HBM.
 // ---------------------------------------------------------------------------
 constexpr float kStaticPivotRel = 9.5367431640625e-07f;   // 2^-20
 
+constexpr int kDiagThreads = 512;
+
 // LDS of the diagonal-block kernels.  During the factorization the block sits
-// column-major in the X region (sA[c][r]) and the U region holds the current
-// step's MFMA operands; for the inverses the U region holds U11 row-major and
-// the X region X = U11^-1 transposed.
+// column-major in xt (A[c][r]) and u holds the current step's MFMA operands; for
+// the inverses u holds the factored block row-major, and xt the blocks of X =
+// U11^-1 and Y = L11^-1 off the diagonal, both transposed: X's below it (block
+// row = X's block column), Y's above.  Their diagonal blocks are in xd
+// (transposed) and yd, and xt's diagonal blocks hold a level's sums for X.
 struct DiagLds {
   __align__(16) float u[NB][NB + 4];
   __align__(16) float xt[NB][NB + 4];
-  float t[8][16][17];              // a level's sums, per block
-  __align__(16) float l11[2][16][20];   // rows as 16-byte vectors, per step parity
-  float yd[8][16][16];             // inverses of L11's diagonal blocks
-  float red[4];
+  float t[8][16][17];              // a level's sums for Y
+  float yd[8][16][17];
+  union {
+    float xd[8][16][17];
+    __align__(16) float l11[2][16][20];   // rows as 16-byte vectors, per step parity
+  };
+  float red[kDiagThreads / 64];
 };
 
 // X = U11^-1 and Y = L11^-1 of the factored block in s.xt (column-major): tinv
@@ -525,50 +532,23 @@ struct DiagLds {
 // NULL) X row-major, yo (may be NULL) Y column-major.
 __device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, float* __restrict__ tinv,
                                                                     float* __restrict__ xo, float* __restrict__ yo) {
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   float (*sU)[NB + 4] = s.u;
   float (*sXT)[NB + 4] = s.xt;
-  float (*sA)[NB + 4] = s.xt;
-  float (*sT)[16][17] = s.t;
-  float (*sYd)[16][16] = s.yd;
-  // ---- X = U11^-1 by 16 x 16 blocks (X upper triangular, kept transposed in
-  // LDS, XT[col][row]): the diagonal blocks X_bb = U_bb^-1 by back substitution,
-  // then by levels d = 1..7 the blocks X_{a,a+d} = -X_aa sum_{m=a+1}^{a+d}
-  // U_am X_{m,a+d}; the blocks of one level are independent.  U11 goes
-  // row-major into sU, the strict lower parts of L11's diagonal blocks into sT
-  // (which the levels use only later), then sXT is cleared.
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {   // 4 x 4 blocks, transposed in registers
-    const int i4 = 4 * (tid & 31), j4 = 4 * (tid >> 5) + 32 * u;
-    float w[4][4];   // w[jj][ii] = A[i4 + ii][j4 + jj]
+  for (int u = 0; u < 2; ++u) {   // row-major, 4 x 4 blocks transposed in registers
+    const int i4 = 4 * (tid & 31), j4 = 4 * (tid >> 5) + 64 * u;
+    float4 v[4];
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const float4 v = *reinterpret_cast<const float4*>(&sA[j4 + jj][i4]);
-      w[jj][0] = v.x;
-      w[jj][1] = v.y;
-      w[jj][2] = v.z;
-      w[jj][3] = v.w;
-    }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int i = i4 + ii;
-      float o[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) o[jj] = w[jj][ii];   // L's strict lower part rides below U
-      *reinterpret_cast<float4*>(&sU[i][j4]) = make_float4(o[0], o[1], o[2], o[3]);
-      if ((i >> 4) == (j4 >> 4)) {
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-          if (i > j4 + jj) sT[i >> 4][i & 15][(j4 + jj) & 15] = w[jj][ii];
-      }
-    }
+    for (int jj = 0; jj < 4; ++jj) v[jj] = *reinterpret_cast<const float4*>(&sXT[j4 + jj][i4]);
+    *reinterpret_cast<float4*>(&sU[i4 + 0][j4]) = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
+    *reinterpret_cast<float4*>(&sU[i4 + 1][j4]) = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
+    *reinterpret_cast<float4*>(&sU[i4 + 2][j4]) = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
+    *reinterpret_cast<float4*>(&sU[i4 + 3][j4]) = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
   }
   __syncthreads();
-  for (int e = tid; e < NB * NB / 4; e += 256)
-    *reinterpret_cast<float4*>(&sXT[e >> 5][(e & 31) * 4]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  __syncthreads();
-  if (tid < NB) {   // thread (b, c): column c of X_bb
+  if (tid < NB) {   // thread (b, c): column c of X_bb by back substitution
     const int b = tid >> 4, c = tid & 15, o = 16 * b;
     float xv[16];
 #pragma unroll
@@ -579,123 +559,112 @@ __device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, 
       xv[i] = v / sU[o + i][o + i];
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sXT[o + c][o + i] = xv[i];
-  } else {          // thread (b, c): column c of L_bb^-1 (unit lower) by forward substitution
-    const int b = (tid - NB) >> 4, c = tid & 15;
+    for (int i = 0; i < 16; ++i) s.xd[b][c][i] = xv[i];
+  } else if (tid < 2 * NB) {   // thread (b, c): column c of Y_bb = L_bb^-1 (unit lower) by forward substitution
+    const int b = (tid - NB) >> 4, c = tid & 15, o = 16 * b;
     float x[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) x[r] = (r == c) ? 1.0f : 0.0f;
 #pragma unroll
     for (int r = 1; r < 16; ++r)
 #pragma unroll
-      for (int k = 0; k < r; ++k) x[r] -= sT[b][r][k] * x[k];
+      for (int k = 0; k < r; ++k) x[r] -= sU[o + r][o + k] * x[k];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sYd[b][r][c] = x[r];
+    for (int r = 0; r < 16; ++r) s.yd[b][r][c] = x[r];
   }
   __syncthreads();
-  // levels on MFMA, the blocks of a level spread over the wavefronts: T_ab into
-  // sT (lane (li, lk) holds rows 4 lk.. of column li), then X_{ab,b} = -X_aa T_ab
-  // from sT, written transposed
+  // by levels d = 1..7 the blocks X_{a,a+d} = -X_aa sum_{m=a+1}^{a+d} U_am
+  // X_{m,a+d} on wavefronts 0-3 and Y_{a+d,a} = -Y_{a+d,a+d} sum_{m=a}^{a+d-1}
+  // L_{a+d,m} Y_{m,a} on 4-7, on MFMA (lane (li, lk) holds rows 4 lk.. of column
+  // li); the blocks of one level are independent
+  const bool isx = wid < 4;
   for (int d = 1; d < 8; ++d) {
-    for (int ab = wid; ab + d < 8; ab += 4) {
-      const int b = ab + d;
-      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int m2 = ab + 1; m2 <= b; ++m2)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          t = Mma<float>::step(sU[16 * ab + li][16 * m2 + 4 * q4 + lk], sXT[16 * b + li][16 * m2 + 4 * q4 + lk], t);
-#pragma unroll
-      for (int it = 0; it < 4; ++it) sT[ab][4 * lk + it][li] = t[it];
-    }
-    __syncthreads();
-    for (int ab = wid; ab + d < 8; ab += 4) {
-      const int b = ab + d;
-      f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        x = Mma<float>::step(sXT[16 * ab + 4 * q4 + lk][16 * ab + li], sT[ab][4 * q4 + lk][li], x);
-      *reinterpret_cast<float4*>(&sXT[16 * b + li][16 * ab + 4 * lk]) = make_float4(-x[0], -x[1], -x[2], -x[3]);
-    }
-    __syncthreads();
-  }
-  // X column-major for the solves (the zeros below its diagonal are filled with
-  // Y below), and row-major, 4 x 4 blocks transposed in registers
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = tid + 256 * u, k = e >> 5, i4 = (e & 31) * 4;
-    if (i4 <= k) *reinterpret_cast<float4*>(tinv + (size_t)k * NB + i4) = *reinterpret_cast<const float4*>(&sXT[k][i4]);
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if (!xo) break;
-    const int k4 = 4 * (tid & 31), c4 = 4 * (tid >> 5) + 32 * u;
-    float4 v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float4*>(&sXT[c4 + j][k4]);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 0) * NB + c4) = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 1) * NB + c4) = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 2) * NB + c4) = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
-    *reinterpret_cast<float4*>(xo + (size_t)(k4 + 3) * NB + c4) = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
-  }
-  // ---- Y = L11^-1 (in place of k_l11inv) by the same levels: Y_bb from sYd,
-  // then Y_{a+d,a} = -Y_{a+d,a+d} sum_{m=a}^{a+d-1} L_{a+d,m} Y_{m,a}, with L's
-  // strict lower part in sU and Y kept transposed in the X region (zeros above
-  // its diagonal); Y leaves column-major after the diagonal-block inverses
-  __syncthreads();
-  for (int e = tid; e < NB * NB / 4; e += 256) {   // YT row k: Y_bb's column k mod 16 in block b, zeros elsewhere
-    const int k = e >> 5, i4 = (e & 31) * 4, b = k >> 4;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if ((i4 >> 4) == b) {
-      const int r = i4 & 15, c = k & 15;
-      v = make_float4(sYd[b][r][c], sYd[b][r + 1][c], sYd[b][r + 2][c], sYd[b][r + 3][c]);
-    }
-    *reinterpret_cast<float4*>(&sXT[k][i4]) = v;
-  }
-  __syncthreads();
-  for (int d = 1; d < 8; ++d) {
-    for (int a = wid; a + d < 8; a += 4) {
+    for (int a = wid & 3; a + d < 8; a += 4) {
       const int r = a + d;
       f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int m2 = a; m2 < r; ++m2)
+      if (isx) {
+        for (int m2 = a + 1; m2 < r; ++m2)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            t = Mma<float>::step(sU[16 * a + li][16 * m2 + 4 * q4 + lk], sXT[16 * r + li][16 * m2 + 4 * q4 + lk], t);
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
-          t = Mma<float>::step(sU[16 * r + li][16 * m2 + 4 * q4 + lk], sXT[16 * a + li][16 * m2 + 4 * q4 + lk], t);
+          t = Mma<float>::step(sU[16 * a + li][16 * r + 4 * q4 + lk], s.xd[r][li][4 * q4 + lk], t);
 #pragma unroll
-      for (int it = 0; it < 4; ++it) sT[a][4 * lk + it][li] = t[it];
+        for (int it = 0; it < 4; ++it) sXT[16 * a + 4 * lk + it][16 * a + li] = t[it];
+      } else {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          t = Mma<float>::step(sU[16 * r + li][16 * a + 4 * q4 + lk], s.yd[a][4 * q4 + lk][li], t);
+        for (int m2 = a + 1; m2 < r; ++m2)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            t = Mma<float>::step(sU[16 * r + li][16 * m2 + 4 * q4 + lk], sXT[16 * a + li][16 * m2 + 4 * q4 + lk], t);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) s.t[a][4 * lk + it][li] = t[it];
+      }
     }
     __syncthreads();
-    for (int a = wid; a + d < 8; a += 4) {
+    for (int a = wid & 3; a + d < 8; a += 4) {
       const int r = a + d;
       f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (isx) {
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        x = Mma<float>::step(sXT[16 * r + 4 * q4 + lk][16 * r + li], sT[a][4 * q4 + lk][li], x);
-      *reinterpret_cast<float4*>(&sXT[16 * a + li][16 * r + 4 * lk]) = make_float4(-x[0], -x[1], -x[2], -x[3]);
+        for (int q4 = 0; q4 < 4; ++q4)
+          x = Mma<float>::step(s.xd[a][4 * q4 + lk][li], sXT[16 * a + 4 * q4 + lk][16 * a + li], x);
+      } else {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) x = Mma<float>::step(s.yd[r][li][4 * q4 + lk], s.t[a][4 * q4 + lk][li], x);
+      }
+      *reinterpret_cast<float4*>(isx ? &sXT[16 * r + li][16 * a + 4 * lk] : &sXT[16 * a + li][16 * r + 4 * lk]) =
+          make_float4(-x[0], -x[1], -x[2], -x[3]);
     }
     __syncthreads();
   }
+  // the diagonal blocks in place: X's transposed, and Y's strict lower part
+  for (int e = tid; e < 8 * 256; e += kDiagThreads) {
+    const int b = e >> 8, k = (e >> 4) & 15, i = e & 15;
+    sXT[16 * b + k][16 * b + i] = i <= k ? s.xd[b][k][i] : s.yd[b][i][k];
+  }
+  __syncthreads();
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = tid + 256 * u, k = e >> 5, i4 = (e & 31) * 4;
+  for (int u = 0; u < 8; ++u) {
+    const int e = tid + kDiagThreads * u, k = e >> 5, i4 = (e & 31) * 4;
     const float4 v = *reinterpret_cast<const float4*>(&sXT[k][i4]);
-    if (yo) *reinterpret_cast<float4*>(yo + (size_t)k * NB + i4) = v;   // column-major: (i, k) at k NB + i
-    float* t = tinv + (size_t)k * NB + i4;
-    if (i4 > k) {
-      *reinterpret_cast<float4*>(t) = v;
-    } else if (i4 + 3 > k) {   // the vector that holds the diagonal (written above by this thread)
-      if (i4 + 1 > k) t[1] = v.y;
-      if (i4 + 2 > k) t[2] = v.z;
-      t[3] = v.w;
+    *reinterpret_cast<float4*>(tinv + (size_t)k * NB + i4) = v;
+    if (yo) {   // column-major: (i, k) at k NB + i
+      const float w[4] = {v.x, v.y, v.z, v.w};
+      float y[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = i4 + q > k ? w[q] : (i4 + q == k ? 1.0f : 0.0f);
+      *reinterpret_cast<float4*>(yo + (size_t)k * NB + i4) = make_float4(y[0], y[1], y[2], y[3]);
     }
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {   // row-major, 4 x 4 blocks transposed in registers
+    if (!xo) break;
+    const int k4 = 4 * (tid & 31), c4 = 4 * (tid >> 5) + 64 * u;
+    float w[4][4];   // w[j][q] = X(k4 + q, c4 + j)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float4 v = *reinterpret_cast<const float4*>(&sXT[c4 + j][k4]);
+      w[j][0] = k4 + 0 <= c4 + j ? v.x : 0.0f;
+      w[j][1] = k4 + 1 <= c4 + j ? v.y : 0.0f;
+      w[j][2] = k4 + 2 <= c4 + j ? v.z : 0.0f;
+      w[j][3] = k4 + 3 <= c4 + j ? v.w : 0.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4*>(xo + (size_t)(k4 + q) * NB + c4) = make_float4(w[0][q], w[1][q], w[2][q], w[3][q]);
   }
 }
 
-__global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, float* __restrict__ linv,
+__global__ __launch_bounds__(kDiagThreads) void k_diag_static(float* __restrict__ LU, float* __restrict__ linv,
                                                      float* __restrict__ tinv, int* __restrict__ piv, int* __restrict__ perm,
                                                      int* __restrict__ status, int npad, int k0) {
   const int mat = blockIdx.x;
   float* A = LU + (size_t)mat * npad * npad;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   __shared__ DiagLds s_all;
   float (*sU)[NB + 4] = s_all.u;
@@ -709,8 +678,8 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
   float m = 0.0f;
   bool nonfinite = false;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = tid + 256 * u, c = e >> 5, r4 = (e & 31) * 4;
+  for (int u = 0; u < 8; ++u) {
+    const int e = tid + kDiagThreads * u, c = e >> 5, r4 = (e & 31) * 4;
     const float4 v = *reinterpret_cast<const float4*>(A + (size_t)(k0 + c) * npad + k0 + r4);
     *reinterpret_cast<float4*>(&sA[c][r4]) = v;
     const float w4[4] = {v.x, v.y, v.z, v.w};
@@ -725,13 +694,16 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if (lane == 0) s_red[wid] = m;
   __syncthreads();
-  const float tau = fmaxf(fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3])) * kStaticPivotRel, FLT_MIN);
+  m = 0.0f;
+#pragma unroll
+  for (int q = 0; q < kDiagThreads / 64; ++q) m = fmaxf(m, s_red[q]);
+  const float tau = fmaxf(m * kStaticPivotRel, FLT_MIN);
   // ---- A11 = L11 U11 by 16-column steps c0 = 16 kb: wavefront 0 factors the
   // step's panel (rows c0.., two per lane) in registers, each pivot row passed
   // on by lane reads, with no barrier; then U12 = L11^-1 A12 for the step's 16
   // rows (a thread per column) and A22 -= L21 U12 on MFMA in 16 x 16 tiles:
   // first the tiles of the next step's panel columns, then the others on
-  // wavefronts 1-3 while wavefront 0 factors that panel (the staging buffers
+  // wavefronts 1-7 while wavefront 0 factors that panel (the staging buffers
   // alternate with the step).
   auto panel = [&](int kb) __attribute__((always_inline)) {
     const int c0 = 16 * kb;
@@ -849,20 +821,20 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
     __syncthreads();
     const int nt = ncol / 16;
     if (nt > 0) {
-      for (int t = wid; t < nt; t += 4) tile(kb, c0 + 16 + 16 * t, c0 + 16);
+      for (int t = wid; t < nt; t += 8) tile(kb, c0 + 16 + 16 * t, c0 + 16);
       __syncthreads();
       if (wid == 0) {
         panel(kb + 1);
       } else {
-        for (int t = wid - 1; t < nt * (nt - 1); t += 3) tile(kb, c0 + 16 + 16 * (t % nt), c0 + 32 + 16 * (t / nt));
+        for (int t = wid - 1; t < nt * (nt - 1); t += 7) tile(kb, c0 + 16 + 16 * (t % nt), c0 + 32 + 16 * (t / nt));
       }
       __syncthreads();
     }
   }
   // the factors to the matrix; pivots and permutation as the identity
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = tid + 256 * u, c = e >> 5, r4 = (e & 31) * 4;
+  for (int u = 0; u < 8; ++u) {
+    const int e = tid + kDiagThreads * u, c = e >> 5, r4 = (e & 31) * 4;
     *reinterpret_cast<float4*>(A + (size_t)(k0 + c) * npad + k0 + r4) = *reinterpret_cast<const float4*>(&sA[c][r4]);
   }
   if (tid < NB) {
@@ -870,7 +842,7 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
     int* pm = perm + ((size_t)mat * kMaxPanels + k0 / NB) * kPermStride;
     pm[1 + tid] = k0 + tid;
     pm[1 + kMaxSwapRows + tid] = k0 + tid;
-    if (tid == 0) pm[0] = NB;
+    if (tid == 0) pm[0] = 0;   // no rows moved: the solves skip it
   }
   diag_inverses(s_all, tinv + ((size_t)mat * (npad / NB) + k0 / NB) * NB * NB,
                 linv + (size_t)mat * kLinvElems + kLinvXOff, linv + (size_t)mat * kLinvElems + 8 * 256);
@@ -879,13 +851,13 @@ __global__ __launch_bounds__(256) void k_diag_static(float* __restrict__ LU, flo
 
 // The triangles' inverses (diag_inverses) of every diagonal block of partially
 // pivoted FP32 factors, one block per panel and matrix, after the factorization.
-__global__ __launch_bounds__(256) void k_diag_inv(const float* __restrict__ LU, float* __restrict__ tinv, int npad) {
+__global__ __launch_bounds__(kDiagThreads) void k_diag_inv(const float* __restrict__ LU, float* __restrict__ tinv, int npad) {
   const int k0 = blockIdx.x * NB, mat = blockIdx.y, tid = threadIdx.x;
   const float* A = LU + (size_t)mat * npad * npad;
   __shared__ DiagLds s;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int e = tid + 256 * u, c = e >> 5, r4 = (e & 31) * 4;
+  for (int u = 0; u < 8; ++u) {
+    const int e = tid + kDiagThreads * u, c = e >> 5, r4 = (e & 31) * 4;
     *reinterpret_cast<float4*>(&s.xt[c][r4]) = *reinterpret_cast<const float4*>(A + (size_t)(k0 + c) * npad + k0 + r4);
   }
   __syncthreads();
@@ -1593,7 +1565,7 @@ __device__ __forceinline__ double fold8(const double (&v)[8], int lane) {
 // Bound by what one CU draws: about 38 GB/s, whatever the loads in flight (8 or
 // 16 columns, waited for together or one by one: its vector cache holds 32 KB of
 // outstanding lines, over a latency of 0.85 us), until 256 CUs reach HBM's rate.
-// Per solve: 100 points, n = 1024, FP32 183 -> 116 us; 256 points, n = 2048, FP32 718 ->
+// Per solve: 100 points, n = 1024, FP32 183 -> 113 us; 256 points, n = 2048, FP32 718 ->
 // 690 (6.2 TB/s); 64 points, n = 2048, FP64 990 -> 857; its band form,
 // half-bandwidth 127, 663 -> 351; FP64 transposed, 128 points, n = 512: 202 -> 105.
 // ---------------------------------------------------------------------------
@@ -1994,7 +1966,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
   // statically pivoted FP32 panels: the diagonal block and L21 (on stream st)
   auto static_panel = [&](int k0, int rend, hipStream_t st, float* lmax = nullptr, int first = 0) {
     if constexpr (std::is_same<T, float>::value) {
-      k_diag_static<<<nmat, 256, 0, st>>>(LU, li, ti, piv, perm, d.status, d.npad, k0);
+      k_diag_static<<<nmat, kDiagThreads, 0, st>>>(LU, li, ti, piv, perm, d.status, d.npad, k0);
       const int nt = (rend - k0 - NB) / NB;   // row tiles of L21 (rend, k0 multiples of 128)
       if (nt > 0) k_l21_mfma<<<xcd_grid(nt, nmat), 256, 0, st>>>(LU, li, d.npad, k0, nt, nmat, lmax, first);
     }
@@ -2121,7 +2093,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
     }
   }
   if constexpr (std::is_same<T, float>::value) {
-    if (!stat) k_diag_inv<<<dim3(np, nmat), 256, 0, s>>>(LU, ti, d.npad);
+    if (!stat) k_diag_inv<<<dim3(np, nmat), kDiagThreads, 0, s>>>(LU, ti, d.npad);
   }
 }
 
