@@ -390,7 +390,7 @@ void fill_devops(bte_handle* h) {
   d.Fs = h->alloc<double>(nxt * d.n);
   d.mu = h->alloc<double>(nxt * d.n);
   {
-    const size_t gx = (d.n + 63) / 64, gy = (nxt + 31) / 32;
+    const size_t gx = (d.n + 15) / 16, gy = (nxt + 31) / 32;   // of the smallest tiles
     d.adj_part = h->alloc<double>(static_cast<size_t>(d.n_params) * gx * gy + nxt * gx);
   }
   d.rmax = h->alloc<unsigned long long>(nxt);

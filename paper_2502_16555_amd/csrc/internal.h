@@ -81,7 +81,7 @@ struct DevOps {
   double* Fs = nullptr;        // [nx_total][n] adjoint: post-V state
   double* mu = nullptr;        // [nx_total][n] adjoint: A^-T X^T lambda
   double* adj_part = nullptr;  // adjoint gradient partial sums, one slot per block:
-                               // [n_params][ceil(nx/32)][ceil(n/64)] then [nx_total][ceil(n/64)]
+                               // [n_params][gy][gx] then [nx_total][gx] (at most ceil(nx/32), ceil(n/16))
   unsigned long long* rmax = nullptr;  // [nx_total] max|r| (as ordered bits)
   unsigned long long* bmax = nullptr;  // [nx_total] max|b|
   unsigned long long* xmax = nullptr;  // [nx_total] max|x|

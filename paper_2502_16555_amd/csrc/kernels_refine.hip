@@ -80,54 +80,16 @@ __global__ __launch_bounds__(256) void k_from_harm(const double* __restrict__ Xh
   }
 }
 
-// ---------------------------------------------------------------------------
-// FP64 residual R = B - X + dt n0_x (X C^T) + dt E_x (X A^T)  (TRANSPOSE: C, A)
-// rows = collocation points, ld doubles apart.  MODE 0: the refinement residual, with the
-// per-point maxima (skipped once the refinement is done); MODE 1: R = B - M X
-// only; MODE 2: R = M X (operator action of Alg. vspace_action, for the Krylov
-// solver); MODE 3: R = B - dt E (X A^T) (the field-coupling term of the fully
-// implicit Jacobian, eq. 1dbte_jac_action).
-//
-// A block computes 16 PT points x 16 OT outputs; its NW wavefronts share the
-// sum over k (a wavefront takes every NW-th chunk of 16), with the operands
-// straight from memory in 16-byte vectors, and their partial tiles meet in LDS.
-// Bound by the FP64 matrix rate (64 cycles per 16 x 16 x 4 product and SIMD)
-// where the tiles fill the chip: hence two shapes.  64 x 32 tiles of four
-// wavefronts load half as much per product, and run where they give every CU a
-// block; otherwise 32 x 16 tiles of eight wavefronts make eight times as many
-// blocks' worth of parallel work from a small grid.  The blocks of one output
-// tile run on one XCD, so that its rows of C and A come from HBM once.
-// Per residual (32 x 64 tiles staged in LDS, one barrier pair per 64 of k, no
-// split before): 100 points, n = 1024 57 -> 19 us; 200 points, n = 512 33 -> 11; 256
-// points, n = 2048 122 -> 83 (53 us at 69 TFLOP/s).  Three chunks in flight took
-// 22 us at the first, five 28: they push each other out of the 32 KB vector cache.
-// ---------------------------------------------------------------------------
-template <int TRANSPOSE, int MODE, int PT, int OT, int NW>
-__global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__ Bv, const double* __restrict__ Xv,
-                                                      double* __restrict__ Rv, const double* __restrict__ C,
-                                                      const double* __restrict__ Aop, const double* __restrict__ E,
-                                                      const double* __restrict__ n0x,
-                                                      unsigned long long* __restrict__ rmax,
-                                                      unsigned long long* __restrict__ bmax,
-                                                      unsigned long long* __restrict__ xmax,
-                                                      const int* __restrict__ status, double dt, int n, int ld,
-                                                      int nx, const int* __restrict__ skip) {
-  if (MODE == 0 && status[1]) return;
-  constexpr int BM = 16 * PT, BN = 16 * OT, CK = 16;
-  constexpr int NOP = MODE == 3 ? 1 : 2;         // operators: A, then C
-  constexpr int DEPTH = 2;                       // chunks in registers: one in use, one on its way
+// s_part[w][q] = this wavefront's part of the tile X[x0 ..][.] M_q^T[.][i0 ..]
+// (TRANSPOSE: M_q) for the operators q: 16 PT rows of X (ld doubles apart) x 16 OT
+// outputs, the sum over k shared by the block's NW wavefronts (each takes every
+// NW-th chunk of 16), operands straight from memory in 16-byte vectors.
+template <int TRANSPOSE, int NOP, int PT, int OT, int NW>
+__device__ __forceinline__ void tile_products(const double* __restrict__ Xv, int ld, const double* const (&M)[NOP],
+                                              int n, int nx, int x0, int i0,
+                                              double (&s_part)[NW][NOP][16 * PT][16 * OT]) {
+  constexpr int CK = 16, DEPTH = 2;   // chunks in registers: one in use, one on its way
   using V2 = double __attribute__((ext_vector_type(2)));
-  int bx, by;
-  xcd_map(blockIdx.x, (nx + BM - 1) / BM, (n + BN - 1) / BN, &bx, &by);
-  if (bx * BN >= n) return;
-  const int x0 = by * BM, i0 = bx * BN;
-  if (MODE != 0 && skip) {  // points already converged need no operator action
-    bool all = true;
-    for (int u = 0; u < BM && x0 + u < nx; ++u)
-      if (!skip[x0 + u]) all = false;
-    if (all) return;
-  }
-  __shared__ double s_part[NW][NOP][BM][BN];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   // operand rows of this lane (rows beyond the last repeat it; their results are dropped)
@@ -138,8 +100,8 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
 #pragma unroll
   for (int o = 0; o < OT; ++o) {
     const size_t i = min(i0 + o * 16 + li, n - 1);
-    op[0][o] = Aop + (TRANSPOSE ? i : i * n);
-    if constexpr (NOP == 2) op[1][o] = C + (TRANSPOSE ? i : i * n);
+#pragma unroll
+    for (int q = 0; q < NOP; ++q) op[q][o] = M[q] + (TRANSPOSE ? i : i * n);
   }
   const int nch = (n + CK - 1) / CK, cnt = (nch - w + NW - 1) / NW;
   struct Chunk {
@@ -209,6 +171,57 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
 #pragma unroll
         for (int t = 0; t < 4; ++t) s_part[w][q][p * 16 + f64_row(lk, t)][o * 16 + li] = acc[q][p][o][t];
   __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// FP64 residual R = B - X + dt n0_x (X C^T) + dt E_x (X A^T)  (TRANSPOSE: C, A)
+// rows = collocation points, ld doubles apart.  MODE 0: the refinement residual, with the
+// per-point maxima (skipped once the refinement is done); MODE 1: R = B - M X
+// only; MODE 2: R = M X (operator action of Alg. vspace_action, for the Krylov
+// solver); MODE 3: R = B - dt E (X A^T) (the field-coupling term of the fully
+// implicit Jacobian, eq. 1dbte_jac_action).
+//
+// A block computes 16 PT points x 16 OT outputs by tile_products, whose partial
+// tiles meet in LDS.  Bound by the FP64 matrix rate (64 cycles per 16 x 16 x 4 product and SIMD)
+// where the tiles fill the chip: hence two shapes.  64 x 32 tiles of four
+// wavefronts load half as much per product, and run where they give every CU a
+// block; otherwise 32 x 16 tiles of eight wavefronts make eight times as many
+// blocks' worth of parallel work from a small grid.  The blocks of one output
+// tile run on one XCD, so that its rows of C and A come from HBM once.
+// Per residual (32 x 64 tiles staged in LDS, one barrier pair per 64 of k, no
+// split before): 100 points, n = 1024 57 -> 19 us; 200 points, n = 512 33 -> 11; 256
+// points, n = 2048 122 -> 83 (53 us at 69 TFLOP/s).  Three chunks in flight took
+// 22 us at the first, five 28: they push each other out of the 32 KB vector cache.
+// ---------------------------------------------------------------------------
+template <int TRANSPOSE, int MODE, int PT, int OT, int NW>
+__global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__ Bv, const double* __restrict__ Xv,
+                                                      double* __restrict__ Rv, const double* __restrict__ C,
+                                                      const double* __restrict__ Aop, const double* __restrict__ E,
+                                                      const double* __restrict__ n0x,
+                                                      unsigned long long* __restrict__ rmax,
+                                                      unsigned long long* __restrict__ bmax,
+                                                      unsigned long long* __restrict__ xmax,
+                                                      const int* __restrict__ status, double dt, int n, int ld,
+                                                      int nx, const int* __restrict__ skip) {
+  if (MODE == 0 && status[1]) return;
+  constexpr int BM = 16 * PT, BN = 16 * OT;
+  constexpr int NOP = MODE == 3 ? 1 : 2;         // operators: A, then C
+  int bx, by;
+  xcd_map(blockIdx.x, (nx + BM - 1) / BM, (n + BN - 1) / BN, &bx, &by);
+  if (bx * BN >= n) return;
+  const int x0 = by * BM, i0 = bx * BN;
+  if (MODE != 0 && skip) {  // points already converged need no operator action
+    bool all = true;
+    for (int u = 0; u < BM && x0 + u < nx; ++u)
+      if (!skip[x0 + u]) all = false;
+    if (all) return;
+  }
+  __shared__ double s_part[NW][NOP][BM][BN];
+  const int tid = threadIdx.x;
+  const double* M[NOP];
+  M[0] = Aop;
+  if constexpr (NOP == 2) M[1] = C;
+  tile_products<TRANSPOSE, NOP, PT, OT, NW>(Xv, ld, M, n, nx, x0, i0, s_part);
   // sums, result, and (MODE 0) max |r|, |b| and |x| per point, reduced over the
   // tile's outputs before one atomic per point (bit patterns of non-negative
   // doubles order like the values, and a NaN orders above +inf)
@@ -329,90 +342,75 @@ __global__ void k_reset_refine(unsigned long long* rmax, unsigned long long* bma
 }
 
 // grad_scal[op] += dt sum_x n0_x mu_x^T C^(op) F*_x  and  grad_E[x] = dt mu_x^T A F*_x.
-// Tiled like the residual: out[x][i] = sum_k F*[x][k] M[i][k] (MFMA f64), then the
-// epilogue contracts with mu[x][i].  Grid: (gx = n/64, gy = ceil(nx/32), n_params + 1).
+// Tiled like the residual: out[x][i] = sum_k F*[x][k] M[i][k] (tile_products), then
+// the epilogue contracts with mu[x][i].  gx tiles of outputs, gy of points and
+// n_params + 1 operators, the blocks of one operator's output tile on one XCD.
 // Every block writes its partial sums to slots of its own (no atomics), and
 // k_adjoint_reduce adds the slots in a fixed order, so the gradients are the same
 // bit for bit from run to run:
 //   pscal[(op * gy + by) * gx + bx]  = dt sum_{x in block} n0_x (mu_x . out_x)   (op < n_params)
 //   pE[x * gx + bx]                  = dt (mu_x . out_x) over the block's i range  (op = n_params)
-__global__ __launch_bounds__(256) void k_adjoint_grads(const double* __restrict__ Mu, const double* __restrict__ Fs,
-                                                       const double* __restrict__ Csb, const double* __restrict__ Aop,
-                                                       const double* __restrict__ n0x, double* __restrict__ pscal,
-                                                       double* __restrict__ pE, double dt, int n, int nx, int nparams) {
-  constexpr int BM = 32, BN = 64, BK = 64;
-  const int op = blockIdx.z;
-  const double* M = (op < nparams) ? Csb + (size_t)op * n * n : Aop;
-  __shared__ double sX[BM][BK + 1];
-  __shared__ double sM[BN][BK + 1];
-  __shared__ double sRed[4][BM];
-  const int x0 = blockIdx.y * BM, i0 = blockIdx.x * BN;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  f64x4 acc[2] = {f64x4{0, 0, 0, 0}, f64x4{0, 0, 0, 0}};
-  for (int k0 = 0; k0 < n; k0 += BK) {
-    for (int e = tid; e < BM * BK; e += 256) {
-      const int r = e / BK, c = e % BK;
-      sX[r][c] = (x0 + r < nx && k0 + c < n) ? Fs[(size_t)(x0 + r) * n + k0 + c] : 0.0;
-    }
-    for (int e = tid; e < BN * BK; e += 256) {
-      const int r = e / BK, c = e % BK;
-      sM[r][c] = (i0 + r < n && k0 + c < n) ? M[(size_t)(i0 + r) * n + k0 + c] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < BK; k += 4) {
-      const double bm = sM[w * 16 + li][k + lk];
+// 128 points, n = 512, 24 parameters: 193 -> 62 us (32 x 64 tiles through LDS, no load
+// in flight during the products, before).
+template <int PT, int OT, int NW>
+__global__ __launch_bounds__(NW * 64) void k_adjoint_grads(const double* __restrict__ Mu,
+                                                           const double* __restrict__ Fs,
+                                                           const double* __restrict__ Csb,
+                                                           const double* __restrict__ Aop,
+                                                           const double* __restrict__ n0x, double* __restrict__ pscal,
+                                                           double* __restrict__ pE, double dt, int n, int nx,
+                                                           int nparams) {
+  constexpr int BM = 16 * PT, BN = 16 * OT;
+  const int gx = (n + BN - 1) / BN, gy = (nx + BM - 1) / BM;
+  int mi, by;
+  xcd_map(blockIdx.x, gy, gx * (nparams + 1), &mi, &by);
+  if (mi >= gx * (nparams + 1)) return;
+  const int op = mi / gx, bx = mi % gx, x0 = by * BM, i0 = bx * BN, tid = threadIdx.x;
+  __shared__ double s_part[NW][1][BM][BN];
+  __shared__ double s_pt[BM];
+  const double* M[1] = {(op < nparams) ? Csb + (size_t)op * n * n : Aop};
+  tile_products<0, 1, PT, OT, NW>(Fs, n, M, n, nx, x0, i0, s_part);
+  // dt mu . out per point, over the tile's outputs
 #pragma unroll
-      for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(sX[b * 16 + li][k + lk], bm, acc[b], 0, 0, 0);
+  for (int e = tid; e < BM * BN; e += NW * 64) {
+    const int xl = e / BN, il = e % BN, x = x0 + xl, i = i0 + il;
+    double v = 0.0;
+    if (x < nx && i < n) {
+#pragma unroll
+      for (int u = 0; u < NW; ++u) v += s_part[u][0][xl][il];
+      v *= Mu[(size_t)x * n + i];
     }
-    __syncthreads();
+#pragma unroll
+    for (int off = 1; off < BN; off <<= 1) v += __shfl_xor(v, off);
+    if (il == 0) {
+      if (op == nparams && x < nx) pE[(size_t)x * gx + bx] = dt * v;
+      s_pt[xl] = x < nx ? dt * n0x[x] * v : 0.0;
+    }
   }
-  // contract with mu: each wave reduces its 16 rows i for each of the 32 points
-  // (lanes of the same lk hold one point) and writes one slot per point
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int xl = b * 16 + f64_row(lk, it);
-      const int x = x0 + xl;
-      const int i = i0 + w * 16 + li;
-      double v = (x < nx && i < n) ? Mu[(size_t)x * n + i] * acc[b][it] : 0.0;
-      for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      if (li == 0) sRed[w][xl] = v;
-    }
   __syncthreads();
-  const size_t gx = gridDim.x, gy = gridDim.y;
-  if (op < nparams) {
-    if (tid == 0) {
-      double total = 0.0;
-      for (int xl = 0; xl < BM && x0 + xl < nx; ++xl)
-        total += dt * n0x[x0 + xl] * (((sRed[0][xl] + sRed[1][xl]) + sRed[2][xl]) + sRed[3][xl]);
-      pscal[((size_t)op * gy + blockIdx.y) * gx + blockIdx.x] = total;
-    }
-  } else if (tid < BM && x0 + tid < nx) {
-    pE[(size_t)(x0 + tid) * gx + blockIdx.x] =
-        dt * (((sRed[0][tid] + sRed[1][tid]) + sRed[2][tid]) + sRed[3][tid]);
+  if (op < nparams && tid < 64) {
+    double v = tid < BM ? s_pt[tid] : 0.0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off);
+    if (tid == 0) pscal[((size_t)op * gy + by) * gx + bx] = v;
   }
 }
 
-// Second pass: gscal[op] += sum over the (by, bx) slots, gE[x] = sum over bx,
-// both in ascending slot order.
-__global__ void k_adjoint_reduce(const double* __restrict__ pscal, const double* __restrict__ pE,
-                                 double* __restrict__ gscal, double* __restrict__ gE, int nparams, int nx, int gx,
-                                 int gy) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < nparams) {
-    const double* p = pscal + (size_t)t * gy * gx;
-    double s = 0.0;
-    for (int q = 0; q < gx * gy; ++q) s += p[q];
-    gscal[t] += s;
-  } else if (t < nparams + nx) {
-    const int x = t - nparams;
-    const double* p = pE + (size_t)x * gx;
-    double s = 0.0;
-    for (int q = 0; q < gx; ++q) s += p[q];
-    gE[x] = s;
+// Second pass: gscal[op] += sum over the (by, bx) slots, gE[x] = sum over bx, a
+// wavefront each, in a fixed order.
+__global__ __launch_bounds__(64) void k_adjoint_reduce(const double* __restrict__ pscal,
+                                                       const double* __restrict__ pE, double* __restrict__ gscal,
+                                                       double* __restrict__ gE, int nparams, int gx, int gy) {
+  const int t = blockIdx.x, lane = threadIdx.x;
+  const bool sc = t < nparams;
+  const double* p = sc ? pscal + (size_t)t * gy * gx : pE + (size_t)(t - nparams) * gx;
+  double s = 0.0;
+  for (int q = lane; q < (sc ? gx * gy : gx); q += 64) s += p[q];
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
+  if (lane == 0) {
+    if (sc) gscal[t] += s;
+    else gE[t - nparams] = s;
   }
 }
 
@@ -478,14 +476,21 @@ void launch_reset_refine(const DevOps& d, hipStream_t s) {
 }
 
 void launch_adjoint_grads(const DevOps& d, double* grad_scal, double* grad_E, hipStream_t s) {
-  const int gx = (d.n + 63) / 64, gy = (d.nx_total + 31) / 32;
-  dim3 g(gx, gy, d.n_params + 1);
-  double* pE = d.adj_part + (size_t)d.n_params * gx * gy;
-  k_adjoint_grads<<<g, 256, 0, s>>>(d.mu, d.Fs, d.Csb, d.Aord, d.n0x, d.adj_part, pE, d.dt, d.n, d.nx_total,
-                                    d.n_params);
-  const int tot = d.n_params + d.nx_total;
-  k_adjoint_reduce<<<(tot + 255) / 256, 256, 0, s>>>(d.adj_part, pE, grad_scal, grad_E, d.n_params, d.nx_total, gx,
-                                                     gy);
+  const int nop = d.n_params + 1;
+  auto go = [&](auto pt, auto ot, auto nw) {
+    constexpr int PT = decltype(pt)::value, OT = decltype(ot)::value, NW = decltype(nw)::value;
+    const int gx = (d.n + 16 * OT - 1) / (16 * OT), gy = (d.nx_total + 16 * PT - 1) / (16 * PT);
+    double* pE = d.adj_part + (size_t)d.n_params * gx * gy;
+    k_adjoint_grads<PT, OT, NW><<<xcd_grid(gy, gx * nop), NW * 64, 0, s>>>(d.mu, d.Fs, d.Csb, d.Aord, d.n0x, d.adj_part,
+                                                                          pE, d.dt, d.n, d.nx_total, d.n_params);
+    k_adjoint_reduce<<<d.n_params + d.nx_total, 64, 0, s>>>(d.adj_part, pE, grad_scal, grad_E, d.n_params, gx, gy);
+  };
+  using std::integral_constant;
+  // the residual's tiles, by the same rule over all operators' tiles
+  if (((d.nx_total + 63) / 64) * ((d.n + 31) / 32) * nop >= 256)
+    go(integral_constant<int, 4>(), integral_constant<int, 2>(), integral_constant<int, 4>());
+  else
+    go(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, 8>());
 }
 
 }  // namespace bte

@@ -629,6 +629,28 @@ def test_adjoint_step_matches_oracle(torch):
     s.close()
 
 
+@pytest.mark.parametrize("nx,nr,nth,bins", [(70, 20, 20, 4), (33, 13, 10, 1)])
+def test_adjoint_gradients_by_both_tiles(torch, nx, nr, nth, bins):
+    """Gradients of 13 operators by 64 x 32 tiles (338 of them, the last of each direction partly
+    filled) and of 4 by 32 x 16 tiles (n = 130), against the oracle; as the test above."""
+    cfg = workloads.small_config(nx=nx, nr=nr, nth=nth, kinds=("elastic", "excitation", "ionization"), E=5e3,
+                                 field_kind="rf", n_bins=bins)
+    ops = oracle.build_operators(cfg)
+    s = solver(cfg)
+    assert s.n_params == 3 * bins
+    F, L, t = _state(ops, 9), _state(ops, 10), 0.21 * cfg["T_rf_s"]
+    lam_o, gs_o, gE_o = S.adjoint_step(ops, F, t, L)
+    Lg = cuda(torch, L)
+    gs = torch.zeros(s.n_params, dtype=torch.float64, device="cuda:0")
+    gE0 = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    gE = torch.zeros(s.nx_total, dtype=torch.float64, device="cuda:0")
+    s.adjoint_step(cuda(torch, F), t, Lg, gs, gE0, gE)
+    close(Lg.cpu().numpy(), lam_o, 1e-10, '')
+    close(gs.cpu().numpy(), gs_o, 1e-10, '')
+    close(gE.cpu().numpy(), gE_o, 1e-10, '')
+    s.close()
+
+
 def test_adjoint_step_is_bitwise_reproducible(torch):
     """The gradient contractions sum their per-block partials in a fixed order
     (no floating-point atomics), so repeated adjoint steps from the same inputs
