@@ -124,7 +124,12 @@ __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, doub
 // Batched Chebyshev-system application for one (eigen-speed i, ordinate pair).
 // Qt holds Q_{i,a} transposed (Qt[c][r] = Q[r][c]) for the ordinates with cos > 0;
 // the mirrored ordinate uses Q(-mu) y = J Q(mu) J y.  transpose=1 applies Q^T.
-// Q is read once per half-step (537 MB at C2 in FP64) by non-temporal loads.
+// Q is read once per half-step (537 MB at 256 x 64 x 32 in FP64) by non-temporal
+// loads, which bound it: sums of 33 to 128 columns are split over two or four
+// groups of threads (shorter ones are on their way at once already), and the transposed product takes eight columns per
+// wavefront, so that enough of them are in flight.  Per half-step: 100 x 64 x 16
+// 13.2 -> 10.2 us, 256 x 64 x 32 83 -> 79 (6.8 TB/s); transposed, 128 x 32
+// x 16, 39 -> 11.
 template <typename QT, int TRANSPOSE>
 __global__ __launch_bounds__(kThreads) void k_advect(double* __restrict__ Y, const QT* __restrict__ Qt,
                                                      const size_t* __restrict__ q_off, const int* __restrict__ x_off,
@@ -147,34 +152,66 @@ __global__ __launch_bounds__(kThreads) void k_advect(double* __restrict__ Y, con
   __syncthreads();
   if (!TRANSPOSE) {
     // out[r] = sum_c Q[r][c] y[c] = sum_c Qt[c][r] y[c]: coalesced over r
-    for (int r = threadIdx.x; r < nx; r += blockDim.x) {
+    static_assert(kThreads == 256, "threads per group");
+    __shared__ double s_sum[2][kThreads];
+    const int lg = nx <= 32 ? 0 : (nx <= 64 ? 2 : (nx <= 128 ? 1 : 0)), groups = 1 << lg, tg = kThreads >> lg;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> (8 - lg));
+    const int len = (nx + groups - 1) >> lg, c0 = g * len, c1 = min(nx, c0 + len);
+    for (int r = threadIdx.x & (tg - 1); r < nx; r += tg) {
       double ap = 0.0, an = 0.0;
-#pragma unroll 8
-      for (int c = 0; c < nx; ++c) {
+#pragma unroll 16
+      for (int c = c0; c < c1; ++c) {
         const double q = static_cast<double>(__builtin_nontemporal_load(&Q[(size_t)c * nx + r]));
         ap += q * sy[c];
         an += q * sy[nx + c];
       }
-      yp[r] = ap;
-      yn[nx - 1 - r] = an;
+      if (groups > 1) {
+        s_sum[0][threadIdx.x] = ap;
+        s_sum[1][threadIdx.x] = an;
+      } else {
+        yp[r] = ap;
+        yn[nx - 1 - r] = an;
+      }
+    }
+    if (groups > 1) {
+      __syncthreads();
+      const int r = threadIdx.x;
+      if (r < nx) {
+        double ap = 0.0, an = 0.0;
+        for (int u = 0; u < groups; ++u) {
+          ap += s_sum[0][u * tg + r];
+          an += s_sum[1][u * tg + r];
+        }
+        yp[r] = ap;
+        yn[nx - 1 - r] = an;
+      }
     }
   } else {
-    // out[c] = sum_r Q[r][c] y[r] = sum_r Qt[c][r] y[r]: one wavefront per output c
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int c = wid; c < nx; c += nw) {
-      double ap = 0.0, an = 0.0;
-      for (int r = lane; r < nx; r += 64) {
-        const double q = static_cast<double>(__builtin_nontemporal_load(&Q[(size_t)c * nx + r]));
-        ap += q * sy[r];
-        an += q * sy[nx + r];
+    // out[c] = sum_r Q[r][c] y[r] = sum_r Qt[c][r] y[r]: eight outputs c per wavefront
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int c = 8 * wid; c < nx; c += 8 * (kThreads / 64)) {
+      double ap[8], an[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ap[u] = an[u] = 0.0;
+#pragma unroll 2
+      for (int r0 = 0; r0 < nx; r0 += 64) {
+        const int r = r0 + lane, rc = min(r, nx - 1);
+        double q[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          q[u] = static_cast<double>(__builtin_nontemporal_load(&Q[(size_t)min(c + u, nx - 1) * nx + rc]));
+        const double zp = r < nx ? sy[rc] : 0.0, zn = r < nx ? sy[nx + rc] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          ap[u] += q[u] * zp;
+          an[u] += q[u] * zn;
+        }
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        ap += __shfl_xor(ap, off);
-        an += __shfl_xor(an, off);
-      }
-      if (lane == 0) {
-        yp[c] = ap;
-        yn[nx - 1 - c] = an;
+      const double tp = fold8(ap, lane), tn = fold8(an, lane);
+      const int cc = c + lane;
+      if (lane < 8 && cc < nx) {
+        yp[cc] = tp;
+        yn[nx - 1 - cc] = tn;
       }
     }
   }

@@ -188,5 +188,26 @@ struct Vec4<_Float16> {
   static constexpr int per = 8;
 };
 
+// Sums of the wavefront for eight values per lane: lane l returns value l mod 8's
+// (the values are halved three times as the lanes pair up, then summed).
+__device__ __forceinline__ double fold8(const double (&v)[8], int lane) {
+  double a[4], b[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool up = lane & 1;
+    a[i] = (up ? v[2 * i + 1] : v[2 * i]) + __shfl_xor(up ? v[2 * i] : v[2 * i + 1], 1);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool up = lane & 2;
+    b[i] = (up ? a[2 * i + 1] : a[2 * i]) + __shfl_xor(up ? a[2 * i] : a[2 * i + 1], 2);
+  }
+  const bool up = lane & 4;
+  double c = (up ? b[1] : b[0]) + __shfl_xor(up ? b[0] : b[1], 4);
+  c += __shfl_xor(c, 8);
+  c += __shfl_xor(c, 16);
+  return c + __shfl_xor(c, 32);
+}
+
 }  // namespace
 }  // namespace bte
