@@ -2,8 +2,7 @@
 // (B - s A_h) u = b of eq. (vspace_batched_system), s = dt E_x, reduced once per
 // discharge to u = Q (I - s H)^-1 W b with H upper Hessenberg; see hessenberg.cpp):
 //   k_mat_apply   Out[x] = M In[x] for the points of one discharge (W, then Q):
-//                 32 points x 64 outputs per block, MFMA f64 16x16x4, K through
-//                 double-buffered LDS;
+//                 MFMA f64 16x16x4 on the residual's tiles;
 //   k_hess_solve  (I - s H) z = y, one block per point, in O(n^2): Givens
 //                 rotations of columns (k-1, k), k = n-1 .. 1, turn G = I - s H
 //                 into an upper triangular R = G Z; column k of R is final once
@@ -15,97 +14,32 @@
 
 #include "internal.h"
 #include "lu_common.h"
+#include "tile_products.h"
 
 namespace bte {
 namespace {
 
-
-// Result row of item t of lane group lk for MFMA f64 16x16x4 (measured layout).
-__device__ inline int f64_row(int lk, int t) { return lk + 4 * t; }
-
 // Out[x][i] = sum_k M[i][k] In[x][k], x in [x0, x0 + nx), i < n; M, In and Out
-// rows of length ld (M zero from column n on).  Block: 32 points x 64 outputs,
-// each wave two 16 x 16 MFMA tiles; K in chunks of 64 through two LDS buffers,
-// the next chunk's 16-byte global loads in flight while the current one is
-// multiplied.  Grid: (ceil(n / 64), ceil(nx / 32)); the blocks of one XCD
-// (block id mod 8) share their rows of M.
-constexpr int kMaBM = 32, kMaBN = 64, kMaBK = 64;
-constexpr int kMaLds = kMaBK + 1;   // odd row stride: the fragment reads are conflict-free
-constexpr int kMaALoads = kMaBM * kMaBK / 2 / 256, kMaBLoads = kMaBN * kMaBK / 2 / 256;
-
-__global__ __launch_bounds__(256) void k_mat_apply(const double* __restrict__ M, const double* __restrict__ In,
-                                                   double* __restrict__ Out, int n, int ld, int x0, int nx) {
-  constexpr int BM = kMaBM, BN = kMaBN, BK = kMaBK, LDL = kMaLds;
-  extern __shared__ double lds[];
-  double* sX = lds;                      // [2][BM][LDL]
-  double* sM = lds + 2 * BM * LDL;       // [2][BN][LDL]
-  const int xb = blockIdx.y * BM, i0 = blockIdx.x * BN;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  f64x2 ra[kMaALoads], rb[kMaBLoads];
-  auto load = [&](int k0) __attribute__((always_inline)) {
+// rows of length ld (M zero from column n on).  The residual's tiles, by the
+// same rule: at 100 points, n = 192 they make 48 blocks of eight wavefronts that
+// share the sum (12 blocks of 64 outputs, K serial, before): 11.8 -> 6.3 us.
+template <int PT, int OT, int NW>
+__global__ __launch_bounds__(NW * 64) void k_mat_apply(const double* __restrict__ M, const double* __restrict__ In,
+                                                       double* __restrict__ Out, int n, int ld, int nx) {
+  constexpr int BM = 16 * PT, BN = 16 * OT;
+  int bx, by;
+  xcd_map(blockIdx.x, (nx + BM - 1) / BM, (n + BN - 1) / BN, &bx, &by);
+  if (bx * BN >= n) return;
+  __shared__ double s_part[NW][1][BM][BN];
+  const double* Mq[1] = {M};
+  tile_products<0, 1, PT, OT, NW>(In, ld, Mq, ld, n, nx, by * BM, bx * BN, s_part);
+  for (int e = threadIdx.x; e < BM * BN; e += NW * 64) {
+    const int xl = e / BN, il = e % BN, x = by * BM + xl, i = bx * BN + il;
+    double v = 0.0;
 #pragma unroll
-    for (int t = 0; t < kMaALoads; ++t) {
-      const int e = tid + 256 * t, r = e / (BK / 2), k = k0 + 2 * (e % (BK / 2));
-      f64x2 v = {0.0, 0.0};
-      if (xb + r < nx && k < n) {
-        v = *reinterpret_cast<const f64x2*>(In + (size_t)(x0 + xb + r) * ld + k);
-        if (k + 1 >= n) v[1] = 0.0;
-      }
-      ra[t] = v;
-    }
-#pragma unroll
-    for (int t = 0; t < kMaBLoads; ++t) {
-      const int e = tid + 256 * t, r = e / (BK / 2), k = k0 + 2 * (e % (BK / 2));
-      f64x2 v = {0.0, 0.0};
-      if (i0 + r < n && k < n) v = *reinterpret_cast<const f64x2*>(M + (size_t)(i0 + r) * ld + k);
-      rb[t] = v;
-    }
-  };
-  auto store = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < kMaALoads; ++t) {
-      const int e = tid + 256 * t, r = e / (BK / 2), c = 2 * (e % (BK / 2));
-      double* d = sX + (buf * BM + r) * LDL + c;
-      d[0] = ra[t][0];
-      d[1] = ra[t][1];
-    }
-#pragma unroll
-    for (int t = 0; t < kMaBLoads; ++t) {
-      const int e = tid + 256 * t, r = e / (BK / 2), c = 2 * (e % (BK / 2));
-      double* d = sM + (buf * BN + r) * LDL + c;
-      d[0] = rb[t][0];
-      d[1] = rb[t][1];
-    }
-  };
-  f64x4 acc[2] = {f64x4{0, 0, 0, 0}, f64x4{0, 0, 0, 0}};
-  const int nch = (n + BK - 1) / BK;
-  load(0);
-  store(0);
-  __syncthreads();
-  for (int c = 0; c < nch; ++c) {
-    const int buf = c & 1;
-    if (c + 1 < nch) load((c + 1) * BK);
-    const double* xa = sX + buf * BM * LDL;
-    const double* mb = sM + (buf * BN + w * 16 + li) * LDL + lk;
-#pragma unroll
-    for (int k = 0; k < BK; k += 4) {
-      const double bm = mb[k];
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[(b * 16 + li) * LDL + k + lk], bm, acc[b], 0, 0, 0);
-    }
-    if (c + 1 < nch) store(buf ^ 1);
-    __syncthreads();
+    for (int u = 0; u < NW; ++u) v += s_part[u][0][xl][il];
+    if (x < nx && i < n) Out[(size_t)x * ld + i] = v;
   }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int xl = xb + b * 16 + f64_row(lk, it);
-      const int i = i0 + w * 16 + li;
-      if (xl < nx && i < n) Out[(size_t)(x0 + xl) * ld + i] = acc[b][it];
-    }
 }
 
 constexpr int kHessThreads = 256;
@@ -315,14 +249,18 @@ __global__ __launch_bounds__(kHessThreads) void k_hess_solve(const double* __res
 
 void launch_mat_apply(const double* M, const double* In, double* Out, int n, int ld, int x0, int nx, hipStream_t s) {
   if (nx <= 0) return;
-  constexpr size_t lds = (size_t)2 * (kMaBM + kMaBN) * kMaLds * sizeof(double);
-  static const bool attr = [] {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mat_apply),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
-  }();
-  (void)attr;
-  dim3 g((n + kMaBN - 1) / kMaBN, (nx + kMaBM - 1) / kMaBM);
-  k_mat_apply<<<g, 256, lds, s>>>(M, In, Out, n, ld, x0, nx);
+  const double* in = In + (size_t)x0 * ld;
+  double* out = Out + (size_t)x0 * ld;
+  auto go = [&](auto pt, auto ot, auto nw) {
+    constexpr int PT = decltype(pt)::value, OT = decltype(ot)::value, NW = decltype(nw)::value;
+    const int grid = xcd_grid((nx + 16 * PT - 1) / (16 * PT), (n + 16 * OT - 1) / (16 * OT));
+    k_mat_apply<PT, OT, NW><<<grid, NW * 64, 0, s>>>(M, in, out, n, ld, nx);
+  };
+  using std::integral_constant;
+  if (((nx + 63) / 64) * ((n + 31) / 32) >= 256)
+    go(integral_constant<int, 4>(), integral_constant<int, 2>(), integral_constant<int, 4>());
+  else
+    go(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, 8>());
 }
 
 int hess_col_stride(int n) { return hess_pairs(n) * kHessSeg; }

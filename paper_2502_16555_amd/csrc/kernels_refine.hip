@@ -8,18 +8,13 @@
 
 #include "internal.h"
 #include "lu_common.h"
+#include "tile_products.h"
 
 namespace bte {
 namespace {
 
-using f64x4 = double __attribute__((ext_vector_type(4)));
-
-// Result row of item t of lane group lk for MFMA f64 16x16x4 (measured layout).
-__device__ inline int f64_row(int lk, int t) { return lk + 4 * t; }
-
 // Rows of n entries (the caller's, at any double address) <-> rows padded with
 // zeros to npad, a block per row (n is even: two ordinates per mu).
-using V2u = double __attribute__((ext_vector_type(2), aligned(8)));
 __global__ __launch_bounds__(256) void k_pad(const double* __restrict__ F, double* __restrict__ Bp, int n, int npad) {
   const double* f = F + (size_t)blockIdx.x * n;
   double* b = Bp + (size_t)blockIdx.x * npad;
@@ -80,99 +75,6 @@ __global__ __launch_bounds__(256) void k_from_harm(const double* __restrict__ Xh
   }
 }
 
-// s_part[w][q] = this wavefront's part of the tile X[x0 ..][.] M_q^T[.][i0 ..]
-// (TRANSPOSE: M_q) for the operators q: 16 PT rows of X (ld doubles apart) x 16 OT
-// outputs, the sum over k shared by the block's NW wavefronts (each takes every
-// NW-th chunk of 16), operands straight from memory in 16-byte vectors.
-template <int TRANSPOSE, int NOP, int PT, int OT, int NW>
-__device__ __forceinline__ void tile_products(const double* __restrict__ Xv, int ld, const double* const (&M)[NOP],
-                                              int n, int nx, int x0, int i0,
-                                              double (&s_part)[NW][NOP][16 * PT][16 * OT]) {
-  constexpr int CK = 16, DEPTH = 2;   // chunks in registers: one in use, one on its way
-  using V2 = double __attribute__((ext_vector_type(2)));
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 15, lk = lane >> 4;
-  // operand rows of this lane (rows beyond the last repeat it; their results are dropped)
-  const double* xp[PT];
-  const double* op[NOP][OT];
-#pragma unroll
-  for (int p = 0; p < PT; ++p) xp[p] = Xv + (size_t)min(x0 + p * 16 + li, nx - 1) * ld;
-#pragma unroll
-  for (int o = 0; o < OT; ++o) {
-    const size_t i = min(i0 + o * 16 + li, n - 1);
-#pragma unroll
-    for (int q = 0; q < NOP; ++q) op[q][o] = M[q] + (TRANSPOSE ? i : i * n);
-  }
-  const int nch = (n + CK - 1) / CK, cnt = (nch - w + NW - 1) / NW;
-  struct Chunk {
-    V2 x[PT][2], m[NOP][OT][2];
-  } buf[DEPTH];
-  // k of a lane's vector j: 8 j + 2 lk, + 1 within the chunk
-  auto load = [&](Chunk& c, int it) {
-    const int kc = CK * (w + NW * min(it, cnt - 1)) + 2 * lk;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int k = min(kc + 8 * j, n - 2);
-#pragma unroll
-      for (int p = 0; p < PT; ++p) c.x[p][j] = *reinterpret_cast<const V2u*>(xp[p] + k);
-#pragma unroll
-      for (int q = 0; q < NOP; ++q)
-#pragma unroll
-        for (int o = 0; o < OT; ++o) {
-          if constexpr (TRANSPOSE) c.m[q][o][j] = V2{op[q][o][(size_t)k * n], op[q][o][(size_t)(k + 1) * n]};
-          else c.m[q][o][j] = *reinterpret_cast<const V2*>(op[q][o] + k);
-        }
-    }
-  };
-  f64x4 acc[NOP][PT][OT];
-#pragma unroll
-  for (int q = 0; q < NOP; ++q)
-#pragma unroll
-    for (int p = 0; p < PT; ++p)
-#pragma unroll
-      for (int o = 0; o < OT; ++o) acc[q][p][o] = f64x4{0, 0, 0, 0};
-  auto product = [&](Chunk& c, int it) {
-    if (CK * (w + NW * it) + CK > n) {   // the last chunk of an n that 16 does not divide
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        if (CK * (w + NW * it) + 2 * lk + 8 * j >= n) {
-#pragma unroll
-          for (int p = 0; p < PT; ++p) c.x[p][j] = V2{0.0, 0.0};
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-#pragma unroll
-        for (int q = 0; q < NOP; ++q)
-#pragma unroll
-          for (int p = 0; p < PT; ++p)
-#pragma unroll
-            for (int o = 0; o < OT; ++o)
-              acc[q][p][o] = __builtin_amdgcn_mfma_f64_16x16x4f64(c.x[p][j][e], c.m[q][o][j][e], acc[q][p][o], 0, 0, 0);
-  };
-  if (cnt > 0) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) load(buf[d], d);
-    for (int it = 0; it < cnt; it += DEPTH)
-#pragma unroll
-      for (int d = 0; d < DEPTH; ++d) {
-        if (it + d < cnt) product(buf[d], it + d);
-        load(buf[d], it + d + DEPTH);
-      }
-  }
-#pragma unroll
-  for (int q = 0; q < NOP; ++q)
-#pragma unroll
-    for (int p = 0; p < PT; ++p)
-#pragma unroll
-      for (int o = 0; o < OT; ++o)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) s_part[w][q][p * 16 + f64_row(lk, t)][o * 16 + li] = acc[q][p][o][t];
-  __syncthreads();
-}
-
 // ---------------------------------------------------------------------------
 // FP64 residual R = B - X + dt n0_x (X C^T) + dt E_x (X A^T)  (TRANSPOSE: C, A)
 // rows = collocation points, ld doubles apart.  MODE 0: the refinement residual, with the
@@ -221,7 +123,7 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
   const double* M[NOP];
   M[0] = Aop;
   if constexpr (NOP == 2) M[1] = C;
-  tile_products<TRANSPOSE, NOP, PT, OT, NW>(Xv, ld, M, n, nx, x0, i0, s_part);
+  tile_products<TRANSPOSE, NOP, PT, OT, NW>(Xv, ld, M, n, n, nx, x0, i0, s_part);
   // sums, result, and (MODE 0) max |r|, |b| and |x| per point, reduced over the
   // tile's outputs before one atomic per point (bit patterns of non-negative
   // doubles order like the values, and a NaN orders above +inf)
@@ -369,7 +271,7 @@ __global__ __launch_bounds__(NW * 64) void k_adjoint_grads(const double* __restr
   __shared__ double s_part[NW][1][BM][BN];
   __shared__ double s_pt[BM];
   const double* M[1] = {(op < nparams) ? Csb + (size_t)op * n * n : Aop};
-  tile_products<0, 1, PT, OT, NW>(Fs, n, M, n, nx, x0, i0, s_part);
+  tile_products<0, 1, PT, OT, NW>(Fs, n, M, n, n, nx, x0, i0, s_part);
   // dt mu . out per point, over the tile's outputs
 #pragma unroll
   for (int e = tid; e < BM * BN; e += NW * 64) {

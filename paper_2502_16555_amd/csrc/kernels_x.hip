@@ -126,10 +126,10 @@ __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, doub
 // the mirrored ordinate uses Q(-mu) y = J Q(mu) J y.  transpose=1 applies Q^T.
 // Q is read once per half-step (537 MB at 256 x 64 x 32 in FP64) by non-temporal
 // loads, which bound it: sums of 33 to 128 columns are split over two or four
-// groups of threads (shorter ones are on their way at once already), and the transposed product takes eight columns per
-// wavefront, so that enough of them are in flight.  Per half-step: 100 x 64 x 16
-// 13.2 -> 10.2 us, 256 x 64 x 32 83 -> 79 (6.8 TB/s); transposed, 128 x 32
-// x 16, 39 -> 11.
+// groups of threads (shorter ones are on their way at once already), and the
+// transposed product takes eight columns per wavefront, so that enough of them
+// are in flight.  Per half-step: 100 x 64 x 16 13.2 -> 10.2 us, 256 x 64 x 32 83 ->
+// 79 (6.8 TB/s); transposed, 128 x 32 x 16, 39 -> 11.
 template <typename QT, int TRANSPOSE>
 __global__ __launch_bounds__(kThreads) void k_advect(double* __restrict__ Y, const QT* __restrict__ Qt,
                                                      const size_t* __restrict__ q_off, const int* __restrict__ x_off,
