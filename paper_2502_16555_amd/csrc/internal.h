@@ -82,9 +82,9 @@ struct DevOps {
   double* mu = nullptr;        // [nx_total][n] adjoint: A^-T X^T lambda
   double* adj_part = nullptr;  // adjoint gradient partial sums, one slot per block:
                                // [n_params][gy][gx] then [nx_total][gx] (at most ceil(nx/32), ceil(n/16))
-  unsigned long long* rmax = nullptr;  // [nx_total] max|r| (as ordered bits)
-  unsigned long long* bmax = nullptr;  // [nx_total] max|b|
-  unsigned long long* xmax = nullptr;  // [nx_total] max|x|
+  unsigned long long* rmax = nullptr;  // [2][nx_total] max|r| (as ordered bits), by sweep parity
+  unsigned long long* bmax = nullptr;  // [2][nx_total] max|b|
+  unsigned long long* xmax = nullptr;  // [2][nx_total] max|x|
   // bounds of the operator norms for the refinement stop: inf-norm (row sums)
   // and 1-norm (column sums) of C_ord and A_ord
   double c_inf = 0.0, a_inf = 0.0, c_one = 0.0, a_one = 0.0;
@@ -252,14 +252,38 @@ void launch_lu_factor(const DevOps& d, int precision, hipStream_t s, LuTimer* ti
 void launch_update(int kind, void* LU, int npad, int k0, int mtr, int mtc, int tj0, int nmat, bool alt_kc,
                    hipStream_t s, int kd = kNB, int lrow = 0, const float* rmax = nullptr,
                    const float* cmax = nullptr);
+// The stop test of a refinement sweep on the maxima of its residual (slot: the
+// sweep's parity); the solve that follows takes the test itself.
+struct RefineCheck {
+  unsigned long long *r = nullptr, *b = nullptr, *x = nullptr;      // the sweep's maxima (r NULL: no test)
+  unsigned long long *r1 = nullptr, *b1 = nullptr, *x1 = nullptr;   // the next sweep's, to be cleared
+  const double *E = nullptr, *n0x = nullptr;
+  double dt = 0.0, cnorm = 0.0, anorm = 0.0, rtol = 0.0;
+  int* status = nullptr;
+  double* resid = nullptr;
+  int sweep = 0, nx = 0;
+};
+inline RefineCheck refine_check(const DevOps& d, bool transpose, double rtol, int sweep) {
+  RefineCheck c;
+  const size_t o = (sweep & 1) ? d.nx_total : 0, o1 = d.nx_total - o;
+  c.r = d.rmax + o, c.b = d.bmax + o, c.x = d.xmax + o;
+  c.r1 = d.rmax + o1, c.b1 = d.bmax + o1, c.x1 = d.xmax + o1;
+  c.E = d.E, c.n0x = d.n0x;
+  c.dt = d.dt, c.cnorm = transpose ? d.c_one : d.c_inf, c.anorm = transpose ? d.a_one : d.a_inf, c.rtol = rtol;
+  c.status = d.status, c.resid = d.resid;
+  c.sweep = sweep, c.nx = d.nx_total;
+  return c;
+}
 // X = LU^-1 B (or LU^-T B with transpose), rows of length npad, FP64 right-hand sides.
+// With a check (check.r; mixed precisions): nothing if the refinement is done or the
+// test ends it, else also clears the next sweep's maxima.
 void launch_lu_solve(const DevOps& d, int precision, bool transpose, const double* Bin, double* Xout,
-                     bool accumulate, bool check_done, hipStream_t s);
+                     bool accumulate, const RefineCheck& check, hipStream_t s);
 // As launch_lu_solve for nrows right-hand sides, row r solved with the factors
 // of matrix mat_of[r] of f (mat_of NULL: matrix r); rows with skip[r] != 0 are
 // left untouched (skip may be NULL).
 void launch_lu_solve_mapped(const DevOps& f, int precision, bool transpose, const int* mat_of, const int* skip,
-                            int nrows, const double* Bin, double* Xout, bool accumulate, bool check_done,
+                            int nrows, const double* Bin, double* Xout, bool accumulate, const RefineCheck& check,
                             hipStream_t s);
 // FP32 -> FP16 copy of n elements (factor storage for preconditioning solves).
 void launch_to_half(const float* src, void* dst, size_t n, hipStream_t s);
@@ -273,12 +297,13 @@ void launch_from_harm(const DevOps& d, int nl, int npad_h, const double* Xh, con
 void launch_pad_rows(const DevOps& d, const double* F, double* Bp, hipStream_t s);
 void launch_unpad_rows(const DevOps& d, const double* Bp, double* F, hipStream_t s);
 // FP64 residual R = B - (I - dt (n0 C + E A)) X (or with A^T for transpose) + per-x norms.
-void launch_residual(const DevOps& d, bool transpose, hipStream_t s);
+void launch_residual(const DevOps& d, bool transpose, int sweep, hipStream_t s);
 // Operator M = I - dt (n0 C + E A) on padded rows: mode 1: R = B - M X; mode 2: R = M X.
 // Tiles of 32 or 64 points that all have skip[x] != 0 are left out (skip may be NULL).
 void launch_apply(const DevOps& d, int mode, const double* B, const double* X, double* R, const int* skip,
                   hipStream_t s);
-void launch_refine_check(const DevOps& d, bool transpose, double rtol, int sweep, bool final_sweep, hipStream_t s);
+// The test after the last sweep (kStNoConv if it fails).
+void launch_refine_check(const RefineCheck& c, hipStream_t s);
 void launch_reset_refine(const DevOps& d, hipStream_t s);
 // p[0..n) = v (a kernel, so that captured graphs hold no memset nodes).
 void launch_fill(double* p, double v, size_t n, hipStream_t s);

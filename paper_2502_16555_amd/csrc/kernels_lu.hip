@@ -1552,11 +1552,24 @@ template <typename T, int TRANSPOSE>
 __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const float* __restrict__ tinv,
                                                 const int* __restrict__ perm, const double* __restrict__ Bin,
                                                 double* __restrict__ Xout,
-                                                const int* __restrict__ status, int accumulate, int check_done,
-                                                int npad, const int* __restrict__ mat_of,
+                                                RefineCheck check, int accumulate, int npad, const int* __restrict__ mat_of,
                                                 const int* __restrict__ skip, int band_lo, int band_up, int paired,
                                                 const int* __restrict__ mirror, int n, int nth) {
-  if (check_done && status[1]) return;
+  if constexpr (sizeof(T) == 4) {
+    if (check.r) {   // a refinement sweep: its stop test first, in every block alike
+      if (check.status[1]) return;
+      const double worst = refine_worst<1024>(check);
+      if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+          check.resid[0] = worst;
+          check.status[2] = check.sweep;
+          if (worst <= check.rtol) check.status[1] = 1;
+        }
+        for (int x = threadIdx.x; x < check.nx; x += 1024) check.r1[x] = check.b1[x] = check.x1[x] = 0ull;
+      }
+      if (worst <= check.rtol) return;
+    }
+  }
   // right-hand side / solution row: the block; factors: that row's own matrix,
   // or the one mat_of names (a shared factorization, e.g. a preconditioner bin)
   const int row = blockIdx.x;
@@ -2099,12 +2112,12 @@ void launch_to_half(const float* src, void* dst, size_t n, hipStream_t s) {
 }
 
 void launch_lu_solve(const DevOps& d, int precision, bool transpose, const double* Bin, double* Xout, bool accumulate,
-                     bool check_done, hipStream_t s) {
-  launch_lu_solve_mapped(d, precision, transpose, nullptr, nullptr, d.nx_total, Bin, Xout, accumulate, check_done, s);
+                     const RefineCheck& check, hipStream_t s) {
+  launch_lu_solve_mapped(d, precision, transpose, nullptr, nullptr, d.nx_total, Bin, Xout, accumulate, check, s);
 }
 
 void launch_lu_solve_mapped(const DevOps& f, int precision, bool transpose, const int* mat_of, const int* skip,
-                            int nrows, const double* Bin, double* Xout, bool accumulate, bool check_done,
+                            int nrows, const double* Bin, double* Xout, bool accumulate, const RefineCheck& check,
                             hipStream_t s) {
   // the mirror flags of the FP32 factors, set at their formation
   const int* mir = (precision != 0 && precision != kFactorsFp16) ? f.mirror : nullptr;
@@ -2112,7 +2125,7 @@ void launch_lu_solve_mapped(const DevOps& f, int precision, bool transpose, cons
     using T = std::remove_const_t<std::remove_pointer_t<decltype(LU)>>;
     auto go = [&](auto tc) {
       k_solve<T, decltype(tc)::value><<<nrows, 1024, 0, s>>>(
-          LU, f.tinv, f.perm, Bin, Xout, f.status, accumulate, check_done, f.npad, mat_of, skip, f.band_kl,
+          LU, f.tinv, f.perm, Bin, Xout, check, accumulate, f.npad, mat_of, skip, f.band_kl,
           f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
     };
     if (transpose) go(std::integral_constant<int, 1>());

@@ -173,12 +173,14 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
 
 template <int TRANSPOSE, int MODE>
 void run_residual(const DevOps& d, const double* B, const double* X, double* R, const double* E, const int* skip,
-                  int ld, hipStream_t s) {
+                  int ld, hipStream_t s, int slot = 0) {
   auto go = [&](auto pt, auto ot, auto nw) {
     constexpr int PT = decltype(pt)::value, OT = decltype(ot)::value, NW = decltype(nw)::value;
     const int grid = xcd_grid((d.nx_total + 16 * PT - 1) / (16 * PT), (d.n + 16 * OT - 1) / (16 * OT));
-    k_residual<TRANSPOSE, MODE, PT, OT, NW><<<grid, NW * 64, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x, d.rmax, d.bmax,
-                                                                    d.xmax, d.status, d.dt, d.n, ld, d.nx_total,
+    const size_t o = (size_t)slot * d.nx_total;
+    k_residual<TRANSPOSE, MODE, PT, OT, NW><<<grid, NW * 64, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x,
+                                                                    d.rmax + o, d.bmax + o, d.xmax + o, d.status, d.dt,
+                                                                    d.n, ld, d.nx_total,
                                                                     skip);
   };
   using std::integral_constant;
@@ -189,50 +191,23 @@ void run_residual(const DevOps& d, const double* B, const double* X, double* R, 
     go(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, 8>());
 }
 
-// Stop test of the refinement: the normwise backward error of every point,
-//   eta_x = max|r_x| / (||M_x|| max|x_x| + max|b_x|),
-// with ||M_x|| <= 1 + dt (n0_x ||C|| + |E_x| ||A||) in the norm that matches
-// max-norms of the vectors (inf-norm for M, 1-norm for M^T).  The residual's own
-// FP64 rounding is of order sqrt(n) eps ||M|| |x|, so a bound relative to |b|
-// alone is unreachable once dt |E| ||A|| grows; eta is not.
-// status[1] = done flag, status[2] = sweeps used; resid[0] = max_x eta_x.
-__global__ void k_refine_check(unsigned long long* __restrict__ rmax, unsigned long long* __restrict__ bmax,
-                               unsigned long long* __restrict__ xmax, const double* __restrict__ E,
-                               const double* __restrict__ n0x, double dt, double cnorm, double anorm,
-                               int* __restrict__ status, double* __restrict__ resid, double rtol, int sweep,
-                               int final_sweep, int nx) {
-  if (status[1]) return;
-  __shared__ double red[256];
-  double worst = 0.0;
-  for (int x = threadIdx.x; x < nx; x += blockDim.x) {
-    const double r = __longlong_as_double(static_cast<long long>(rmax[x]));
-    const double b = __longlong_as_double(static_cast<long long>(bmax[x]));
-    const double xm = __longlong_as_double(static_cast<long long>(xmax[x]));
-    const double mn = 1.0 + dt * (n0x[x] * cnorm + fabs(E[x]) * anorm);
-    const double den = mn * xm + b;
-    const double q = (den > 0.0) ? r / den : (r > 0.0 ? INFINITY : 0.0);
-    worst = fmax(worst, (q == q) ? q : INFINITY);
-    rmax[x] = 0ull;
-    bmax[x] = 0ull;
-    xmax[x] = 0ull;
-  }
-  red[threadIdx.x] = worst;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
+// The test after the last sweep: status[1] = done flag, status[2] = sweeps used,
+// resid[0] = max_x eta_x (the sweeps before are tested by the solves, which set
+// the same).
+__global__ __launch_bounds__(256) void k_refine_check(RefineCheck c) {
+  if (c.status[1]) return;
+  const double worst = refine_worst<256>(c);
   if (threadIdx.x == 0) {
-    resid[0] = red[0];
-    status[2] = sweep;
-    if (red[0] <= rtol) status[1] = 1;
-    else if (final_sweep) atomicOr(status, kStNoConv);
+    c.resid[0] = worst;
+    c.status[2] = c.sweep;
+    if (worst <= c.rtol) c.status[1] = 1;
+    else atomicOr(c.status, kStNoConv);
   }
 }
 
 __global__ void k_reset_refine(unsigned long long* rmax, unsigned long long* bmax, unsigned long long* xmax,
-                               int* status, int nx) {
-  for (int x = threadIdx.x; x < nx; x += blockDim.x) {
+                               int* status, int n) {
+  for (int x = threadIdx.x; x < n; x += blockDim.x) {
     rmax[x] = 0ull;
     bmax[x] = 0ull;
     xmax[x] = 0ull;
@@ -350,9 +325,9 @@ void launch_apply_field(const DevOps& d, int mode, const double* B, const double
   else run_residual<0, 2>(d, B, X, R, E, nullptr, d.n, s);
 }
 
-void launch_residual(const DevOps& d, bool transpose, hipStream_t s) {
-  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s);
-  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s);
+void launch_residual(const DevOps& d, bool transpose, int sweep, hipStream_t s) {
+  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s, sweep & 1);
+  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s, sweep & 1);
 }
 
 namespace {
@@ -367,14 +342,10 @@ void launch_fill(double* p, double v, size_t n, hipStream_t s) {
   k_fill<<<blocks, 256, 0, s>>>(p, v, n);
 }
 
-void launch_refine_check(const DevOps& d, bool transpose, double rtol, int sweep, bool final_sweep, hipStream_t s) {
-  k_refine_check<<<1, 256, 0, s>>>(d.rmax, d.bmax, d.xmax, d.E, d.n0x, d.dt, transpose ? d.c_one : d.c_inf,
-                                   transpose ? d.a_one : d.a_inf, d.status, d.resid, rtol, sweep, final_sweep ? 1 : 0,
-                                   d.nx_total);
-}
+void launch_refine_check(const RefineCheck& c, hipStream_t s) { k_refine_check<<<1, 256, 0, s>>>(c); }
 
 void launch_reset_refine(const DevOps& d, hipStream_t s) {
-  k_reset_refine<<<1, 256, 0, s>>>(d.rmax, d.bmax, d.xmax, d.status, d.nx_total);
+  k_reset_refine<<<1, 256, 0, s>>>(d.rmax, d.bmax, d.xmax, d.status, 2 * d.nx_total);
 }
 
 void launch_adjoint_grads(const DevOps& d, double* grad_scal, double* grad_E, hipStream_t s) {

@@ -209,5 +209,33 @@ __device__ __forceinline__ double fold8(const double (&v)[8], int lane) {
   return c + __shfl_xor(c, 32);
 }
 
+// Stop test of the refinement: the largest normwise backward error of the points,
+//   eta_x = max|r_x| / (||M_x|| max|x_x| + max|b_x|),
+// with ||M_x|| <= 1 + dt (n0_x ||C|| + |E_x| ||A||) in the norm that matches
+// max-norms of the vectors (inf-norm for M, 1-norm for M^T).  The residual's own
+// FP64 rounding is of order sqrt(n) eps ||M|| |x|, so a bound relative to |b|
+// alone is unreachable once dt |E| ||A|| grows; eta is not.  On every thread of
+// the block.
+template <int NT>
+__device__ __forceinline__ double refine_worst(const RefineCheck& c) {
+  __shared__ double red[NT / 64];
+  double worst = 0.0;
+  for (int x = threadIdx.x; x < c.nx; x += NT) {
+    const double r = __longlong_as_double(static_cast<long long>(c.r[x]));
+    const double b = __longlong_as_double(static_cast<long long>(c.b[x]));
+    const double xm = __longlong_as_double(static_cast<long long>(c.x[x]));
+    const double mn = 1.0 + c.dt * (c.n0x[x] * c.cnorm + fabs(c.E[x]) * c.anorm);
+    const double den = mn * xm + b;
+    const double q = (den > 0.0) ? r / den : (r > 0.0 ? INFINITY : 0.0);
+    worst = fmax(worst, (q == q) ? q : INFINITY);
+  }
+  worst = wave_max(worst);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = worst;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) worst = fmax(worst, red[w]);
+  return worst;
+}
+
 }  // namespace
 }  // namespace bte
