@@ -374,7 +374,7 @@ void fill_devops(bte_handle* h) {
   d.lu = h->alloc<char>(nxt * d.npad * d.npad * elt);
   d.xscr = h->alloc<char>(nxt * d.npad * bte::kNB * elt);
   d.linv = h->alloc<char>(nxt * bte::kLinvElems * elt);
-  if (c.precision != BTE_FP64) d.tinv = h->alloc<float>(nxt * d.npad * bte::kNB);
+  if (c.precision != BTE_FP64) d.tinv = static_cast<float*>(d.xscr);
   if (c.precision == BTE_MIXED_FP32) {
     d.lmax = h->alloc<float>(nxt * d.npad);
     d.umax = h->alloc<float>(nxt * d.npad);
@@ -1459,7 +1459,7 @@ bte_status bte_set_vsolver(bte_handle* h, int32_t kind, int32_t n_bins, double E
     f.linv = h->kalloc<char>(static_cast<size_t>(nmat) * bte::kLinvElems * elt);
     f.piv = h->kalloc<int>(static_cast<size_t>(nmat) * d.npad);
     f.perm = h->kalloc<int>(static_cast<size_t>(nmat) * bte::kMaxPanels * bte::kPermStride);
-    f.tinv = lu_prec == BTE_FP64 ? nullptr : h->kalloc<float>(static_cast<size_t>(nmat) * d.npad * bte::kNB);
+    f.tinv = lu_prec == BTE_FP64 ? nullptr : static_cast<float*>(f.xscr);
     f.precision = lu_prec;
     f.update_kc = 0;
     f.form_xpb = 0;

@@ -70,7 +70,8 @@ struct DevOps {
   float* lmax = nullptr;       // [nx_total][npad] groups of four: max |L| of every row over the group's panels so far
   float* umax = nullptr;       // [nx_total][npad] and max |U| of every column (the split update's scales)
   float* tinv = nullptr;       // FP32 factors: [nx_total][npad / kNB][kNB][kNB] column-major inverses of every
-                               // diagonal block's triangles (U^-1 above, L^-1 strictly below the diagonal)
+                               // diagonal block's triangles (U^-1 above, L^-1 strictly below the diagonal), in
+                               // xscr's memory: written where and when the factorization no longer stages there
   int* piv = nullptr;          // [nx_total][npad]
   int* perm = nullptr;         // [nx_total][kMaxPanels][kPermStride] row permutation of every panel
   double* E = nullptr;         // [nx_total]

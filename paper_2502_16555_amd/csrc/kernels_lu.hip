@@ -527,7 +527,7 @@ struct DiagLds {
 };
 
 // X = U11^-1 and Y = L11^-1 of the factored block in s.xt (column-major): tinv
-// holds both triangles column-major (X on and above the diagonal, Y's strict
+// (may be NULL) holds both triangles column-major (X on and above the diagonal, Y's strict
 // lower part below it, its unit diagonal implied; for the solves); xo (may be
 // NULL) X row-major, yo (may be NULL) Y column-major.
 __device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, float* __restrict__ tinv,
@@ -631,7 +631,7 @@ __device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, 
   for (int u = 0; u < 8; ++u) {
     const int e = tid + kDiagThreads * u, k = e >> 5, i4 = (e & 31) * 4;
     const float4 v = *reinterpret_cast<const float4*>(&sXT[k][i4]);
-    *reinterpret_cast<float4*>(tinv + (size_t)k * NB + i4) = v;
+    if (tinv) *reinterpret_cast<float4*>(tinv + (size_t)k * NB + i4) = v;
     if (yo) {   // column-major: (i, k) at k NB + i
       const float w[4] = {v.x, v.y, v.z, v.w};
       float y[4];
@@ -844,13 +844,14 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_static(float* __restrict_
     pm[1 + kMaxSwapRows + tid] = k0 + tid;
     if (tid == 0) pm[0] = 0;   // no rows moved: the solves skip it
   }
-  diag_inverses(s_all, tinv + ((size_t)mat * (npad / NB) + k0 / NB) * NB * NB,
+  diag_inverses(s_all, tinv ? tinv + ((size_t)mat * (npad / NB) + k0 / NB) * NB * NB : nullptr,
                 linv + (size_t)mat * kLinvElems + kLinvXOff, linv + (size_t)mat * kLinvElems + 8 * 256);
   if (__syncthreads_or(nonfinite) && tid == 0) atomicOr(status, kStNonFinite);
 }
 
-// The triangles' inverses (diag_inverses) of every diagonal block of partially
-// pivoted FP32 factors, one block per panel and matrix, after the factorization.
+// The triangles' inverses (diag_inverses) of every diagonal block of FP32 factors
+// that did not leave them on the way, one block per panel and matrix, after the
+// factorization.
 __global__ __launch_bounds__(kDiagThreads) void k_diag_inv(const float* __restrict__ LU, float* __restrict__ tinv, int npad) {
   const int k0 = blockIdx.x * NB, mat = blockIdx.y, tid = threadIdx.x;
   const float* A = LU + (size_t)mat * npad * npad;
@@ -1955,10 +1956,13 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
     launch_update(kind, LU, d.npad, k0, mtr, mtc, 0, nmat, alt_kc, s, kd);
     if (tm) ++tm->launches;
   };
+  // the block inverses share xscr: static panels leave theirs on the way where
+  // nothing is staged there (partial pivoting and the panels of a pair stage)
+  const bool early = stat && (quads || !pairs || np < 3);
   // statically pivoted FP32 panels: the diagonal block and L21 (on stream st)
   auto static_panel = [&](int k0, int rend, hipStream_t st, float* lmax = nullptr, int first = 0) {
     if constexpr (std::is_same<T, float>::value) {
-      k_diag_static<<<nmat, kDiagThreads, 0, st>>>(LU, li, ti, piv, perm, d.status, d.npad, k0);
+      k_diag_static<<<nmat, kDiagThreads, 0, st>>>(LU, li, early ? ti : nullptr, piv, perm, d.status, d.npad, k0);
       const int nt = (rend - k0 - NB) / NB;   // row tiles of L21 (rend, k0 multiples of 128)
       if (nt > 0) k_l21_mfma<<<xcd_grid(nt, nmat), 256, 0, st>>>(LU, li, d.npad, k0, nt, nmat, lmax, first);
     }
@@ -2085,7 +2089,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
     }
   }
   if constexpr (std::is_same<T, float>::value) {
-    if (!stat) k_diag_inv<<<dim3(np, nmat), kDiagThreads, 0, s>>>(LU, ti, d.npad);
+    if (!early) k_diag_inv<<<dim3(np, nmat), kDiagThreads, 0, s>>>(LU, ti, d.npad);
   }
 }
 
