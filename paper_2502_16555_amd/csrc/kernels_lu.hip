@@ -13,10 +13,11 @@
 //   panel     partial pivoting (max |a|, ties to the lowest row), the panel's
 //             row permutation for the trailing columns, and the inverses of
 //             the 16 x 16 diagonal blocks of its unit lower block L11: FP64 by
-//             the kernels of kernels_panel.hip, FP32 by
+//             the kernels of kernels_panel.hip, FP32 and the tall FP64 panels
+//             of many matrices by
 //   k_panel   one 512-thread block per matrix (256 for short panels),
-//             register-resident sub-panels of 16 columns, left-looking across
-//             the sub-panels, and
+//             register-resident sub-panels of 8 or 16 columns, left-looking
+//             across the sub-panels, and
 //   k_dinv    (one block per matrix);
 //   k_l11inv  four blocks per matrix: L11^-1 by blocked substitution on the
 //             identity (16-row blocks, each two MFMA products);
@@ -145,21 +146,22 @@ __global__ __launch_bounds__(256) void k_form(T* __restrict__ LU, const double* 
 // from LDS), are factored in registers, and then only their U rows of the rest
 // of the panel are formed.  The tall part of the panel is read once per
 // sub-panel as L rather than read and written by a right-looking update, which
-// halves the traffic of a 2048-row panel (1.4x faster, with the same products
-// in the same order, hence the same bits).  FP32 factors only.
+// halves the traffic of a 2048-row panel (1.4x faster FP32, 1.6x FP64, with the
+// same products in the same order, hence the same bits).
 // ---------------------------------------------------------------------------
-template <int NT, int RPT, int IB, int CB>
-__global__ __launch_bounds__(NT) void k_panel(float* __restrict__ LU, int* __restrict__ piv,
+template <typename T, int NT, int RPT, int IB, int CB>
+__global__ __launch_bounds__(NT) void k_panel(T* __restrict__ LU, int* __restrict__ piv,
                                                          int* __restrict__ perm, int* __restrict__ status, int npad,
                                                          int k0, int rend) {
   // rows >= rend are zero in the panel columns (banded systems) and take no part
   static_assert(IB % CB == 0 || CB % IB == 0, "the L chunk and the sub-panel width must nest");
-  using T = float;
   constexpr int NW = NT / 64;
   const int mat = blockIdx.x;
   T* A = LU + (size_t)mat * npad * npad;
   int* ip = piv + (size_t)mat * npad;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  __shared__ double s_val[2][NW];
+  __shared__ int s_idx[2][NW];
   __shared__ unsigned long long s_key[2][NW];
   __shared__ T s_row[2][1][IB];
   __shared__ T s_cand[2][NW][IB];
@@ -230,24 +232,42 @@ __global__ __launch_bounds__(NT) void k_panel(float* __restrict__ LU, int* __res
 #pragma clang loop unroll(full)
     for (int j = 0; j < IB; ++j) {
       const int c = c0 + j;
+      double best = -1.0;
       int bi = INT_MAX;
-      // one 64-bit key per candidate, the bits of |a| (monotone for
+      // FP32: one 64-bit key per candidate, the bits of |a| (monotone for
       // non-negative floats) over ~row, so that a single maximum picks the
       // largest |a| and, among equal ones, the lowest row; 0 = no candidate
       // (NaN or outside the panel's rows)
       unsigned long long key = 0;
+      if constexpr (sizeof(T) == 4) {
 #pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int r = c0 + tid + q * NT;
-        const float av = fabsf(a[q][j]);
-        if (r >= c && r < rend && av == av) {
-          const unsigned long long k =
-              (static_cast<unsigned long long>(__float_as_uint(av)) << 32) | static_cast<unsigned>(~r);
-          key = k > key ? k : key;
+        for (int q = 0; q < RPT; ++q) {
+          const int r = c0 + tid + q * NT;
+          const float av = fabsf(a[q][j]);
+          if (r >= c && r < rend && av == av) {
+            const unsigned long long k =
+                (static_cast<unsigned long long>(__float_as_uint(av)) << 32) | static_cast<unsigned>(~r);
+            key = k > key ? k : key;
+          }
         }
+        key = wave_max_u64(key);
+        bi = key ? static_cast<int>(~static_cast<unsigned>(key)) : INT_MAX;
+      } else {
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+          const int r = c0 + tid + q * NT;
+          if (r >= c && r < rend) {
+            const double v = fabs(static_cast<double>(a[q][j]));
+            if (v > best) {
+              best = v;
+              bi = r;
+            }
+          }
+        }
+        const double wm = wave_max(best);
+        bi = wave_min(best == wm ? bi : INT_MAX);
+        best = wm;
       }
-      key = wave_max_u64(key);
-      bi = key ? static_cast<int>(~static_cast<unsigned>(key)) : INT_MAX;
       // One barrier per column: every wavefront publishes its partial maximum
       // together with the row it belongs to, thread j publishes row c; after the
       // barrier every thread reduces the partials to the same pivot p and finds
@@ -255,7 +275,14 @@ __global__ __launch_bounds__(NT) void k_panel(float* __restrict__ LU, int* __res
       // column parity: one is rewritten two columns later, when every thread has
       // passed the barrier of the column in between and finished reading it.
       const int par = j & 1;
-      if (lane == 0) s_key[par][wid] = key;
+      if (lane == 0) {
+        if constexpr (sizeof(T) == 4) {
+          s_key[par][wid] = key;
+        } else {
+          s_val[par][wid] = best;
+          s_idx[par][wid] = bi;
+        }
+      }
 #pragma unroll
       for (int q = 0; q < RPT; ++q) {
         if (c0 + tid + q * NT == bi) {
@@ -269,16 +296,30 @@ __global__ __launch_bounds__(NT) void k_panel(float* __restrict__ LU, int* __res
       }
       __syncthreads();
       int p = INT_MAX, pw = 0;
-      unsigned long long km = 0;
+      if constexpr (sizeof(T) == 4) {
+        unsigned long long km = 0;
 #pragma unroll
-      for (int u = 0; u < NW; ++u) {
-        const unsigned long long ok = s_key[par][u];
-        if (ok > km) {
-          km = ok;
-          pw = u;
+        for (int u = 0; u < NW; ++u) {
+          const unsigned long long ok = s_key[par][u];
+          if (ok > km) {
+            km = ok;
+            pw = u;
+          }
+        }
+        if (km) p = static_cast<int>(~static_cast<unsigned>(km));
+      } else {
+        double v = -1.0;
+#pragma unroll
+        for (int u = 0; u < NW; ++u) {
+          const double ov = s_val[par][u];
+          const int oi = s_idx[par][u];
+          if (ov > v || (ov == v && oi < p)) {
+            v = ov;
+            p = oi;
+            pw = u;
+          }
         }
       }
-      if (km) p = static_cast<int>(~static_cast<unsigned>(km));
       // a column of NaNs has no candidate: keep row c (every index stays in
       // range whatever the data) and report the non-finite value
       const T* prow = s_cand[par][pw];
@@ -948,8 +989,8 @@ __global__ __launch_bounds__(256, 2) void k_l21_mfma(float* __restrict__ LU, con
 // forward substitution in registers).  Output: the first 8 x 256 elements of
 // the matrix's kLinvElems slot, [b][r][c] row-major.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(128) void k_dinv(const float* __restrict__ LU, float* __restrict__ dinv, int npad, int k0) {
-  using T = float;
+template <typename T>
+__global__ __launch_bounds__(128) void k_dinv(const T* __restrict__ LU, T* __restrict__ dinv, int npad, int k0) {
   __shared__ T sD[8][16][17];
   const int mat = blockIdx.x, tid = threadIdx.x;
   const T* A = LU + (size_t)mat * npad * npad;
@@ -1937,20 +1978,35 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
   // K = 256 update, which reads and writes A22 half as often; the last two
   // panels go singly
   auto panel = [&](int k0, int rend) {
-    if constexpr (std::is_same<T, double>::value) {
-      launch_panel_f64(LU, li, xs, piv, perm, d.status, d.npad, k0, rend, nmat, s);
-    } else {
-      // block shape and L chunk by panel height (measured): short panels (the
-      // last ones) take four wavefronts, which have the larger register budget
-      const int rows = rend - k0;
-      constexpr int NT = kPanelThreads;  // 512 threads holding up to 4 rows each
-      if (rows <= NT / 2) k_panel<NT / 2, 1, 16, 8><<<nmat, NT / 2, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
-      else if (rows <= NT) k_panel<NT / 2, 2, 16, 8><<<nmat, NT / 2, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
-      else if (rows <= 2 * NT) k_panel<NT, 2, 16, 8><<<nmat, NT, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
-      else k_panel<NT, 4, 16, 8><<<nmat, NT, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
-      // (banded factors, whose rend is short of npad, are FP64)
-      if (k0 + NB < d.npad) k_dinv<<<nmat, 128, 0, s>>>(LU, li, d.npad, k0);
+    const int rows = rend - k0;
+    constexpr int NT = kPanelThreads;  // 512 threads holding up to 4 rows each
+    constexpr bool F64 = sizeof(T) == 8;
+    if constexpr (F64) {
+      // kernels_panel.hip, whose tall panels pass over memory once per 16 columns,
+      // in time with the rows of all matrices; with more of them the left-looking
+      // kernel, one pass per sub-panel, is the faster: from about 1800 rows at 128
+      // matrices (690 us each; 2048 rows 751 against 700), 900 at 192 (452 and 453;
+      // 2048 rows 1017 against 853), 450 at 256 (512 rows 378 against 361, 384 rows
+      // 322 against 335; 2048 rows 1357 against 1007), never at 64 (486 against 655)
+      if (rows <= 2 * NB || static_cast<double>(nmat) * nmat * rows <= 3.0e7) {
+        launch_panel_f64(LU, li, xs, piv, perm, d.status, d.npad, k0, rend, nmat, s);
+        return;
+      }
     }
+    // block shape and L chunk by panel height (measured): short panels take four
+    // wavefronts, which have the larger register budget
+    if (rows <= NT / 2) {
+      if constexpr (!F64)
+        k_panel<T, NT / 2, 1, 16, 8><<<nmat, NT / 2, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
+    } else if (rows <= NT) {
+      k_panel<T, NT / 2, 2, 16, 8><<<nmat, NT / 2, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
+    } else if (rows <= 2 * NT) {
+      k_panel<T, NT, 2, 16, F64 ? 4 : 8><<<nmat, NT, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
+    } else {
+      // (FP64: 8-column sub-panels, where 16 columns of four rows would spill)
+      k_panel<T, NT, 4, F64 ? 8 : 16, F64 ? 4 : 8><<<nmat, NT, 0, s>>>(LU, piv, perm, d.status, d.npad, k0, rend);
+    }
+    if (k0 + NB < d.npad) k_dinv<T><<<nmat, 128, 0, s>>>(LU, li, d.npad, k0);
   };
   auto update = [&](int k0, int mtr, int mtc, int kd) {
     launch_update(kind, LU, d.npad, k0, mtr, mtc, 0, nmat, alt_kc, s, kd);

@@ -879,6 +879,26 @@ def test_fp64_panels_of_every_height_match_restatement(torch, nr, nth):
     s.close()
 
 
+@pytest.mark.parametrize("nx,nr,nth", [(256, 40, 16), (170, 48, 24)])
+def test_fp64_panels_of_many_matrices_match_restatement(torch, nx, nr, nth):
+    """FP64 panels of batches large enough for the left-looking kernel (256 matrices: 640 and 512
+    rows, then the others; 170: 1152 rows, then the others): as the test above."""
+    import lu_reference as LR
+    cfg = workloads.small_config(nx=nx, nr=nr, nth=nth, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf", dt_frac=0.05)
+    ops = oracle.build_operators(cfg)
+    s = solver(cfg, precision="fp64")
+    E = np.linspace(-1.2e4, 1.2e4, nx)
+    Eg = cuda(torch, E)
+    for x in (0, nx - 1):
+        lu, piv = s.factor_export(Eg, x)
+        ref, ip = LR.factor(LR.pad(S.v_matrix(ops, E[x])), 16, pairs=True)
+        assert (ip != np.arange(len(ip))).sum() > len(ip) // 10
+        assert np.array_equal(piv, ip), x
+        close(lu, ref, 1e-12, (x, "factors"))
+    s.close()
+
+
 @pytest.mark.parametrize("nr,nth,form", [
     (nr, nth, form) for nr, nth in [(10, 6), (24, 10), (40, 16), (48, 24)]
     for form in ["fp64", "static_fp32", "pivoted_fp32", "fp16_bins"]
