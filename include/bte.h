@@ -421,8 +421,8 @@ bte_status bte_get_timing(bte_handle* h, double* ms_out);
  *     group's earlier panels' updates at depth 128 j, in place and in one
  *     launch, the columns beyond the group one update of depth 512; a last
  *     group that does not fit goes singly); other factors take pairs.  Measured
- *     at Nx = 256, n = 2048: 17.8 ms per FP32 step against 18.5 with pairs
- *     (BF16x3 14.45 against 15.15).  0: single panels.  Unlike the other keys this one changes the
+ *     at Nx = 256, n = 2048: 13.5 ms per FP32 step against 18.8 with pairs
+ *     (BF16x3 12.8 against 13.9).  0: single panels.  Unlike the other keys this one changes the
  *     rounding of the trailing updates (not the pivots of a well-separated
  *     column); it only takes effect at the next factorization.
  *   BTE_TUNE_STATIC_PIVOTING: 0 or 1 (default 1 for the mixed precisions, 0 for
@@ -440,10 +440,8 @@ bte_status bte_get_timing(bte_handle* h, double* ms_out);
  *     panel updates that panel's columns first; the panel's diagonal-block
  *     factorization and L21 then run on a side stream (default priority)
  *     during the rest of the update.  Same arithmetic in the same order: the
- *     results do not depend on it.  Measured at Nx = 256, n = 2048: 0.3 ms
- *     slower per FP32 step (the update fills every CU's registers, so the
- *     side kernels wait for its blocks to drain), 0.1 ms faster with the
- *     split-bf16 update; the autotuner tries both.
+ *     results do not depend on it.  Panels in groups of four (the default)
+ *     do not take it; the autotuner tries both.
  *   BTE_TUNE_FORM_OVERLAP: 0 (default) or 1.  With statically pivoted FP32
  *     factors, panels in pairs, dense systems and one factorization group, the
  *     matrices' columns and rows below 256 are formed first, and the rest of
