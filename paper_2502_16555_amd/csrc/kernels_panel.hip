@@ -18,6 +18,8 @@
 //                 blocks per matrix.
 // All of them also write the inverses of L11's 16 x 16 diagonal blocks, which
 // the formation of L11^-1 starts from.
+// (The tall panels of many matrices, which these passes over memory would bind,
+// go to the left-looking kernel: the rule is at the factorization's dispatch.)
 // Measured per panel, 64 matrices, against the former kernel (one block per
 // matrix, 8 or 16 columns in registers, the rest of the panel re-read from
 // memory between them; it did not get faster with fewer rows): 128 rows 72 us
