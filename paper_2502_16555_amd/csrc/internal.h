@@ -89,7 +89,7 @@ struct DevOps {
   // bounds of the operator norms for the refinement stop: inf-norm (row sums)
   // and 1-norm (column sums) of C_ord and A_ord
   double c_inf = 0.0, a_inf = 0.0, c_one = 0.0, a_one = 0.0;
-  int* status = nullptr;       // [4]: status bits, done flag, sweeps, spare
+  int* status = nullptr;       // [4]: status bits, done flag of the even sweeps, sweeps, done flag of the odd sweeps
   double* resid = nullptr;     // [1] final max_x |r|/|b|
   double* scratch3 = nullptr;  // [3*nx_total] moments scratch
   // heavies' update of the hybrid model (Poisson field mode only)
@@ -254,16 +254,24 @@ void launch_update(int kind, void* LU, int npad, int k0, int mtr, int mtc, int t
                    hipStream_t s, int kd = kNB, int lrow = 0, const float* rmax = nullptr,
                    const float* cmax = nullptr);
 // The stop test of a refinement sweep on the maxima of its residual (slot: the
-// sweep's parity); the solve that follows takes the test itself.
+// sweep's parity); the solve that follows takes the test itself.  Every block of
+// that solve takes it, so no block may read a word that another one of the launch
+// writes: the done flag has a slot per sweep parity too, which the sweep's own
+// solve writes, and that solve, like the sweep's residual, reads the slot of the
+// sweep before (cleared for sweep 0 by launch_reset_refine).
 struct RefineCheck {
   unsigned long long *r = nullptr, *b = nullptr, *x = nullptr;      // the sweep's maxima (r NULL: no test)
   unsigned long long *r1 = nullptr, *b1 = nullptr, *x1 = nullptr;   // the next sweep's, to be cleared
   const double *E = nullptr, *n0x = nullptr;
   double dt = 0.0, cnorm = 0.0, anorm = 0.0, rtol = 0.0;
+  const int* done = nullptr;    // the refinement ended at an earlier sweep
+  int* done1 = nullptr;         // ended at this sweep or earlier
   int* status = nullptr;
   double* resid = nullptr;
   int sweep = 0, nx = 0;
 };
+// Place in DevOps::status of the done flag that a sweep's test writes.
+constexpr int done_slot(int sweep) { return (sweep & 1) ? 3 : 1; }
 inline RefineCheck refine_check(const DevOps& d, bool transpose, double rtol, int sweep) {
   RefineCheck c;
   const size_t o = (sweep & 1) ? d.nx_total : 0, o1 = d.nx_total - o;
@@ -271,6 +279,7 @@ inline RefineCheck refine_check(const DevOps& d, bool transpose, double rtol, in
   c.r1 = d.rmax + o1, c.b1 = d.bmax + o1, c.x1 = d.xmax + o1;
   c.E = d.E, c.n0x = d.n0x;
   c.dt = d.dt, c.cnorm = transpose ? d.c_one : d.c_inf, c.anorm = transpose ? d.a_one : d.a_inf, c.rtol = rtol;
+  c.done = d.status + done_slot(sweep + 1), c.done1 = d.status + done_slot(sweep);
   c.status = d.status, c.resid = d.resid;
   c.sweep = sweep, c.nx = d.nx_total;
   return c;

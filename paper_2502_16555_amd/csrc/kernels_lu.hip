@@ -1599,17 +1599,21 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
                                                 const int* __restrict__ mirror, int n, int nth) {
   if constexpr (sizeof(T) == 4) {
     if (check.r) {   // a refinement sweep: its stop test first, in every block alike
-      if (check.status[1]) return;
-      const double worst = refine_worst<1024>(check);
+      const bool ended = *check.done != 0;   // (written by the launches before this one only)
+      const double worst = ended ? 0.0 : refine_worst<1024>(check);
+      const bool stop = ended || worst <= check.rtol;
       if (blockIdx.x == 0) {
         if (threadIdx.x == 0) {
-          check.resid[0] = worst;
-          check.status[2] = check.sweep;
-          if (worst <= check.rtol) check.status[1] = 1;
+          if (!ended) {
+            check.resid[0] = worst;
+            check.status[2] = check.sweep;
+          }
+          *check.done1 = stop;
         }
-        for (int x = threadIdx.x; x < check.nx; x += 1024) check.r1[x] = check.b1[x] = check.x1[x] = 0ull;
+        if (!stop)
+          for (int x = threadIdx.x; x < check.nx; x += 1024) check.r1[x] = check.b1[x] = check.x1[x] = 0ull;
       }
-      if (worst <= check.rtol) return;
+      if (stop) return;
     }
   }
   // right-hand side / solution row: the block; factors: that row's own matrix,

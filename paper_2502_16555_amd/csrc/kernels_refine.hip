@@ -103,9 +103,9 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
                                                       unsigned long long* __restrict__ rmax,
                                                       unsigned long long* __restrict__ bmax,
                                                       unsigned long long* __restrict__ xmax,
-                                                      const int* __restrict__ status, double dt, int n, int ld,
+                                                      const int* __restrict__ done, double dt, int n, int ld,
                                                       int nx, const int* __restrict__ skip) {
-  if (MODE == 0 && status[1]) return;
+  if (MODE == 0 && *done) return;   // (no launch that may run beside this one writes it)
   constexpr int BM = 16 * PT, BN = 16 * OT;
   constexpr int NOP = MODE == 3 ? 1 : 2;         // operators: A, then C
   int bx, by;
@@ -173,13 +173,14 @@ __global__ __launch_bounds__(NW * 64) void k_residual(const double* __restrict__
 
 template <int TRANSPOSE, int MODE>
 void run_residual(const DevOps& d, const double* B, const double* X, double* R, const double* E, const int* skip,
-                  int ld, hipStream_t s, int slot = 0) {
+                  int ld, hipStream_t s, int sweep = 0) {
   auto go = [&](auto pt, auto ot, auto nw) {
     constexpr int PT = decltype(pt)::value, OT = decltype(ot)::value, NW = decltype(nw)::value;
     const int grid = xcd_grid((d.nx_total + 16 * PT - 1) / (16 * PT), (d.n + 16 * OT - 1) / (16 * OT));
-    const size_t o = (size_t)slot * d.nx_total;
+    const size_t o = (size_t)(sweep & 1) * d.nx_total;
+    const int* done = d.status + done_slot(sweep + 1);   // of the sweep before
     k_residual<TRANSPOSE, MODE, PT, OT, NW><<<grid, NW * 64, 0, s>>>(B, X, R, d.Cord, d.Aord, E, d.n0x,
-                                                                    d.rmax + o, d.bmax + o, d.xmax + o, d.status, d.dt,
+                                                                    d.rmax + o, d.bmax + o, d.xmax + o, done, d.dt,
                                                                     d.n, ld, d.nx_total,
                                                                     skip);
   };
@@ -191,17 +192,15 @@ void run_residual(const DevOps& d, const double* B, const double* X, double* R, 
     go(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, 8>());
 }
 
-// The test after the last sweep: status[1] = done flag, status[2] = sweeps used,
-// resid[0] = max_x eta_x (the sweeps before are tested by the solves, which set
-// the same).
+// The test after the last sweep: status[2] = sweeps used, resid[0] = max_x eta_x
+// (the sweeps before are tested by the solves, which set the same).
 __global__ __launch_bounds__(256) void k_refine_check(RefineCheck c) {
-  if (c.status[1]) return;
+  if (*c.done) return;
   const double worst = refine_worst<256>(c);
   if (threadIdx.x == 0) {
     c.resid[0] = worst;
     c.status[2] = c.sweep;
-    if (worst <= c.rtol) c.status[1] = 1;
-    else atomicOr(c.status, kStNoConv);
+    if (!(worst <= c.rtol)) atomicOr(c.status, kStNoConv);
   }
 }
 
@@ -213,7 +212,7 @@ __global__ void k_reset_refine(unsigned long long* rmax, unsigned long long* bma
     xmax[x] = 0ull;
   }
   if (threadIdx.x == 0) {
-    status[1] = 0;
+    status[done_slot(0)] = status[done_slot(1)] = 0;
     status[2] = 0;
   }
 }
@@ -326,8 +325,8 @@ void launch_apply_field(const DevOps& d, int mode, const double* B, const double
 }
 
 void launch_residual(const DevOps& d, bool transpose, int sweep, hipStream_t s) {
-  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s, sweep & 1);
-  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s, sweep & 1);
+  if (transpose) run_residual<1, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s, sweep);
+  else run_residual<0, 0>(d, d.B, d.X, d.R, d.E, nullptr, d.npad, s, sweep);
 }
 
 namespace {

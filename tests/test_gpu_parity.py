@@ -823,6 +823,37 @@ def test_refinement_nonconvergence_is_latched_and_the_handle_recovers(torch):
     s.close()
 
 
+@pytest.mark.parametrize("static", [1, 0])
+def test_refinement_of_more_points_than_run_at_once(torch, static):
+    """V steps of 1600 points (a refinement solve holds about 512 blocks on the card at a time, so
+    that later ones start while the first take the sweep's stop test): every row against the
+    oracle, and the same bits from each of four steps.  Tolerance: refinement stops at 1e-14 of
+    the right-hand side on matrices of small condition number."""
+    from paper_2502_16555_amd import _lib
+    nx_per = (700, 500, 400)
+    cfg, members = _ensemble_case(nx_per)
+    s = solver(cfg, precision="mixed_fp32")
+    s.set_tuning(_lib.TUNE_STATIC_PIVOTING, static)
+    rng = np.random.default_rng(17)
+    F = rng.standard_normal((sum(nx_per), 10, 6)) * 1e3
+    E = rng.uniform(-1.2e4, 1.2e4, sum(nx_per))
+    runs = []
+    for _ in range(4):
+        Fg = cuda(torch, F)
+        s.vstep(Fg, cuda(torch, E))
+        code, sweeps, resid = s.status()
+        assert code == 0 and sweeps >= 1 and resid <= 1e-14, (code, sweeps, resid)
+        runs.append(Fg.cpu().numpy())
+    s.close()
+    assert all(np.array_equal(r, runs[0]) for r in runs)
+    x0 = 0
+    for m, nx in zip(members, nx_per):
+        ops = oracle.build_operators(dict(m, nx=5, nx_per=[5]))   # (the V systems do not depend on the grid)
+        for x in range(x0, x0 + nx):
+            close(runs[0][x].ravel(), np.linalg.solve(S.v_matrix(ops, E[x]), F[x].ravel()), 1e-10, x)
+        x0 += nx
+
+
 @pytest.mark.parametrize("prec", ["fp64", "mixed_fp32", "mixed_bf16x3", "mixed_bf16"])
 def test_device_factors_match_blocked_restatement(torch, prec):
     """Device LU factors and pivots against the NumPy restatement of the same blocked
