@@ -118,7 +118,9 @@ __global__ __launch_bounds__(512) void k_panel_reg(double* __restrict__ LU, doub
     } else if constexpr (NF > 1) {
       for (int j = 0; j < SW; ++j) lds_barrier();   // the steps' barriers
     }
-    lds_barrier();
+    // (the first group's U rows go to the matrix where other wavefronts' first loads come from)
+    if (sp == 0) loads_barrier();
+    else lds_barrier();
     // final values of the group's columns; L21 operands, zero for retired rows;
     // the new pivot rows' entries to the right
     double av[RT][4];
@@ -269,6 +271,7 @@ __global__ __launch_bounds__(64 * NW) void k_panel_tall(double* __restrict__ LU,
   if (tid == 0) s_cnt = SW;
   if (tid < SW * SW) sX[tid / SW][NB - SW + tid % SW] = tid / SW == tid % SW ? 1.0 : 0.0;
   pivot_steps<RPT, NW>(x, c0, &s, s_piv, singular, nonfinite);
+  loads_barrier();   // the rows and ro go out below at positions that other wavefronts hold
   const bool last = c0 + SW == NB;
   int* pm = perm + ((size_t)mat * kMaxPanels + k0 / NB) * kPermStride;
 #pragma unroll

@@ -92,6 +92,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Barrier past which every global load that the block issued before it has its
+// value: for stores to locations that other wavefronts have read (lds_barrier
+// orders no global access, and a load may still be on its way behind it).
+__device__ __forceinline__ void loads_barrier() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt 0, the other counters free
+  __syncthreads();
+}
+
 // Wavefront reductions through DPP lane permutations (quad swaps, half-row and
 // row mirrors) inside each row of 16 lanes, then the four row results by lane
 // reads: no LDS round trip on the pivot search's critical path.
