@@ -1991,8 +1991,10 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
       // kernel, one pass per sub-panel, is the faster: from about 1800 rows at 128
       // matrices (690 us each; 2048 rows 751 against 700), 900 at 192 (452 and 453;
       // 2048 rows 1017 against 853), 450 at 256 (512 rows 378 against 361, 384 rows
-      // 322 against 335; 2048 rows 1357 against 1007), never at 64 (486 against 655)
-      if (rows <= 2 * NB || static_cast<double>(nmat) * nmat * rows <= 3.0e7) {
+      // 322 against 335; 2048 rows 1357 against 1007), never at 64 (486 against 655).
+      // All the handle's matrices count, whatever group of them this call factors,
+      // so that the factors do not depend on the grouping.
+      if (rows <= 2 * NB || static_cast<double>(d.nx_total) * d.nx_total * rows <= 3.0e7) {
         launch_panel_f64(LU, li, xs, piv, perm, d.status, d.npad, k0, rend, nmat, s);
         return;
       }

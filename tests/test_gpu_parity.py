@@ -930,6 +930,26 @@ def test_fp64_panels_of_many_matrices_match_restatement(torch, nx, nr, nth):
     s.close()
 
 
+def test_fp64_groups_keep_the_panel_kernels_of_the_whole_batch(torch):
+    """FP64 factors of 170 matrices of 1152 rows, whose tall panels go to the left-looking kernel,
+    in one group and in two or three, which alone would not: the same bits."""
+    from paper_2502_16555_amd import _lib
+    cfg = workloads.small_config(nx=170, nr=48, nth=24, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf", dt_frac=0.05)
+    s = solver(cfg, precision="fp64")
+    F = np.random.default_rng(8).standard_normal((170, 48, 24)) * 1e3
+    E = cuda(torch, np.linspace(-1.2e4, 1.2e4, 170))
+    out = []
+    for g in (1, 2, 3):
+        s.set_tuning(_lib.TUNE_LU_STREAMS, g)
+        Fg = cuda(torch, F)
+        s.vstep(Fg, E)
+        assert s.status()[0] == 0
+        out.append(Fg.cpu().numpy())
+    s.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
 @pytest.mark.parametrize("nr,nth,form", [
     (nr, nth, form) for nr, nth in [(10, 6), (24, 10), (40, 16), (48, 24)]
     for form in ["fp64", "static_fp32", "pivoted_fp32", "fp16_bins"]
