@@ -1992,9 +1992,13 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
       // matrices (690 us each; 2048 rows 751 against 700), 900 at 192 (452 and 453;
       // 2048 rows 1017 against 853), 450 at 256 (512 rows 378 against 361, 384 rows
       // 322 against 335; 2048 rows 1357 against 1007), never at 64 (486 against 655).
-      // All the handle's matrices count, whatever group of them this call factors,
-      // so that the factors do not depend on the grouping.
-      if (rows <= 2 * NB || static_cast<double>(d.nx_total) * d.nx_total * rows <= 3.0e7) {
+      // Beyond 256 matrices the line stays there: both kernels' times grow with their
+      // number (V steps of n = 384, whose one tall panel has 384 rows: 384 matrices
+      // 1.53 ms against 1.75, 512 1.73 against 1.90, 1024 3.44 against 3.75; n = 640
+      // 5.25 against 5.35 and 10.40 against 10.53; n = 1024 15.4 against 14.3 and 30.4
+      // against 28.4).  All the handle's matrices count, whatever group of them this
+      // call factors, so that the factors do not depend on the grouping.
+      if (rows <= 3 * NB || static_cast<double>(d.nx_total) * d.nx_total * rows <= 3.0e7) {
         launch_panel_f64(LU, li, xs, piv, perm, d.status, d.npad, k0, rend, nmat, s);
         return;
       }

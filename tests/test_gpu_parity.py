@@ -930,6 +930,25 @@ def test_fp64_panels_of_many_matrices_match_restatement(torch, nx, nr, nth):
     s.close()
 
 
+def test_fp64_panels_of_three_tiles_in_a_large_batch_match_restatement(torch):
+    """FP64 factors of 400 matrices of 384 rows (the tallest panel that a batch of any size leaves
+    to the tall-panel kernel): as the test above."""
+    import lu_reference as LR
+    cfg = workloads.small_config(nx=50, nr=24, nth=16, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf", dt_frac=0.05)
+    ops = oracle.build_operators(cfg)
+    s = solver(dict(cfg, n_discharges=8, nx_per=[50] * 8, n0_per=[cfg["n0_m3"]] * 8, E0_per=[1.2e4] * 8),
+               precision="fp64")
+    E = np.linspace(-1.2e4, 1.2e4, 400)
+    Eg = cuda(torch, E)
+    for x in (0, 137, 399):
+        lu, piv = s.factor_export(Eg, x)
+        ref, ip = LR.factor(LR.pad(S.v_matrix(ops, E[x])), 16, pairs=True)
+        assert np.array_equal(piv, ip), x
+        close(lu, ref, 1e-12, (x, "factors"))
+    s.close()
+
+
 def test_fp64_groups_keep_the_panel_kernels_of_the_whole_batch(torch):
     """FP64 factors of 170 matrices of 1152 rows, whose tall panels go to the left-looking kernel,
     in one group and in two or three, which alone would not: the same bits."""
