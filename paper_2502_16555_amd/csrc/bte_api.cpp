@@ -475,18 +475,18 @@ void v_solve_krylov(bte_handle* h, double* F, hipStream_t s) {
   bte::launch_pad_rows(d, F, d.B, s);
   bte::launch_bin_map(d, q, s);
   // initial guess x0 = H b
-  bte::launch_lu_solve_mapped(h->kf, h->krylov_prec, false, q.mat_of, nullptr, nxt, d.B, d.X, false, {}, s);
+  bte::launch_lu_solve_mapped(h->kf, h->krylov_prec, q.mat_of, nullptr, nxt, d.B, d.X, false, s);
   for (int cyc = 0; cyc < h->krylov_cycles; ++cyc) {
     bte::launch_apply(d, 1, d.B, d.X, q.R, cyc == 0 ? nullptr : q.conv, s);   // R = B - M X
     bte::launch_gmres_init(d, q, cyc == 0, s);
     for (int j = 0; j < q.m; ++j) {
-      bte::launch_lu_solve_mapped(h->kf, h->krylov_prec, false, q.mat_of, q.conv, nxt, q.V + j * vs, q.Z, false,
-                                  {}, s);                      // z = H v_j
+      bte::launch_lu_solve_mapped(h->kf, h->krylov_prec, q.mat_of, q.conv, nxt, q.V + j * vs, q.Z, false,
+                                  s);                          // z = H v_j
       bte::launch_apply(d, 2, nullptr, q.Z, q.W, q.conv, s);     // w = M z
       bte::launch_gmres_arnoldi(d, q, j, s);
     }
     bte::launch_gmres_combine(d, q, s);                          // Z = V y
-    bte::launch_lu_solve_mapped(h->kf, h->krylov_prec, false, q.mat_of, q.inact, nxt, q.Z, d.X, true, {}, s);
+    bte::launch_lu_solve_mapped(h->kf, h->krylov_prec, q.mat_of, q.inact, nxt, q.Z, d.X, true, s);
   }
   bte::launch_gmres_status(d, q, s);
   bte::launch_unpad_rows(d, d.X, F, s);
@@ -501,7 +501,7 @@ void v_solve_banded(bte_handle* h, double* F, hipStream_t s) {
   const int nl = h->cfg.nl;
   bte::launch_to_harm(d, nl, b.npad, F, h->d_TS, d.B, s);
   bte::launch_lu_factor(b, 0, s, h->timing == 1 ? &h->lu_timer[0] : nullptr);
-  bte::launch_lu_solve_mapped(b, 0, false, nullptr, nullptr, d.nx_total, d.B, d.X, false, {}, s);
+  bte::launch_lu_solve(b, 0, false, d.B, d.X, false, {}, s);
   bte::launch_from_harm(d, nl, b.npad, d.X, d.B, h->d_TO, F, s);
 }
 
@@ -561,7 +561,7 @@ void v_solve_again(bte_handle* h, const double* in, double* out, bool transpose,
   DevOps& d = h->d;
   const int prec = h->cfg.precision;
   bte::launch_pad_rows(d, in, d.B, s);
-  bte::launch_lu_solve(d, prec, transpose, d.B, d.X, false, {}, s);
+  bte::launch_lu_solve(d, prec, transpose, d.B, d.X, false, {}, s, !refine);
   if (prec != BTE_FP64 && refine) {
     bte::launch_reset_refine(d, s);
     for (int it = 1; it <= h->refine_max_iter; ++it) {

@@ -286,15 +286,15 @@ inline RefineCheck refine_check(const DevOps& d, bool transpose, double rtol, in
 }
 // X = LU^-1 B (or LU^-T B with transpose), rows of length npad, FP64 right-hand sides.
 // With a check (check.r; mixed precisions): nothing if the refinement is done or the
-// test ends it, else also clears the next sweep's maxima.
+// test ends it, else also clears the next sweep's maxima.  precond: X only
+// preconditions (FP32 factors: accurate to the diagonal blocks' FP32 inverses).
 void launch_lu_solve(const DevOps& d, int precision, bool transpose, const double* Bin, double* Xout,
-                     bool accumulate, const RefineCheck& check, hipStream_t s);
-// As launch_lu_solve for nrows right-hand sides, row r solved with the factors
-// of matrix mat_of[r] of f (mat_of NULL: matrix r); rows with skip[r] != 0 are
-// left untouched (skip may be NULL).
-void launch_lu_solve_mapped(const DevOps& f, int precision, bool transpose, const int* mat_of, const int* skip,
-                            int nrows, const double* Bin, double* Xout, bool accumulate, const RefineCheck& check,
-                            hipStream_t s);
+                     bool accumulate, const RefineCheck& check, hipStream_t s, bool precond = false);
+// A preconditioner's solve for nrows right-hand sides, row r with the factors of
+// matrix mat_of[r] of f (mat_of NULL: matrix r); rows with skip[r] != 0 are left
+// untouched (skip may be NULL).
+void launch_lu_solve_mapped(const DevOps& f, int precision, const int* mat_of, const int* skip, int nrows,
+                            const double* Bin, double* Xout, bool accumulate, hipStream_t s);
 // FP32 -> FP16 copy of n elements (factor storage for preconditioning solves).
 void launch_to_half(const float* src, void* dst, size_t n, hipStream_t s);
 // Ordinate -> harmonic coefficients (P_S, l-major, rows of npad_h, l < nl) and

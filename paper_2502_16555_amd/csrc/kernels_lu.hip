@@ -1570,9 +1570,15 @@ __device__ __attribute__((always_inline)) inline void diag_chain(const double (*
 // right-hand side.
 // transpose = 0: x = U^-1 L_m^-1 P_m ... L_1^-1 P_1 b
 // transpose = 1: y = P_1^T L_1^-T ... P_m^T L_m^-T U^-T c
-// Diagonal blocks: FP32 and FP16 factors are refined or precondition, and take
-// the inverses of the block's triangles (tinv: one 128 x 128 product per block,
-// 0.3 us, in place of a chain of 128 steps, 2.2 us); FP64 factors solve with the
+// Diagonal blocks: FP32 and FP16 factors take the FP32 inverses X of the block's
+// triangles (tinv: a 128 x 128 product, 0.3 us, in place of a chain of 128 steps,
+// 2.2 us).  X's own error grows with the block's condition number, where a
+// substitution's does not, so FP32 factors correct the product with the block's
+// triangle D itself, x = X b, x += X (b - D x), in FP64 sums: what is left of
+// X's error is its square.  (Without the correction a refinement took a second
+// or third sweep where the substitution took one or two, and six in place of two at
+// a thousand times the usual step; with it the counts are the substitution's.)
+// FP16 factors only precondition, and do without.  FP64 factors solve with the
 // block itself, staged in LDS, on one wavefront.
 // Off-diagonal strips are applied column-oriented: a thread takes a 16-byte
 // vector of consecutive rows; short strips split the 128 columns over up to 16
@@ -1586,11 +1592,13 @@ __device__ __attribute__((always_inline)) inline void diag_chain(const double (*
 // Bound by what one CU draws: about 38 GB/s, whatever the loads in flight (8 or
 // 16 columns, waited for together or one by one: its vector cache holds 32 KB of
 // outstanding lines, over a latency of 0.85 us), until 256 CUs reach HBM's rate.
-// Per solve: 100 points, n = 1024, FP32 183 -> 113 us; 256 points, n = 2048, FP32 718 ->
-// 690 (6.2 TB/s); 64 points, n = 2048, FP64 990 -> 857; its band form,
-// half-bandwidth 127, 663 -> 351; FP64 transposed, 128 points, n = 512: 202 -> 105.
+// Per solve, against a chain per diagonal block and whole strips: 100 points, n =
+// 1024, FP32 183 -> 137 us (113 uncorrected: the block's own 64 KB cost 14 us, the two
+// products 10); 256 points, n = 2048, FP32 718 -> 740 (690 uncorrected); 64 points,
+// n = 2048, FP64 990 -> 857; its band form, half-bandwidth 127, 663 -> 351; FP64
+// transposed, 128 points, n = 512: 202 -> 105.
 // ---------------------------------------------------------------------------
-template <typename T, int TRANSPOSE>
+template <typename T, int TRANSPOSE, bool CORR>
 __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const float* __restrict__ tinv,
                                                 const int* __restrict__ perm, const double* __restrict__ Bin,
                                                 double* __restrict__ Xout,
@@ -1628,12 +1636,18 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
   __shared__ double sb[kMaxRows];
   __shared__ double s_rc[F64 ? NB : 1];
   __shared__ int s_nr[kMaxPanels];
-  // the staged diagonal block (FP64; FP32 transposed), or the strips' and blocks' partial sums
+  static_assert(!CORR || sizeof(T) == 4, "the corrected product is the FP32 factors'");
+  __shared__ double s_v[CORR ? 2 : 1][CORR ? NB : 1];   // the solution so far, its residual
+  // the staged diagonal block (FP64; transposed: the inverse and, CORR, the block's
+  // columns), and the strips' and blocks' partial sums, which FP64 factors lay over
+  // the block
   constexpr int STAGE = (F64 || TRANSPOSE) ? NB * (NB + 1) * static_cast<int>(sizeof(D)) : 0;
-  constexpr int PART = 1024 * PER * 8;
-  __shared__ __align__(16) unsigned char smem[STAGE > PART ? STAGE : PART];
+  constexpr int STAGE2 = TRANSPOSE && CORR ? STAGE : 0;
+  constexpr int PART = TRANSPOSE && !F64 ? 8 * NB * 8 : 1024 * PER * 8;
+  __shared__ __align__(16) unsigned char smem[F64 ? (STAGE > PART ? STAGE : PART) : STAGE + STAGE2 + PART];
   D (*sD)[NB + 1] = reinterpret_cast<D (*)[NB + 1]>(smem);
-  double* s_part = reinterpret_cast<double*>(smem);
+  D (*sE)[NB + 1] = reinterpret_cast<D (*)[NB + 1]>(smem + STAGE);
+  double* s_part = reinterpret_cast<double*>(smem + (F64 ? 0 : STAGE + STAGE2));
   const int mat = mat_of ? mat_of[row] : row;
   const T* A = LU + (size_t)mat * npad * npad;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -1714,19 +1728,37 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
     }
     lds_barrier();
   };
-  // diagonal block of panel q: FP64 the factors' own, else the inverses of its
-  // triangles; thread t holds row t mod 128 of the columns t / 128 + 8 u
+  // diagonal block of panel q: FP64 the factors' own, thread t holding row t mod 128
+  // of the columns t / 128 + 8 u; else the inverses of its triangles (dv) and, CORR,
+  // the block (ev), a wavefront holding 16 consecutive columns of half of the rows.
+  // lo, up: the triangles that are wanted; a wavefront with none of their entries
+  // loads none (the halves are dealt so that every SIMD has as many of those)
   constexpr int NS = NB * NB / 1024;
+  constexpr bool EV = CORR && !TRANSPOSE;
   D dv[NS];
-  const unsigned dr = tid % NB;
-  const int dc = __builtin_amdgcn_readfirstlane(tid / NB);
-  auto load_diag = [&](int q) {
+  float ev[EV ? NS : 1];
+  const int dh = F64 ? __builtin_amdgcn_readfirstlane((tid >> 6) & 1) : __builtin_amdgcn_readfirstlane(tid >> 9);
+  const int dc = F64 ? __builtin_amdgcn_readfirstlane(tid / NB) : __builtin_amdgcn_readfirstlane((tid >> 6) & 7);
+  const unsigned dr = 64 * dh + lane;
+  constexpr int CS = F64 ? 8 : 1;          // columns c0d, c0d + CS, ...
+  const int c0d = F64 ? dc : NS * dc;
+  const bool no_lo = dh == 0 && dc >= 4, no_up = dh == 1 && dc < 4;   // (not FP64)
+  auto load_diag = [&](int q, bool lo, bool up) {
+    if constexpr (!F64 && !TRANSPOSE) {
+      if (!((lo & !no_lo) | (up & !no_up))) return;
+    }
+    const T* block = A + (size_t)(q * NB + c0d) * npad + q * NB;
     const D* first;
-    if constexpr (F64) first = A + (size_t)(q * NB + dc) * npad + q * NB;
-    else first = tinv + (((size_t)mat * np + q) * NB + dc) * NB;
-    UniformCols<D> cols(first, 8 * (F64 ? npad : NB));
+    if constexpr (F64) first = block;
+    else first = tinv + (((size_t)mat * np + q) * NB + c0d) * NB;
+    UniformCols<D> cols(first, CS * (F64 ? npad : NB));
 #pragma unroll
     for (int u = 0; u < NS; ++u) dv[u] = cols.next()[dr];
+    if constexpr (EV) {
+      UniformCols<T> bcols(block, npad);
+#pragma unroll
+      for (int u = 0; u < NS; ++u) ev[u] = bcols.next()[dr];
+    }
   };
   // FP64: into LDS the strict triangle the chain reads (lower: L; upper: U, whose
   // diagonal goes to s_rc as reciprocals), zeros elsewhere
@@ -1734,7 +1766,7 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
     D dg = 1;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const int r = dr, c = dc + 8 * u;
+      const int r = dr, c = c0d + CS * u;
       if constexpr (F64) {
         dg = r == c ? dv[u] : dg;
         sD[r][c] = (upper ? r < c : r > c) ? dv[u] : 0.0;
@@ -1777,29 +1809,73 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
       }
       lds_barrier();
     } else {
-      const int r = dr, g = dc;
-      double acc = 0.0;
+      int r = dr;
+      if constexpr (EV) asm("" : "+v"(r));   // (addresses made from it here, not kept in registers over the strips)
+      // a triangle's product with v: entry(u, c) of row r, column c; on the threads t < NB
+      const bool none = UP == (TRANSPOSE != 0) ? no_lo : no_up;   // (of the triangle, or its transpose)
+      auto times = [&](auto entry, const double* v) {
+        double acc = 0.0;
+        if (!none) {
 #pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        const int c = g + 8 * u;
-        if constexpr (TRANSPOSE) acc += static_cast<double>(sD[c][r]) * sb[k0 + c];   // row c of the block, column r
-        else acc += ((UP ? r <= c : r > c) ? static_cast<double>(dv[u]) : 0.0) * sb[k0 + c];
-      }
-      if constexpr (TRANSPOSE) lds_barrier();   // the staged block is read
-      s_part[g * NB + r] = acc;
-      lds_barrier();
-      if (tid < NB) {
-        double t = UP ? 0.0 : sb[k0 + tid];
+          for (int u = 0; u < NS; ++u) {
+            acc += static_cast<double>(entry(u, c0d + u)) * v[c0d + u];
+            if (!TRANSPOSE && u % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (all of v ahead would spill)
+          }
+        }
+        s_part[dc * NB + r] = acc;
+        lds_barrier();
+        double t = 0.0;
+        if (tid < NB) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) t += s_part[q * NB + tid];
-        sb[k0 + tid] = t;
+          for (int q = 0; q < 8; ++q) t += s_part[q * NB + tid];
+        }
+        return t;
+      };
+      if constexpr (!TRANSPOSE) {   // the other triangle's entries, where the wavefront has both
+        if ((dc >> 2) == dh) {
+#pragma unroll
+          for (int u = 0; u < NS; ++u) {
+            const bool in = UP ? r <= c0d + u : r > c0d + u;
+            dv[u] = in ? dv[u] : 0.0f;
+            if constexpr (EV) ev[u] = in ? ev[u] : 0.0f;
+          }
+        }
       }
+      auto inv = [&](int u, int c) -> float {
+        if constexpr (TRANSPOSE) return sD[c][r];   // row c of the block, column r
+        else return dv[u];
+      };
+      if constexpr (TRANSPOSE && CORR) {   // (dv is free: the inverse is staged; the block travels meanwhile)
+        UniformCols<T> cols(A + (size_t)(k0 + c0d) * npad + k0, npad);
+#pragma unroll
+        for (int u = 0; u < NS; ++u) dv[u] = cols.next()[dr];
+      }
+      double x0 = times(inv, sb + k0);
+      if (!UP && tid < NB) x0 += sb[k0 + tid];   // (the unit diagonal of L is implied)
+      if constexpr (CORR) {
+        if (tid < NB) s_v[0][tid] = x0;
+        if constexpr (TRANSPOSE) {
+#pragma unroll
+          for (int u = 0; u < NS; ++u) sE[r][c0d + u] = (UP ? r <= c0d + u : r > c0d + u) ? dv[u] : 0.0f;
+        }
+        lds_barrier();
+        auto own = [&](int u, int c) -> float {
+          if constexpr (TRANSPOSE) return sE[c][r];
+          else return ev[u];
+        };
+        const double res = times(own, s_v[0]);
+        if (tid < NB) s_v[1][tid] = sb[k0 + tid] - (UP ? 0.0 : s_v[0][tid]) - res;
+        lds_barrier();
+        x0 = times(inv, s_v[1]);
+        if (tid < NB) x0 += UP ? s_v[0][tid] : s_v[0][tid] + s_v[1][tid];
+      }
+      if (tid < NB) sb[k0 + tid] = x0;
       lds_barrier();
     }
   };
   using Up = std::true_type;
   using Lo = std::false_type;
-  load_diag(0);
+  load_diag(0, true, TRANSPOSE != 0);
   // the permutations of a panel and the next one: FP64 factors a phase ahead
   int pa = 0, pb = 0, qa = 0, qb = 0;
   auto load_perm = [&](int q) {
@@ -1832,21 +1908,23 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
       if (first) permute(p + 1, own(p + 1, 1, qb), own(p + 1, 0, qa));
       if constexpr (F64) lds_barrier();
       solve_diag(k0, Lo());   // unit lower triangular diagonal block
-      if (p + 1 < np) {                  // the last panel's block serves U too
-        load_diag(p + 1);
+      if (p + 1 < np) {
+        load_diag(p + 1, true, false);
         if constexpr (F64) load_perm(p + 1);
         apply(lower(p), p + 2 < np ? lower(p + 1) : upper(np - 1));
       }
     }
     for (int p = np - 1; p >= 0; --p) {
       const int k0 = p * NB;
-      if constexpr (F64) {
+      if constexpr (F64) {   // (the last panel's block is there)
         store_diag(true);
         lds_barrier();
+      } else if (p == np - 1) {
+        load_diag(p, false, true);
       }
       solve_diag(k0, Up());   // upper triangular diagonal block
       if (p > 0) {
-        load_diag(p - 1);
+        load_diag(p - 1, false, true);
         apply(upper(p), upper(p - 1));
       }
     }
@@ -1885,7 +1963,7 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
       store_diag(true);
       lds_barrier();
       solve_diag(k0, Up());
-      if (p + 1 < np) load_diag(p + 1);   // the last panel's block serves L^T too
+      if (p + 1 < np) load_diag(p + 1, true, true);
       // c[col] -= sum_j U[k0+j][col] z_j for col >= k0 + NB
       for (int col = k0 + NB + 8 * w; col < npad; col += 8 * NWV) {
         const double t = dots8(col, k0, k0 + NB);
@@ -1896,7 +1974,7 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
     // for p = m..1: z <- L_p^-T z, then z <- P_p^T z
     for (int p = np - 1; p >= 0; --p) {
       const int k0 = p * NB;
-      if (p < np - 1) load_diag(p);
+      if (CORR || p < np - 1) load_diag(p, true, true);   // (FP64: the last panel's block is there)
       // z_j -= sum_{r >= k0+NB} L[r][k0+j] z_r (16 wavefronts, eight columns each)
       if (k0 + NB < npad) {
         const double t = dots8(k0 + 8 * w, k0 + NB, npad);
@@ -2181,29 +2259,47 @@ void launch_to_half(const float* src, void* dst, size_t n, hipStream_t s) {
   k_to_half<<<4096, 256, 0, s>>>(src, static_cast<_Float16*>(dst), n);
 }
 
-void launch_lu_solve(const DevOps& d, int precision, bool transpose, const double* Bin, double* Xout, bool accumulate,
-                     const RefineCheck& check, hipStream_t s) {
-  launch_lu_solve_mapped(d, precision, transpose, nullptr, nullptr, d.nx_total, Bin, Xout, accumulate, check, s);
-}
 
-void launch_lu_solve_mapped(const DevOps& f, int precision, bool transpose, const int* mat_of, const int* skip,
-                            int nrows, const double* Bin, double* Xout, bool accumulate, const RefineCheck& check,
-                            hipStream_t s) {
+namespace {
+// precond: the solution only preconditions (forward solves)
+void solve_impl(const DevOps& f, int precision, bool transpose, bool precond, const int* mat_of, const int* skip,
+                int nrows, const double* Bin, double* Xout, bool accumulate, const RefineCheck& check, hipStream_t s) {
   // the mirror flags of the FP32 factors, set at their formation
   const int* mir = (precision != 0 && precision != kFactorsFp16) ? f.mirror : nullptr;
-  auto run = [&](auto* LU) {
+  auto run = [&](auto* LU, auto tc, auto corr) {
     using T = std::remove_const_t<std::remove_pointer_t<decltype(LU)>>;
-    auto go = [&](auto tc) {
-      k_solve<T, decltype(tc)::value><<<nrows, 1024, 0, s>>>(
-          LU, f.tinv, f.perm, Bin, Xout, check, accumulate, f.npad, mat_of, skip, f.band_kl,
-          f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
-    };
-    if (transpose) go(std::integral_constant<int, 1>());
-    else go(std::integral_constant<int, 0>());
+    k_solve<T, decltype(tc)::value, decltype(corr)::value><<<nrows, 1024, 0, s>>>(
+        LU, f.tinv, f.perm, Bin, Xout, check, accumulate, f.npad, mat_of, skip, f.band_kl,
+        f.band_kl > 0 ? f.band_kl + f.band_ku : 0, lu_paired(f) ? 1 : 0, mir, f.n, f.nth);
   };
-  if (precision == 0) run(static_cast<const double*>(f.lu));
-  else if (precision == kFactorsFp16) run(static_cast<const _Float16*>(f.lu));
-  else run(static_cast<const float*>(f.lu));
+  using Fwd = std::integral_constant<int, 0>;
+  using Tr = std::integral_constant<int, 1>;
+  const auto* f64 = static_cast<const double*>(f.lu);
+  const auto* f32 = static_cast<const float*>(f.lu);
+  const auto* f16 = static_cast<const _Float16*>(f.lu);
+  if (precision == 0) {
+    if (transpose) run(f64, Tr(), std::false_type());
+    else run(f64, Fwd(), std::false_type());
+  } else if (precision == kFactorsFp16) {   // (preconditioners alone)
+    run(f16, Fwd(), std::false_type());
+  } else if (transpose) {
+    run(f32, Tr(), std::true_type());
+  } else if (precond) {
+    run(f32, Fwd(), std::false_type());
+  } else {
+    run(f32, Fwd(), std::true_type());
+  }
+}
+}  // namespace
+
+void launch_lu_solve(const DevOps& d, int precision, bool transpose, const double* Bin, double* Xout, bool accumulate,
+                     const RefineCheck& check, hipStream_t s, bool precond) {
+  solve_impl(d, precision, transpose, precond, nullptr, nullptr, d.nx_total, Bin, Xout, accumulate, check, s);
+}
+
+void launch_lu_solve_mapped(const DevOps& f, int precision, const int* mat_of, const int* skip, int nrows,
+                            const double* Bin, double* Xout, bool accumulate, hipStream_t s) {
+  solve_impl(f, precision, false, true, mat_of, skip, nrows, Bin, Xout, accumulate, {}, s);
 }
 
 }  // namespace bte

@@ -1009,6 +1009,47 @@ def test_triangular_solves_of_every_height(torch, nr, nth, form):
     s.close()
 
 
+@pytest.mark.parametrize("static", [1, 0])
+@pytest.mark.parametrize("nr,nth,dt_frac", [(48, 24, 0.05), (64, 16, 1.0), (20, 16, 1.0)])
+def test_refinement_takes_the_sweeps_of_a_substitution(torch, nr, nth, dt_frac, static):
+    """Long time steps (50 and 1000 times the usual one), whose diagonal blocks' FP32 inverses alone
+    would leave errors that cost further sweeps: the solves with FP32 factors, with and without
+    interchanges, refine in as many sweeps as 64-bit substitutions with the same factors do here
+    (simulated to half the stop)."""
+    import lu_reference as LR
+    from paper_2502_16555_amd import _lib
+    cfg = workloads.small_config(nx=3, nr=nr, nth=nth, kinds=("elastic", "excitation", "ionization"), E=1.2e4,
+                                 field_kind="rf", dt_frac=dt_frac)
+    ops = oracle.build_operators(cfg)
+    s = solver(cfg, precision="mixed_fp32")
+    s.set_tuning(_lib.TUNE_STATIC_PIVOTING, static)
+    n, dt, E = s.n, cfg["dt_s"], np.array([1.2e4, 6e3, 50.0])
+    F = _state(ops, 3)
+    M0 = S.v_matrix(ops, 0.0)
+    c_inf = np.abs((np.eye(n) - M0) / dt).sum(1).max()
+    a_inf = np.abs((M0 - S.v_matrix(ops, 1.0)) / dt).sum(1).max()
+    want = 0
+    for x in range(3):
+        lu, piv = s.factor_export(cuda(torch, E), x)
+        A = LR.pad(S.v_matrix(ops, E[x]))
+        b = np.zeros(len(A))
+        b[:n] = F[x].ravel()
+        sol = LR.solve(lu, piv, b, pairs=True)
+        for k in range(11):
+            r = b - A @ sol
+            norm = 1.0 + dt * (c_inf + abs(E[x]) * a_inf)
+            if np.abs(r).max() <= 0.5e-14 * (norm * np.abs(sol).max() + np.abs(b).max()):
+                break
+            sol = sol + LR.solve(lu, piv, r, pairs=True)
+        want = max(want, k)
+    Fg = cuda(torch, F)
+    s.vstep(Fg, cuda(torch, E))
+    code, sweeps, resid = s.status()
+    s.close()
+    assert code == 0 and resid <= 1e-14, (code, sweeps, resid)
+    assert sweeps <= want, (sweeps, want)
+
+
 @pytest.mark.parametrize("prec", ["mixed_fp32", "mixed_bf16x3", "mixed_bf16"])
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_partial_pivoting_vstep_matches_oracle(torch, case, prec):
