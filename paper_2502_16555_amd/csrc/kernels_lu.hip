@@ -2006,7 +2006,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
   T* LU = static_cast<T*>(d.lu) + (size_t)m0 * np2;
   T* xs = static_cast<T*>(d.xscr) + (size_t)m0 * d.npad * NB;
   T* li = static_cast<T*>(d.linv) + (size_t)m0 * kLinvElems;  // inverses of L11 and its diagonal blocks
-  float* ti = d.tinv + (size_t)m0 * d.npad * NB;              // FP32: the diagonal blocks' inverses, for the solves
+  float* ti = d.tinv ? d.tinv + (size_t)m0 * d.npad * NB : nullptr;   // FP32: the diagonal blocks' inverses, for the solves
   int* piv = d.piv + (size_t)m0 * d.npad;
   int* perm = d.perm + (size_t)m0 * kMaxPanels * kPermStride;
   const int xpb = d.form_xpb > 0 ? d.form_xpb : (sizeof(T) == 4 ? 8 : 16);   // matrices per formation block
@@ -2027,7 +2027,8 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
   // statically pivoted dense factors in groups of four panels (lu_pairs 2):
   // the updates of a group's panels on the columns beyond the group are
   // deferred to one K = 512 update
-  const bool quads = stat && d.lu_pairs == 2 && d.band_kl == 0 && np >= 4;
+  // (FP32 products at those depths need the maxima of L's rows and U's columns)
+  const bool quads = stat && d.lu_pairs == 2 && d.band_kl == 0 && np >= 4 && (bf16_terms || (d.lmax && d.umax));
   const bool fsplit = !quads && stat && pairs && la && la->form_overlap && la->side && np >= 4 && d.band_kl == 0;
   if (fsplit) {
     (void)hipEventRecord(la->form_ev[0], s);

@@ -4,6 +4,8 @@
 // old values are read and written once (the LDS-staged epilogue), L21 and U12
 // are read once per tile; blocks of one matrix stay on one XCD so that its L21
 // and U12 come from that XCD's L2.
+#include <stdexcept>
+
 #include "internal.h"
 #include "lu_common.h"
 
@@ -416,6 +418,8 @@ void launch_update_k(int kind, void* LU, int npad, int k0, int mtr, int mtc, int
     else if (kind == 0) k_update<double, 16, 4, 2, 1, KD><<<gu, 256, 0, s>>>(D, npad, k0, mtr, mtc, tj0, nmat, lrow);
     else if (alt_kc) k_update<float, 32, 1, 2, 1, KD><<<gu, 256, 0, s>>>(A, npad, k0, mtr, mtc, tj0, nmat, lrow);
     else k_update<float, 16, 4, 4, 1, KD><<<gu, 256, 0, s>>>(A, npad, k0, mtr, mtc, tj0, nmat, lrow);
+  } else {
+    throw std::logic_error("no trailing update of this depth without the row and column maxima");
   }
 }
 
@@ -430,7 +434,8 @@ void launch_update(int kind, void* LU, int npad, int k0, int mtr, int mtc, int t
     case 4 * NB: go(std::integral_constant<int, 4 * NB>{}); break;
     case 3 * NB: go(std::integral_constant<int, 3 * NB>{}); break;
     case 2 * NB: go(std::integral_constant<int, 2 * NB>{}); break;
-    default: go(std::integral_constant<int, NB>{}); break;
+    case NB: go(std::integral_constant<int, NB>{}); break;
+    default: throw std::logic_error("trailing update of an unknown depth");
   }
 }
 
