@@ -406,9 +406,10 @@ bte_status bte_get_timing(bte_handle* h, double* ms_out);
  *   BTE_TUNE_UPDATE_KC: K chunk of the trailing-update tiles staged per LDS
  *     buffer: 16 or 32 (FP32 factors), 8 or 16 (FP64); 0 = default (16).  The
  *     16-chunk FP32 form runs four blocks per CU, the 32-chunk form two.  The
- *     BF16 updates have a fixed chunk of 32 (reported as such), and so have the
- *     FP32 updates of panels in groups of four, whose products run on split f16
- *     operands (the setting then applies to the other panel groupings only).
+ *     BF16 updates have a fixed chunk of 32 (reported as such).  The FP32
+ *     updates of panels in groups of four have one too, their products running
+ *     on split f16 operands: the setting applies to the other panel groupings
+ *     only, and the autotuner leaves it out.
  *   BTE_TUNE_FORM_XPB: matrices formed per block of the formation kernel,
  *     1..64; 0 = default (8 for FP32 factors, 16 for FP64).
  *   BTE_TUNE_PANEL_PAIRS: 2 (default), 1 or 0.  1: dense factors take the
@@ -441,7 +442,7 @@ bte_status bte_get_timing(bte_handle* h, double* ms_out);
  *     factorization and L21 then run on a side stream (default priority)
  *     during the rest of the update.  Same arithmetic in the same order: the
  *     results do not depend on it.  Panels in groups of four (the default)
- *     do not take it; the autotuner tries both.
+ *     do not take it; the autotuner tries both for the others.
  *   BTE_TUNE_FORM_OVERLAP: 0 (default) or 1.  With statically pivoted FP32
  *     factors, panels in pairs, dense systems and one factorization group, the
  *     matrices' columns and rows below 256 are formed first, and the rest of

@@ -18,15 +18,23 @@ import os
 from . import _lib
 
 
-def candidates(precision: str) -> dict:
-    """Candidate values per tuning key (the first one is the library default)."""
+def candidates(precision: str, groups_of_four: bool = False) -> dict:
+    """Candidate values per tuning key (the first one is the library default).  Panels in groups
+    of four have a fixed update chunk and take no look-ahead: those keys keep their defaults."""
     kc = [16, 8] if precision == "fp64" else [16, 32]
     if precision in ("mixed_bf16", "mixed_bf16x3"):
         kc = [32]   # the bf16 updates have a fixed chunk
-    c = {_lib.TUNE_LU_STREAMS: [1, 2], _lib.TUNE_UPDATE_KC: kc, _lib.TUNE_FORM_XPB: [8, 4, 16, 32]}
+    c = {_lib.TUNE_LU_STREAMS: [1, 2], _lib.TUNE_UPDATE_KC: kc[:1] if groups_of_four else kc,
+         _lib.TUNE_FORM_XPB: [8, 4, 16, 32]}
     if precision != "fp64":
-        c[_lib.TUNE_LOOK_AHEAD] = [0, 1]   # the statically pivoted panels on a side stream
+        c[_lib.TUNE_LOOK_AHEAD] = [0] if groups_of_four else [0, 1]   # the statically pivoted panels on a side stream
     return c
+
+
+def takes_groups_of_four(solver, precision: str) -> bool:
+    """Whether the handle factors its panels of 128 columns in groups of four."""
+    return (precision != "fp64" and solver.n > 3 * 128 and solver.get_tuning(_lib.TUNE_PANEL_PAIRS) == 2
+            and solver.get_tuning(_lib.TUNE_STATIC_PIVOTING) == 1)
 
 
 def size_class(n: int, nx_total: int, precision: str) -> str:
@@ -100,7 +108,8 @@ def autotune(solver, F, precision: str, t0: float = 0.0, steps: int = 2, cache_p
     if measure is None:
         def measure():
             return _time_steps(solver, F, t0, steps)
-    best, cost, trials = coordinate_descent(solver.set_tuning, measure, candidates(precision))
+    cands = candidates(precision, takes_groups_of_four(solver, precision))
+    best, cost, trials = coordinate_descent(solver.set_tuning, measure, cands)
     if cache_path:
         cache[cls] = {"settings": {str(k): v for k, v in best.items()}, "ms_per_step": cost}
         d = os.path.dirname(os.path.abspath(cache_path))

@@ -51,3 +51,28 @@ def test_size_classes_and_cache(tmp_path):
     s2 = FakeSolver()
     r2 = AT.autotune(s2, None, "fp64", cache_path=str(path), measure=None)
     assert r2["cached"] and s2.settings == r["settings"]
+
+
+def test_settings_without_effect_are_not_tried():
+    """Statically pivoted panels in groups of four fix the update chunk and take no look-ahead:
+    neither is timed, and both stay at their defaults, unless the handle groups its panels
+    otherwise or has fewer than four."""
+    class Handle(FakeSolver):
+        def __init__(self, n, pairs=2, static=1):
+            super().__init__(n=n)
+            self.settings = {_lib.TUNE_PANEL_PAIRS: pairs, _lib.TUNE_STATIC_PIVOTING: static}
+
+        def get_tuning(self, k):
+            return self.settings[k]
+
+    def tried(s, precision):
+        r = AT.autotune(s, None, precision, measure=lambda: 1.0)
+        seen = {k: {v for kk, v in s.log if kk == k} for k in (_lib.TUNE_UPDATE_KC, _lib.TUNE_LOOK_AHEAD)}
+        return r["settings"], seen[_lib.TUNE_UPDATE_KC], seen[_lib.TUNE_LOOK_AHEAD]
+
+    best, kc, ahead = tried(Handle(2048), "mixed_fp32")
+    assert kc == {16} and ahead == {0}
+    assert best[_lib.TUNE_UPDATE_KC] == 16 and best[_lib.TUNE_LOOK_AHEAD] == 0
+    assert tried(Handle(2048), "mixed_bf16x3")[1:] == ({32}, {0})
+    for s in (Handle(384), Handle(2048, pairs=1), Handle(2048, static=0)):
+        assert tried(s, "mixed_fp32")[1:] == ({16, 32}, {0, 1})

@@ -1484,6 +1484,29 @@ def test_autotuned_shapes_leave_results_unchanged(torch, tmp_path):
         s.close()
 
 
+@pytest.mark.parametrize("pairs,static", [(1, 1), (0, 1), (2, 0)])
+def test_fp32_update_chunks_of_other_groupings(torch, pairs, static):
+    """The FP32 updates of panels in pairs or singly, which have two chunk sizes: the same bits by
+    either, and the oracle's step."""
+    from paper_2502_16555_amd import _lib
+    cfg = CASES["panels4"]()
+    ops = oracle.build_operators(cfg)
+    F0 = _state(ops, 8)
+    s = solver(cfg, precision="mixed_fp32")
+    s.set_tuning(_lib.TUNE_PANEL_PAIRS, pairs)
+    s.set_tuning(_lib.TUNE_STATIC_PIVOTING, static)
+    out = []
+    for kc in (16, 32):
+        s.set_tuning(_lib.TUNE_UPDATE_KC, kc)
+        F = cuda(torch, F0)
+        s.step(F, 0.0)
+        assert s.status()[0] == 0
+        out.append(F.cpu().numpy())
+    s.close()
+    assert np.array_equal(out[0], out[1])
+    close(out[0], S.step(ops, F0, 0.0), 1e-10, "step")
+
+
 @pytest.mark.parametrize("fprec", ["fp64", "mixed_fp32", "fp16_factors"])
 @pytest.mark.parametrize("case", ["ragged", "panels", "panels4"])
 def test_krylov_vstep_matches_oracle(torch, case, fprec):
