@@ -30,14 +30,18 @@ __device__ inline bool finite_d(double v) { return (v - v) == 0.0; }
 // entries into whole lines: one block per point, as before, wrote Y eight bytes
 // at a time and kept 100 of 256 CUs.  The ordinate pairs of 16 points run on
 // one XCD, whose L2 joins their parts of the state's lines.
-// Per transform to modes / back: 100 x 64 x 16 13.7 / 12.3 -> 7.1 / 8.1 us, 256 x 64
-// x 32 23 / 22 -> 8.4 / 9.4.
+// The contraction ends at Nr (rounded up to 16), and one discharge's place is an
+// argument: on small grids a chain of loads, divisions and products on zeros was
+// half of the time.  Per transform to modes / back, against one block per point:
+// 16 x 16 x 8 3.5 / 3.2 -> 3.6 / 3.2 us (5.2 / 5.1 with 64 speeds contracted always), 180
+// x 16 x 8 3.8 / 3.6 (5.4 / 4.6), 18 x 48 x 16 5.0 / 4.8 (6.2 / 6.9), 100 x 64 x 16
+// 13.7 / 12.3 -> 6.7 / 6.1 (7.1 / 8.1), 256 x 64 x 32 23 / 22 -> 7.8 / 7.9 (8.4 / 9.4).
 constexpr int kModeX = 16, kModeA = 2, kModeK = 64;
 template <int TO_X>
 __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, double* __restrict__ Y,
                                                     const double* __restrict__ W, const int* __restrict__ x_off,
                                                     const int* __restrict__ nx_of, int nr, int nth, int transposeW,
-                                                    int tiles, int nd, int* __restrict__ status,
+                                                    int tiles, int nd, int nx_one, int* __restrict__ status,
                                                     const double* __restrict__ X, const double* __restrict__ Fn,
                                                     const double* __restrict__ mu, double dt) {
   using V2 = double __attribute__((ext_vector_type(2), aligned(8)));   // (F is the caller's: any double address)
@@ -47,14 +51,18 @@ __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, doub
   int tile, item;
   xcd_map(blockIdx.x, pairs * groups, tiles * nd, &tile, &item);
   if (tile >= tiles * nd) return;
-  const int d = tile / tiles, nx = nx_of[d], xt = (tile % tiles) * kModeX;
+  // (one discharge: no loads before those of the state)
+  const int d = nd == 1 ? 0 : tile / tiles;
+  const int nx = nd == 1 ? nx_one : nx_of[d], xo = nd == 1 ? 0 : x_off[d];
+  const int xt = (tile - d * tiles) * kModeX;
   if (xt >= nx) return;
-  const int a0 = (item % pairs) * kModeA, n = nr * nth;
+  const int grp = groups == 1 ? 0 : item / pairs;
+  const int a0 = (item - grp * pairs) * kModeA, n = nr * nth;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  double* Yd = Y + (size_t)x_off[d] * n;
-  double* Fd = F + (size_t)x_off[d] * n;
-  const int m0 = (item / pairs) * 64 + 16 * w;   // this wavefront's output speeds
+  double* Yd = Y + (size_t)xo * n;
+  double* Fd = F + (size_t)xo * n;
+  const int m0 = grp * 64 + 16 * w;   // this wavefront's output speeds
   const int mrow = min(m0 + li, nr - 1);
   const double* wr = W + (transposeW ? (size_t)mrow : (size_t)mrow * nr);
   const int ws = transposeW ? nr : 1;
@@ -65,33 +73,51 @@ __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, doub
   for (int k0 = 0; k0 < nr; k0 += kModeK) {
     double wv[kModeK / 4];
 #pragma unroll
-    for (int q = 0; q < kModeK / 4; ++q) wv[q] = wr[(size_t)min(k0 + 4 * q + lk, nr - 1) * ws];
+    for (int q = 0; q < kModeK / 4; ++q) {
+      if (q % 4 == 0 && k0 + 4 * q >= nr) break;   // (the contraction ends at Nr, rounded up to 16)
+      wv[q] = wr[(size_t)min(k0 + 4 * q + lk, nr - 1) * ws];
+    }
     if (k0 > 0) __syncthreads();
+    // (loads without branches, from entries of the discharge; all before the first store)
     if constexpr (TO_X) {
+      constexpr int NU = kModeA * kModeK * kModeX / kThreads, KU = kModeK / NU;
+      double v[NU];
+      const int x = tid % kModeX, a = tid / kModeX % kModeA, k = k0 + tid / (kModeX * kModeA);
+      const double* p = Yd + (size_t)(a0 + a) * nx + min(xt + x, nx - 1);
 #pragma unroll
-      for (int u = 0; u < kModeA * kModeK * kModeX / kThreads; ++u) {
-        const int e = tid + kThreads * u, x = e % kModeX, a = e / kModeX % kModeA, k = e / (kModeX * kModeA);
-        sF[a][k][x] = (k0 + k < nr && xt + x < nx) ? Yd[(size_t)((k0 + k) * nth + a0 + a) * nx + xt + x] : 0.0;
+      for (int u = 0; u < NU; ++u) {
+        if (u % (16 / KU) == 0 && k0 + KU * u >= nr) break;
+        v[u] = p[(size_t)min(k + KU * u, nr - 1) * (nth * nx)];
+      }
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (u % (16 / KU) == 0 && k0 + KU * u >= nr) break;
+        sF[a][k - k0 + KU * u][x] = (k + KU * u < nr && xt + x < nx) ? v[u] : 0.0;
       }
     } else {
+      constexpr int NU = kModeK * kModeX / kThreads, XU = kModeX / NU;
+      V2 v[NU];
+      const int k = tid % kModeK, x = tid / kModeK;
+      const double* p = Fd + (size_t)min(k0 + k, nr - 1) * nth + a0;
 #pragma unroll
-      for (int u = 0; u < kModeK * kModeX / kThreads; ++u) {
-        const int e = tid + kThreads * u, k = e % kModeK, x = e / kModeK;
-        V2 v = V2{0.0, 0.0};
-        if (k0 + k < nr && xt + x < nx)
-          v = *reinterpret_cast<const V2*>(Fd + (size_t)(xt + x) * n + (size_t)(k0 + k) * nth + a0);
-        bad |= !finite_d(v[0]) | !finite_d(v[1]);
-        sF[0][k][x] = v[0];
-        sF[1][k][x] = v[1];
+      for (int u = 0; u < NU; ++u) v[u] = *reinterpret_cast<const V2*>(p + (size_t)min(xt + x + XU * u, nx - 1) * n);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        bad |= !finite_d(v[u][0]) | !finite_d(v[u][1]);
+        const bool in = k0 + k < nr && xt + x + XU * u < nx;
+        sF[0][k][x + XU * u] = in ? v[u][0] : 0.0;
+        sF[1][k][x + XU * u] = in ? v[u][1] : 0.0;
       }
     }
     __syncthreads();
     if (m0 < nr) {
 #pragma unroll
-      for (int q = 0; q < kModeK / 4; ++q)
+      for (int q = 0; q < kModeK / 4; ++q) {
+        if (q % 4 == 0 && k0 + 4 * q >= nr) break;
 #pragma unroll
         for (int a = 0; a < kModeA; ++a)
           acc[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[q], sF[a][4 * q + lk][li], acc[a], 0, 0, 0);
+      }
     }
   }
   if (!TO_X && bad) atomicOr(status, kStNonFinite);
@@ -101,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void k_modes(double* __restrict__ F, doub
     const int m = m0 + lk + 4 * t;   // result row of item t
     if (m >= nr || x >= nx) continue;
     if constexpr (TO_X) {
-      const size_t o = (size_t)x * n + (size_t)m * nth + a0, og = (size_t)x_off[d] * n + o;
+      const size_t o = (size_t)x * n + (size_t)m * nth + a0, og = (size_t)xo * n + o;
       V2 v = V2{acc[0][t], acc[1][t]};
       if constexpr (TO_X == 2) {
         const V2 f = *reinterpret_cast<const V2*>(Fd + o), xv = *reinterpret_cast<const V2*>(X + og);
@@ -384,7 +410,7 @@ static void run_modes(const DevOps& d, double* F, const double* W, int transpose
                       const double* X = nullptr, const double* Fn = nullptr) {
   const int tiles = (d.max_nx + kModeX - 1) / kModeX;
   const int grid = xcd_grid(d.nth / kModeA * ((d.nr + 63) / 64), tiles * d.nd);
-  k_modes<TO_X><<<grid, kThreads, 0, s>>>(F, d.Y, W, d.x_off, d.nx_of, d.nr, d.nth, transposeW, tiles, d.nd, d.status,
+  k_modes<TO_X><<<grid, kThreads, 0, s>>>(F, d.Y, W, d.x_off, d.nx_of, d.nr, d.nth, transposeW, tiles, d.nd, d.max_nx, d.status,
                                          X, Fn, d.mu_th, d.dt);
 }
 

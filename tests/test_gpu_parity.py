@@ -677,6 +677,32 @@ def test_adjoint_step_is_bitwise_reproducible(torch):
     s.close()
 
 
+@pytest.mark.parametrize("nx_per,nr,nth", [((3,), 4, 2), ((16,), 16, 2), ((17,), 17, 4), ((15, 33, 4), 32, 2),
+                                           ((34,), 33, 6), ((18, 16, 17), 48, 2), ((33,), 64, 2), ((20,), 65, 2),
+                                           ((5, 40), 130, 2)])
+def test_mode_transforms_at_edges_of_their_tiles(torch, nx_per, nr, nth):
+    """Half-steps and their transposes where the transforms to modes and back end a tile of 16
+    points, 16 output speeds or 16 (64) contracted speeds, with one discharge and several, against
+    the oracle per discharge.  Tolerance: that of the half-steps elsewhere."""
+    base = workloads.small_config(nx=nx_per[0], nr=nr, nth=nth, kinds=("elastic",))
+    nd = len(nx_per)
+    cfg = dict(base, n_discharges=nd, nx_per=list(nx_per), n0_per=[base["n0_m3"]] * nd, E0_per=[2e3] * nd)
+    s = solver(cfg, precision="fp64")
+    F = np.random.default_rng(6).standard_normal((sum(nx_per), nr, nth)) * 1e3
+    Fg, Tg = cuda(torch, F), cuda(torch, F)
+    s.xstep(Fg)
+    s.xstep_T(Tg)
+    assert s.status()[0] == 0
+    s.close()
+    x0 = 0
+    for nx in nx_per:
+        ops = oracle.build_operators(dict(base, nx=nx, nx_per=[nx]))
+        sl = slice(x0, x0 + nx)
+        close(Fg.cpu().numpy()[sl], S.x_half_step(ops, F[sl]), 1e-11, (nx, "forward"))
+        close(Tg.cpu().numpy()[sl], S.x_half_step_T(ops, F[sl]), 1e-11, (nx, "transposed"))
+        x0 += nx
+
+
 def test_nonfinite_state_is_reported(torch):
     from paper_2502_16555_amd import _lib
     cfg = workloads.config("C0")
