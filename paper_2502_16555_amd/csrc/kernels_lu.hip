@@ -1330,8 +1330,7 @@ __global__ __launch_bounds__(256, 2) void k_u12(T* __restrict__ LU, const T* __r
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256, 2) void k_u12pre(T* __restrict__ LU, const int* __restrict__ perm,
-                                                T* __restrict__ xscr, int npad, int k1, int nct, int nmat,
-                                                int ident, int kj) {
+                                                T* __restrict__ xscr, int npad, int k1, int nct, int nmat) {
   using V = typename Vec4<T>::type;
   constexpr int PER = Vec4<T>::per;
   // FP32 operand layout as in k_u12 (the U_p stores are W's pattern)
@@ -1342,9 +1341,7 @@ __global__ __launch_bounds__(256, 2) void k_u12pre(T* __restrict__ LU, const int
   xcd_map(blockIdx.x, nct, nmat, &mat, &ct);
   if (mat >= nmat) return;
   T* A = LU + (size_t)mat * npad * npad;
-  // the deferred updates of the kj panels before this one (a pair's first
-  // panel: kj = 1; in groups of four, up to 3): K = 128 kj from column kp
-  const int kp = k1 - kj * NB;
+  const int kp = k1 - NB;   // the pair's first panel
   const int c0 = k1 + NB + ct * 128;
   const int* src = perm + ((size_t)mat * kMaxPanels + k1 / NB) * kPermStride + 1 + kMaxSwapRows;
   __shared__ __align__(16) T smem[4 * KC * LD];   // the operand chunks, then the passes of W
@@ -1354,10 +1351,7 @@ __global__ __launch_bounds__(256, 2) void k_u12pre(T* __restrict__ LU, const int
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int wr = (w >> 1) * 64, wc = (w & 1) * 64;
-  // ident: statically pivoted factors, whose top rows are the panel's own (the
-  // identity that the diagonal kernel records too), so that this kernel need
-  // not wait for it
-  if (tid < NB) s_src[tid] = ident ? k1 + tid : src[tid];
+  if (tid < NB) s_src[tid] = src[tid];
   __syncthreads();
   constexpr int NAS = KC * 128 / 256;         // gathered L_p elements per thread and chunk
   constexpr int NBV = KC * 128 / PER / 256;   // U_p vectors per thread and chunk
@@ -1399,7 +1393,7 @@ __global__ __launch_bounds__(256, 2) void k_u12pre(T* __restrict__ LU, const int
   load(0);
   store(0);
   __syncthreads();
-  const int NCH = kj * (NB / KC);
+  constexpr int NCH = NB / KC;
   for (int ch = 0; ch < NCH; ++ch) {
     const int buf = ch & 1;
     if (ch + 1 < NCH) load((ch + 1) * KC);
@@ -2192,7 +2186,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
       // this panel's U12 from its top rows with panel p-1's deferred update,
       // the interchanges' other rows moved down, panel p-1's L rows permuted
       // (statically pivoted panels interchange no rows: nothing to move)
-      k_u12pre<T><<<xcd_grid(nct, nmat), 256, 0, s>>>(LU, perm, xs, d.npad, k0, nct, nmat, 0, 1);
+      k_u12pre<T><<<xcd_grid(nct, nmat), 256, 0, s>>>(LU, perm, xs, d.npad, k0, nct, nmat);
       if (!stat) k_move_down<T><<<xcd_grid(nct, nmat), 256, 0, s>>>(LU, perm, d.npad, k0, nct, nmat);
       k_u12<T, true><<<xcd_grid(nct, nmat), 256, 0, s>>>(LU, li, perm, xs, d.npad, k0, nct, nmat);
       if (!stat) k_perm_lp<T><<<xcd_grid(NB / 16, nmat), 256, 0, s>>>(LU, perm, d.npad, k0, nmat);
