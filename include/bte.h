@@ -62,7 +62,10 @@ typedef enum {
   BTE_FP64 = 0,           /* FP64 LU (MFMA f64) and FP64 advection                       */
   BTE_MIXED_FP32 = 1,     /* FP32 LU + FP64 iterative refinement of the V-step residual
                            * (groups of four panels: FP32 products from f16 hi + lo
-                           * operands, at least as accurate as FP32 matrix products)   */
+                           * operands, 23 bits of an entry down to 2^-15 of the largest
+                           * of its row of L or column of U in the group, below that an
+                           * absolute 2^-39 of it; BTE_TUNE_PANEL_PAIRS 0 or 1: FP32
+                           * operands)                                                */
   BTE_MIXED_BF16 = 2,     /* as MIXED_FP32, LU trailing updates with bf16 operands
                            * (MFMA bf16, FP32 accumulation)                           */
   BTE_MIXED_BF16X3 = 3,   /* as MIXED_BF16 with operands split a = hi + lo in bf16 and

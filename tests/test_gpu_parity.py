@@ -1153,6 +1153,39 @@ def test_split_operand_updates_reproduce_the_matrix(torch, nr, nth):
         s.close()
 
 
+@pytest.mark.parametrize("dt_frac,spread,E0", [(1e-3, 1.0, 6e3), (1e-3, 1e4, 6e3), (0.05, 1e6, 1e4), (1.0, 1.0, 1e4)])
+def test_split_operand_updates_of_graded_matrices(torch, dt_frac, spread, E0):
+    """Collision operators scaled by 1/spread, 1, spread and 1/spread in four energy bins, which
+    spreads the rows and columns of the factors over up to twelve decades, and long steps: the
+    split f16 products hold an entry to 2^-39 of the largest of its row of L or column of U.  The
+    factors' error entry by entry against |L||U|, beside that of the same factors on the FP32
+    matrix unit (panels in pairs), whose other parts (inverses of the diagonal blocks, replaced
+    pivots) are the same: no larger in the mean, no more than twice it at the worst entry."""
+    from paper_2502_16555_amd import _lib
+    cfg = workloads.small_config(nx=3, nr=64, nth=16, kinds=("elastic", "excitation", "ionization"), E=E0,
+                                 field_kind="rf", dt_frac=dt_frac, n_bins=4)
+    cfg["scal"] = np.array([1.0 / spread, 1.0, spread, 1.0 / spread] * 3)
+    s = solver(cfg, precision="mixed_fp32")
+    n = s.n
+    C, A0 = s.operator(0, n * n).reshape(n, n), s.operator(1, n * n).reshape(n, n)
+    E = np.array([E0, 0.3 * E0, 50.0])
+    err = {}
+    for pairs in (2, 1):
+        s.set_tuning(_lib.TUNE_PANEL_PAIRS, pairs)
+        for x in range(3):
+            lu, _ = s.factor_export(cuda(torch, E), x)
+            M = (np.eye(n) - cfg["dt_s"] * (cfg["n0_m3"] * C + E[x] * A0)).astype(np.float32).astype(np.float64)
+            L, U = np.tril(lu, -1) + np.eye(n), np.triu(lu)
+            size = np.abs(L) @ np.abs(U)
+            e = np.abs(M - L @ U)[size > 0] / size[size > 0]
+            err[pairs, x] = np.sqrt(np.mean(e ** 2)), e.max()
+    s.close()
+    for x in range(3):
+        (mean, worst), (mean32, worst32) = err[2, x], err[1, x]
+        assert mean <= 1.1 * mean32, (x, err)
+        assert worst <= 2.0 * worst32, (x, err)
+
+
 def test_residual_of_large_grids(torch):
     """Refinement residuals by the 64 x 32 tiles (200 points, n = 2040: 256 tiles, the last of each
     direction partly filled), against direct solves at points of the first, second and last tile
