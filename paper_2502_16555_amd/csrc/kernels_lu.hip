@@ -569,8 +569,8 @@ struct DiagLds {
 
 // X = U11^-1 and Y = L11^-1 of the factored block in s.xt (column-major): tinv
 // (may be NULL) holds both triangles column-major (X on and above the diagonal, Y's strict
-// lower part below it, its unit diagonal implied; for the solves); xo (may be
-// NULL) X row-major, yo (may be NULL) Y column-major.
+// lower part below it, its unit diagonal implied; for the solves); xo X row-major,
+// yo Y column-major.
 __device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, float* __restrict__ tinv,
                                                                     float* __restrict__ xo, float* __restrict__ yo) {
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -673,17 +673,14 @@ __device__ __attribute__((always_inline)) inline void diag_inverses(DiagLds& s, 
     const int e = tid + kDiagThreads * u, k = e >> 5, i4 = (e & 31) * 4;
     const float4 v = *reinterpret_cast<const float4*>(&sXT[k][i4]);
     if (tinv) *reinterpret_cast<float4*>(tinv + (size_t)k * NB + i4) = v;
-    if (yo) {   // column-major: (i, k) at k NB + i
-      const float w[4] = {v.x, v.y, v.z, v.w};
-      float y[4];
+    const float w[4] = {v.x, v.y, v.z, v.w};   // column-major: (i, k) at k NB + i
+    float y[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) y[q] = i4 + q > k ? w[q] : (i4 + q == k ? 1.0f : 0.0f);
-      *reinterpret_cast<float4*>(yo + (size_t)k * NB + i4) = make_float4(y[0], y[1], y[2], y[3]);
-    }
+    for (int q = 0; q < 4; ++q) y[q] = i4 + q > k ? w[q] : (i4 + q == k ? 1.0f : 0.0f);
+    *reinterpret_cast<float4*>(yo + (size_t)k * NB + i4) = make_float4(y[0], y[1], y[2], y[3]);
   }
 #pragma unroll
   for (int u = 0; u < 2; ++u) {   // row-major, 4 x 4 blocks transposed in registers
-    if (!xo) break;
     const int k4 = 4 * (tid & 31), c4 = 4 * (tid >> 5) + 64 * u;
     float w[4][4];   // w[j][q] = X(k4 + q, c4 + j)
 #pragma unroll
@@ -890,20 +887,155 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_static(float* __restrict_
   if (__syncthreads_or(nonfinite) && tid == 0) atomicOr(status, kStNonFinite);
 }
 
-// The triangles' inverses (diag_inverses) of every diagonal block of FP32 factors
-// that did not leave them on the way, one block per panel and matrix, after the
-// factorization.
-__global__ __launch_bounds__(kDiagThreads) void k_diag_inv(const float* __restrict__ LU, float* __restrict__ tinv, int npad) {
-  const int k0 = blockIdx.x * NB, mat = blockIdx.y, tid = threadIdx.x;
-  const float* A = LU + (size_t)mat * npad * npad;
-  __shared__ DiagLds s;
+// The triangles' inverses of every diagonal block of FP32 factors that did not
+// leave them on the way (k_diag_static), one block per panel and matrix, after the
+// factorization: as tinv holds them, in place, the block row-major with X = U^-1 in
+// the place of its upper half and Y = L^-1 in that of its lower one.  By halves, for
+// halves of 16, 32 and 64 rows,
+//   X12 = -(X11 U12) X22,   Y21 = -Y22 (L21 Y11),
+// on MFMA in 16 x 16 blocks (lane (li, lk) holds rows 4 lk.. of column li), half of
+// the wavefronts each.  A chain of latencies between its load and its store: three
+// levels instead of a column of blocks at a time, and room for two blocks per CU: 16
+// panels of 256 matrices 202 us (273 by diagonals of blocks, the factors and the
+// inverses side by side, one block per CU).
+struct DiagInvLds {
+  __align__(16) float a[NB][NB + 4];
+  float d[8][16][17];   // diagonal blocks: X_bb on and above the diagonal, Y_bb's strict lower part below it
+};
+static_assert(2 * sizeof(DiagInvLds) <= 160 * 1024, "two blocks per CU");
+
+__global__ __launch_bounds__(512, 4) void k_diag_inv(const float* __restrict__ LU, float* __restrict__ tinv, int npad) {
+  const int k0 = blockIdx.x * NB, mat = blockIdx.y;
+  const float* A = LU + (size_t)mat * npad * npad + (size_t)k0 * npad + k0;
+  float* out = tinv + ((size_t)mat * gridDim.x + blockIdx.x) * NB * NB;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  __shared__ DiagInvLds s;
+  const int i4 = 4 * (tid & 31);
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int e = tid + kDiagThreads * u, c = e >> 5, r4 = (e & 31) * 4;
-    *reinterpret_cast<float4*>(&s.xt[c][r4]) = *reinterpret_cast<const float4*>(A + (size_t)(k0 + c) * npad + k0 + r4);
+  for (int u = 0; u < 2; ++u) {   // row-major, 4 x 4 blocks transposed in registers
+    const int j4 = 4 * (tid >> 5) + 64 * u;
+    float4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float4*>(A + (size_t)(j4 + j) * npad + i4);
+    *reinterpret_cast<float4*>(&s.a[i4 + 0][j4]) = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
+    *reinterpret_cast<float4*>(&s.a[i4 + 1][j4]) = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
+    *reinterpret_cast<float4*>(&s.a[i4 + 2][j4]) = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
+    *reinterpret_cast<float4*>(&s.a[i4 + 3][j4]) = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
   }
   __syncthreads();
-  diag_inverses(s, tinv + ((size_t)mat * gridDim.x + blockIdx.x) * NB * NB, nullptr, nullptr);
+  if (tid < NB) {   // thread (b, c): column c of X_bb by back substitution
+    const int b = tid >> 4, c = tid & 15, o = 16 * b;
+    float x[16];
+#pragma unroll
+    for (int i = 15; i >= 0; --i) {
+      float v = (i == c) ? 1.0f : 0.0f;
+#pragma unroll
+      for (int m = i + 1; m < 16; ++m) v = fmaf(-s.a[o + i][o + m], x[m], v);
+      x[i] = v / s.a[o + i][o + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (i <= c) s.d[b][i][c] = x[i];
+  } else if (tid < 2 * NB) {   // thread (b, c): column c of Y_bb (unit lower) by forward substitution
+    const int b = (tid - NB) >> 4, c = tid & 15, o = 16 * b;
+    float x[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = (r == c) ? 1.0f : 0.0f;
+#pragma unroll
+    for (int r = 1; r < 16; ++r)
+#pragma unroll
+      for (int k = 0; k < r; ++k) x[r] -= s.a[o + r][o + k] * x[k];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (r > c) s.d[b][r][c] = x[r];
+  }
+  __syncthreads();
+  // entry (i, j) of X_bb and of Y_bb
+  auto xb = [&](int b, int i, int j) { return i <= j ? s.d[b][i][j] : 0.0f; };
+  auto yb = [&](int b, int i, int j) { return i > j ? s.d[b][i][j] : (i == j ? 1.0f : 0.0f); };
+  // t += the product of blocks whose entries (li, k) and (k, li) are given
+  auto mul = [&](f32x4 t, auto left, auto right) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t = Mma<float>::step(left(4 * q + lk), right(4 * q + lk), t);
+    return t;
+  };
+  auto row = [&](int p, int q) { return [&, p, q](int k) { return s.a[16 * p + li][16 * q + k]; }; };
+  auto col = [&](int p, int q) { return [&, p, q](int k) { return s.a[16 * p + k][16 * q + li]; }; };
+  const bool isx = wid < 4;
+  auto level = [&](auto hc) __attribute__((always_inline)) {
+    constexpr int H = decltype(hc)::value;   // blocks per half; H x H blocks for each of 4 / H pairs of halves
+    f32x4 t[H];
+    // the e-th block of this wavefront: (a, r) of X, (r, a) of Y, a in the first half, r in the second (from mid)
+    auto place = [&](int e, int& a, int& r, int& mid) {
+      const int id = (wid & 3) + 4 * e, pair = id / (H * H), i = id % (H * H);
+      mid = (2 * pair + 1) * H;
+      a = mid - H + i / H;
+      r = mid + i % H;
+    };
+    auto put = [&](int e, f32x4 v) {
+      int a, r, mid;
+      place(e, a, r, mid);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *(isx ? &s.a[16 * a + 4 * lk + i][16 * r + li] : &s.a[16 * r + 4 * lk + i][16 * a + li]) = v[i];
+    };
+#pragma unroll
+    for (int e = 0; e < H; ++e) {
+      int a, r, mid;
+      place(e, a, r, mid);
+      t[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (isx) {
+        t[e] = mul(t[e], [&](int k) { return xb(a, li, k); }, col(a, r));
+        for (int m = a + 1; m < mid; ++m) t[e] = mul(t[e], row(a, m), col(m, r));
+      } else {
+        t[e] = mul(t[e], row(r, a), [&](int k) { return yb(a, k, li); });
+        for (int m = a + 1; m < mid; ++m) t[e] = mul(t[e], row(r, m), col(m, a));
+      }
+    }
+    __syncthreads();   // U12 and L21 are used up: the products in their places
+#pragma unroll
+    for (int e = 0; e < H; ++e) put(e, t[e]);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < H; ++e) {
+      int a, r, mid;
+      place(e, a, r, mid);
+      t[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (isx) {
+        t[e] = mul(t[e], row(a, r), [&](int k) { return xb(r, k, li); });
+        for (int m = mid; m < r; ++m) t[e] = mul(t[e], row(a, m), col(m, r));
+      } else {
+        t[e] = mul(t[e], [&](int k) { return yb(r, li, k); }, col(r, a));
+        for (int m = mid; m < r; ++m) t[e] = mul(t[e], row(r, m), col(m, a));
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < H; ++e) put(e, -t[e]);
+    __syncthreads();
+  };
+  level(std::integral_constant<int, 1>());
+  level(std::integral_constant<int, 2>());
+  level(std::integral_constant<int, 4>());
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {   // column-major, 4 x 4 blocks transposed in registers
+    const int j4 = 4 * (tid >> 5) + 64 * u, b = i4 >> 4;
+    float v[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 w = *reinterpret_cast<const float4*>(&s.a[i4 + i][j4]);
+      v[i][0] = w.x, v[i][1] = w.y, v[i][2] = w.z, v[i][3] = w.w;
+    }
+    if (b == j4 >> 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[i][j] = s.d[b][(i4 & 15) + i][(j4 & 15) + j];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<float4*>(out + (size_t)(j4 + j) * NB + i4) = make_float4(v[0][j], v[1][j], v[2][j], v[3][j]);
+  }
 }
 
 // lmax (may be NULL): max |L21| of every row, over this panel (first) or with
@@ -1587,8 +1719,8 @@ __device__ __attribute__((always_inline)) inline void diag_chain(const double (*
 // 16 columns, waited for together or one by one: its vector cache holds 32 KB of
 // outstanding lines, over a latency of 0.85 us), until 256 CUs reach HBM's rate.
 // Per solve, against a chain per diagonal block and whole strips: 100 points, n =
-// 1024, FP32 183 -> 137 us (113 uncorrected: the block's own 64 KB cost 14 us, the two
-// products 10); 256 points, n = 2048, FP32 718 -> 740 (690 uncorrected); 64 points,
+// 1024, FP32 183 -> 135 us (112 uncorrected: the block's own triangle costs 13 us, the
+// two products 10); 256 points, n = 2048, FP32 718 -> 725 (690 uncorrected); 64 points,
 // n = 2048, FP64 990 -> 857; its band form, half-bandwidth 127, 663 -> 351; FP64
 // transposed, 128 points, n = 512: 202 -> 105.
 // ---------------------------------------------------------------------------
@@ -1725,8 +1857,9 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
   // diagonal block of panel q: FP64 the factors' own, thread t holding row t mod 128
   // of the columns t / 128 + 8 u; else the inverses of its triangles (dv) and, CORR,
   // the block (ev), a wavefront holding 16 consecutive columns of half of the rows.
-  // lo, up: the triangles that are wanted; a wavefront with none of their entries
-  // loads none (the halves are dealt so that every SIMD has as many of those)
+  // lo, up: the triangles that are wanted; rows of a wavefront's columns with none of
+  // their entries are not loaded (the halves are dealt so that every SIMD has as many
+  // wavefronts without any)
   constexpr int NS = NB * NB / 1024;
   constexpr bool EV = CORR && !TRANSPOSE;
   D dv[NS];
@@ -1738,8 +1871,8 @@ __global__ __launch_bounds__(1024) void k_solve(const T* __restrict__ LU, const 
   const int c0d = F64 ? dc : NS * dc;
   const bool no_lo = dh == 0 && dc >= 4, no_up = dh == 1 && dc < 4;   // (not FP64)
   auto load_diag = [&](int q, bool lo, bool up) {
-    if constexpr (!F64 && !TRANSPOSE) {
-      if (!((lo & !no_lo) | (up & !no_up))) return;
+    if constexpr (!F64 && !TRANSPOSE) {   // (rows without entries of the triangle, in steps of 16)
+      if (!((lo & (static_cast<int>(dr) >= c0d)) | (up & (static_cast<int>(dr) < c0d + NS)))) return;
     }
     const T* block = A + (size_t)(q * NB + c0d) * npad + q * NB;
     const D* first;
@@ -2228,7 +2361,7 @@ void factor_impl(const DevOps& d, hipStream_t s, LuTimer* tm, int m0, int nmat, 
     }
   }
   if constexpr (std::is_same<T, float>::value) {
-    if (!early) k_diag_inv<<<dim3(np, nmat), kDiagThreads, 0, s>>>(LU, ti, d.npad);
+    if (!early) k_diag_inv<<<dim3(np, nmat), 512, 0, s>>>(LU, ti, d.npad);
   }
 }
 
