@@ -540,7 +540,7 @@ __global__ __launch_bounds__(NT) void k_panel(T* __restrict__ LU, int* __restric
 //                  blocks, then seven levels of off-diagonal blocks), half of
 //                  the wavefronts each; both go into the matrix's linv slot
 //                  for L21 and U12, and their triangles into tinv for the
-//                  solves.  A chain of latencies throughout: 56 -> 45 us for up to
+//                  solves (other FP32 factors' by k_diag_inv).  A chain of latencies throughout: 56 -> 45 us for up to
 //                  256 matrices (X, then Y, on 256 threads before);
 //   k_l21_mfma     L21 = A21 X for 128 rows per block: one MFMA product (K =
 //                  128, the zero blocks of X skipped), A21 straight from HBM.
@@ -549,7 +549,7 @@ constexpr float kStaticPivotRel = 9.5367431640625e-07f;   // 2^-20
 
 constexpr int kDiagThreads = 512;
 
-// LDS of the diagonal-block kernels.  During the factorization the block sits
+// LDS of k_diag_static.  During the factorization the block sits
 // column-major in xt (A[c][r]) and u holds the current step's MFMA operands; for
 // the inverses u holds the factored block row-major, and xt the blocks of X =
 // U11^-1 and Y = L11^-1 off the diagonal, both transposed: X's below it (block

@@ -46,11 +46,12 @@ constexpr int NB = kNB;
 // Tiles of 128 x 128, four wavefronts of 64 x 64.  With 32-bit lane offsets
 // beside uniform bases three or four blocks fit on a CU, so that one block's
 // loads and read-modify-write run under another's products.  K = 512 on 256
-// matrices, 1536 trailing columns: 2.07 ms (3.1 TB/s of tile and operand bytes;
-// split bf16 1.91) against 4.64 ms on the FP32 matrix unit, which is bound by
-// its rate; the L-shaped updates of 1920, 1792 and 1664 rows 335, 414 and 489
-// us, 4.4 TB/s, against 344, 542 and 671.  The epilogue without LDS (16 bytes
-// per lane, 64 per column) took 2.26 ms and 370, 449, 515 us; tiles of 256 x 256
+// matrices, 1536 trailing columns, in a loop of its own: 2.07 ms (3.1 TB/s of tile
+// and operand bytes; split bf16 1.91) against 4.64 ms on the FP32 matrix unit, which
+// is bound by its rate; the L-shaped updates of 1920, 1792 and 1664 rows 335, 414 and
+// 489 us, 4.4 TB/s, against 344, 542 and 671.  In the step, behind the kernels that
+// write L21 and U12: 2.23 ms, and 325, 424 and 504 us.  The epilogue without LDS
+// (16 bytes per lane, 64 per column) took 2.26 ms and 370, 449, 515 us; tiles of 256 x 256
 // in one block per CU, with no products under the read-modify-write, 2.6 ms.
 // ---------------------------------------------------------------------------
 using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
